@@ -54,7 +54,8 @@ typedef enum {
 enum { LP_FP64 = 0, LP_FP32_REFINED = 1 };
 enum { LP_W_UNIT = 0, LP_W_GAUSS = 1 };
 
-/* debug_flags: route every particle through the exact slow paths, fix
+/* debug_flags: route every particle through the selection's second kernel
+ * (LP_DEBUG_SORTED_STENCIL) or the Householder refit (LP_DEBUG_QR_FIT), fix
  * the lanes per particle of the fits (see lp_autotune), make the fits
  * read every neighbour from global memory instead of from the tile's
  * neighbours staged in LDS, or dispatch the fits by stencil size class
@@ -101,8 +102,8 @@ typedef struct {
  * LP_W_GAUSS (w = exp(-4 r^2 / R^2)).  ghost_margin: an octant is covered
  * when a neighbour lies beyond ghost_margin * h on every axis (0.5).
  * fallback_tol: stencils with min|r_jj|/max|r_jj| below it (or fewer than 9
- * rows) use a linear fit (1e-12).  debug_flags: LP_DEBUG_* bits (sorted
- * stencil path for every particle, Householder refit for every stencil,
+ * rows) use a linear fit (1e-12).  debug_flags: LP_DEBUG_* bits (the
+ * selection's second kernel for every particle, Householder refit for every stencil,
  * 2 or 4 lanes per particle in the fits, mirror numbering through a
  * separate scan of the per-tile counts as above 2048 tiles of 4,096
  * particles).
@@ -439,7 +440,8 @@ lp_status lp_step_noalloc(void* stream, const lp_config* cfg, int32_t n_sys,
 lp_status lp_sync_status(lp_ctx* ctx, int64_t* index);
 
 /* Diagnostics accumulated since the last call (host int64[8]):
- * particles, mirrors (last stencil build), QR refits, sorted-path stencils,
+ * particles, mirrors (last stencil build), QR refits, stencils selected by
+ * the selection's second kernel,
  * particles below the wall after updates, neighbour-list rebuilds by
  * lp_step; then resets them.  Entries 6 and 7 describe the current
  * neighbour list (0 when there is none): tiles of BLOCK = 256 consecutive
@@ -455,7 +457,7 @@ lp_status lp_stats(lp_ctx* ctx, int64_t* out8);
  * record HIP events on the context's stream around its kernel groups:
  * 0 displacement check and re-sort + list rebuild (with its tile map) or
  * state copy, 1 stencil selection (k_select alone; the mirror kernels
- * before it are in no phase), 2 exact sorted-stencil path, 3 pass-1 fit +
+ * before it are in no phase), 2 the selection's second kernel, 3 pass-1 fit +
  * closure (k_pass1_st), 4 pass-1 QR refits, 5 pass-2 fit + RHS + update
  * (k_pass2_st), 6 pass-2 QR refits; each lp_step then
  * waits for its last event.  lp_profile_read (host double[8], int64 steps)

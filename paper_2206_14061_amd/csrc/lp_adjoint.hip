@@ -236,7 +236,7 @@ __device__ __forceinline__ void adj2_particle(const View& v, const AdjSeed& S,
     const GridInfo& g = v.grid[s];
     const lp_params& prm = v.prm[s];
     const Rec r = load_rec(v, i);
-    const bool staged = ns >= 0 && !(r.mode & MODE_SORTED);
+    const bool staged = ns >= 0;
     const int32_t* tsrc = v.tile_src + tile * STAGE_CAP;
     const bool lin = B.flags[i] & FLAG_LINEAR;
     const double Pi = B.P[i], Ei = B.eta[i];
@@ -484,7 +484,7 @@ __global__ __launch_bounds__(BLOCK * LPP, 1) void k_adj_pass1(View v, AdjBufs B,
         const GridInfo& g = v.grid[s];
         const lp_params& prm = v.prm[s];
         const Rec r = load_rec(v, i);
-        const bool staged = ns >= 0 && !(r.mode & MODE_SORTED);
+        const bool staged = ns >= 0;
         // rows with the velocities of their points (ghosts: u_i)
         // (this lane's share of them)
         auto rows = [&](auto&& body) {

@@ -42,10 +42,8 @@ View make_view(lp_ctx* c, const double* const st[7])
     v.tile_src = w.tile_src;
     v.tile_cnt = w.tile_cnt;
     v.vs = w.vs;
-    v.code = w.code;
     v.rec = w.rec;
     v.kmask = w.kmask;
-    v.hsten = w.hsten;
     v.ghost_margin = c->cfg.ghost_margin;
     v.fallback_tol = c->cfg.fallback_tol;
     v.redo_ratio = 1.0 / c->cfg.cond_max;
@@ -83,7 +81,7 @@ void free_work(Work& w)
     for (int a = 0; a < 3; ++a) f(w.xref[a]);
     f(w.mirror_of); f(w.msrc); f(w.bsum); f(w.cs); f(w.ce);
     f(w.vl); f(w.vcnt); f(w.tile_src); f(w.tile_cnt); f(w.vs);
-    f(w.code); f(w.rec); f(w.kmask); f(w.hsten); f(w.hard); f(w.hard_n);
+    f(w.rec); f(w.kmask); f(w.hard); f(w.hard_n);
     f(w.redo); f(w.redo_n);
     f(w.P); f(w.eta); f(w.hand); f(w.uf);
     for (int a = 0; a < 7; ++a) f(w.adj[a]);
@@ -520,11 +518,14 @@ static lp_status tile_map_fork(lp_ctx* c)
     c->stream = own;
     if (r != LP_OK) return r;
     e = hipEventRecord(c->map_join, c->map_stream);
-    return e == hipSuccess ? LP_OK : hip_fail(c, e, "tile map join");
+    if (e != hipSuccess) return hip_fail(c, e, "tile map join");
+    c->map_forked = true;
+    return LP_OK;
 }
 
 static lp_status tile_map_join(lp_ctx* c)
 {
+    c->map_forked = false;
     const hipError_t e = hipStreamWaitEvent(c->stream, c->map_join, 0);
     return e == hipSuccess ? LP_OK : hip_fail(c, e, "tile map join");
 }

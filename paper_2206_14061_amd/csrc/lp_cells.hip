@@ -475,8 +475,9 @@ __global__ void k_gather7(int64_t n, const int32_t* perm, State7 in, Dest7 out,
     if (p4) {
         // the positions' records, which the list build and the selection read
         double2* r = reinterpret_cast<double2*>(p4 + 4 * i);
-        r[0] = make_double2(v[0], v[1]);
-        r[1] = make_double2(v[2], 0.0);
+        // (+ 0.0: no -0 in a record)
+        r[0] = make_double2(v[0] + 0.0, v[1] + 0.0);
+        r[1] = make_double2(v[2] + 0.0, 0.0);
     }
     if (ids) ids_tmp[i] = ids[j];
 }
@@ -601,10 +602,11 @@ __global__ __launch_bounds__(BLOCK) void k_copy_disp2(int64_t n, int n_sys,
 #pragma unroll
         for (int a = 0; a < 7; ++a) reinterpret_cast<double2*>(dst.a[a])[j] = f[a];
         double2* rec = reinterpret_cast<double2*>(p4 + 4 * i);
-        rec[0] = make_double2(f[0].x, f[1].x);
-        rec[1] = make_double2(f[2].x, 0.0);
-        rec[2] = make_double2(f[0].y, f[1].y);
-        rec[3] = make_double2(f[2].y, 0.0);
+        // (+ 0.0: no -0 in a record)
+        rec[0] = make_double2(f[0].x + 0.0, f[1].x + 0.0);
+        rec[1] = make_double2(f[2].x + 0.0, 0.0);
+        rec[2] = make_double2(f[0].y + 0.0, f[1].y + 0.0);
+        rec[3] = make_double2(f[2].y + 0.0, 0.0);
         r = fmax(r, disp_ratio(grid[sys_of(off, n_sys, i)], f[0].x, f[1].x, f[2].x, qx.x,
                                qy.x, qz.x));
         r = fmax(r, disp_ratio(grid[sys_of(off, n_sys, i + 1)], f[0].y, f[1].y, f[2].y,
@@ -618,8 +620,8 @@ __global__ __launch_bounds__(BLOCK) void k_copy_disp2(int64_t n, int n_sys,
 #pragma unroll
         for (int a = 0; a < 7; ++a) dst.a[a][i] = f[a];
         double2* rec = reinterpret_cast<double2*>(p4 + 4 * i);
-        rec[0] = make_double2(f[0], f[1]);
-        rec[1] = make_double2(f[2], 0.0);
+        rec[0] = make_double2(f[0] + 0.0, f[1] + 0.0);
+        rec[1] = make_double2(f[2] + 0.0, 0.0);
         r = fmax(r, disp_ratio(grid[sys_of(off, n_sys, i)], f[0], f[1], f[2], rx[i], ry[i],
                                rz[i]));
     }
@@ -649,8 +651,8 @@ __global__ __launch_bounds__(BLOCK) void k_copy_disp(int64_t n, int n_sys,
 #pragma unroll
         for (int a = 0; a < 7; ++a) dst.a[a][i] = f[a];
         double2* rec = reinterpret_cast<double2*>(p4 + 4 * i);
-        rec[0] = make_double2(f[0], f[1]);
-        rec[1] = make_double2(f[2], 0.0);
+        rec[0] = make_double2(f[0] + 0.0, f[1] + 0.0);
+        rec[1] = make_double2(f[2] + 0.0, 0.0);
         r = fmax(r, disp_ratio(grid[sys_of(off, n_sys, i)], f[0], f[1], f[2], rx[i], ry[i],
                                rz[i]));
     }

@@ -124,12 +124,8 @@ __device__ __forceinline__ double fit_row(const View& v, const GridInfo& g, int6
     ghost = false;
     const int ng = __popc((unsigned)r.gm & 0xFFu);
     if (row < r.m) {
-        if (r.mode & MODE_SORTED) {
-            pt = id_point(v, g, v.hsten[(int64_t)row * n + i], xi, yi);
-        } else {
-            const int k = mask_select(r, row);
-            pt = list_point(v, g, v.vl[vl_at(n, i, k)], xi, yi);
-        }
+        const int k = mask_select(r, row);
+        pt = list_point(v, g, v.vl[vl_at(n, i, k)], xi, yi);
         const double dx = dsub(pt.x, xi), dy = dsub(pt.y, yi), dz = dsub(pt.z, zi);
         taylor_row3(dx * g.inv_h, dy * g.inv_h, dz * g.inv_h, a);
         double sw = 1.0;

@@ -391,9 +391,9 @@ __global__ __launch_bounds__(BLOCK, 2) void k_pass1(View v, StepOut o,
 // Pass 1 with the neighbours of the block's tile staged in LDS (one lane
 // per particle): the positions and velocities of the tile's list sources
 // are loaded once, coalesced, and every stencil row reads them from LDS.
-// A tile that is not staged, and a particle on the sorted path, read their
-// neighbours from global memory as k_pass1<1> does, and so does every
-// tile when the tile map is stale (map_ok = 0).  UNIT: the weights are unit
+// A tile that is not staged reads its neighbours from global memory as
+// k_pass1<1> does, and so does every tile when the tile map is stale
+// (map_ok = 0).  UNIT: the weights are unit
 // (known at compile time).
 template <bool UNIT>
 // skip_rows > 0: particles whose stencils have at most skip_rows rows
@@ -435,7 +435,7 @@ __global__ __launch_bounds__(BLOCK, 2) void k_pass1_st(View v, StepOut o,
         }
     };
     int mt;
-    if (S >= 0 && !(r.mode & MODE_SORTED)) {
+    if (S >= 0) {
         mt = for_rows_staged<FIT_BATCH, UNIT>(v, g, i, r, sx, sy, sz,
                                         [&](const double* a, double w, const Pt* p) {
             moments_add(M, a, w);
@@ -606,9 +606,9 @@ __global__ __launch_bounds__(BLOCK) void k_pass2(View v, const double* P,
 // Pass 2 with the neighbours of the block's tile staged in LDS (one lane
 // per particle): positions, P, eta and the pressure a mirror of each list
 // source carries are loaded once, coalesced, and every stencil row reads
-// them from LDS.  A tile that is not staged, and a particle on the sorted
-// path, read their neighbours from global memory as k_pass2<1> does, and
-// so does every tile when the tile map is stale (map_ok = 0).  UNIT: the
+// them from LDS.  A tile that is not staged reads its neighbours from
+// global memory as k_pass2<1> does, and so does every tile when the tile
+// map is stale (map_ok = 0).  UNIT: the
 // weights are unit (known at compile time).
 template <bool UNIT>
 __global__ __launch_bounds__(BLOCK) void k_pass2_st(View v, const double* P,
@@ -646,7 +646,7 @@ __global__ __launch_bounds__(BLOCK) void k_pass2_st(View v, const double* P,
             yE[q] += a[q] * bE;
         }
     };
-    if (S >= 0 && !(r.mode & MODE_SORTED)) {
+    if (S >= 0) {
         for_rows_staged<PASS2_BATCH, UNIT>(v, g, i, r, sx, sy, sz,
                                      [&](const double* a, double w, const Pt* p) {
             if (!p) add_y(a, w, 0.0, 0.0);
@@ -738,7 +738,7 @@ __global__ __launch_bounds__(BLOCK, 2) void k_pass1_ref(View v, StepOut o, float
     const GridInfo& g = v.grid[s];
     const Rec r = load_rec(v, i);
     const double ui = v.u[i], vi = v.v[i], wi = v.w[i];
-    const bool staged = S >= 0 && !(r.mode & MODE_SORTED);
+    const bool staged = S >= 0;
     // body(a, w, has, uj, vj, wj) for every row, bt.value rows at a time:
     // has is false for a ghost row, which carries u_i
     auto rows = [&](auto bt, auto&& body) -> int {
@@ -883,7 +883,7 @@ __global__ __launch_bounds__(BLOCK, 2) void k_pass2_ref(View v, const double* P,
     const Rec r = load_rec(v, i);
     const bool lin = fl & FLAG_LINEAR;
     const double Pi = P[i], Ei = eta[i];
-    const bool staged = S >= 0 && !(r.mode & MODE_SORTED);
+    const bool staged = S >= 0;
     // body(a, w, Pj, Ej) for every row (what pass2_values gives), bt.value
     // rows at a time
     auto rows = [&](auto bt, auto&& body) {

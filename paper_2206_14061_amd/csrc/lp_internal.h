@@ -14,11 +14,6 @@ namespace lp {
 constexpr int NCOEF = 9;          // unknowns of the 2nd-order 3D fit
 constexpr int MMAX_LIMIT = 64;    // largest supported stencil cap
 constexpr int MAXROWS = MMAX_LIMIT + 8;
-constexpr int HIST_BUCKETS = 64;  // r^2 histogram of the stencil selection
-#ifndef LP_LIST_CAP
-#define LP_LIST_CAP 16
-#endif
-constexpr int LIST_CAP = LP_LIST_CAP;  // cut-bucket members ranked per thread
 constexpr int VCAP = 256;         // neighbour-list entries per particle
 constexpr int MASK_WORDS = VCAP / 64;  // keep bitmask words per particle
 // Neighbour-list layout: a particle's entries come in chunks of VCHUNK
@@ -48,6 +43,28 @@ __device__ __forceinline__ void vl_load(const int32_t* vl, int64_t n, int64_t i,
         e[4 * w + 3] = a.w;
     }
 }
+// Slot words (16 bits per list entry) come in chunks of four entries of a
+// particle (8 bytes), chunk c of every particle before chunk c + 1.
+__host__ __device__ __forceinline__ int64_t vs_at(int64_t n, int64_t i, int k)
+{
+    return ((int64_t)(k >> 2) * n + i) * 4 + (k & 3);
+}
+// entries k0 .. k0 + 3 (k0 a multiple of 4), one 8-byte access
+__device__ __forceinline__ void vs_load4(const uint16_t* vs, int64_t n, int64_t i, int k0,
+                                         uint32_t* w)
+{
+    const uint2 a = *reinterpret_cast<const uint2*>(vs + vs_at(n, i, k0));
+    w[0] = a.x & 0xFFFFu;
+    w[1] = a.x >> 16;
+    w[2] = a.y & 0xFFFFu;
+    w[3] = a.y >> 16;
+}
+__device__ __forceinline__ void vs_store4(uint16_t* vs, int64_t n, int64_t i, int k0,
+                                          const uint32_t* w)
+{
+    *reinterpret_cast<uint2*>(vs + vs_at(n, i, k0)) =
+        make_uint2(w[0] | (w[1] << 16), w[2] | (w[3] << 16));
+}
 // A tile is BLOCK consecutive particles.  The fits stage the fields of the
 // distinct sources of a tile's neighbour lists in LDS (at most STAGE_CAP
 // of them); a list entry names its source's slot in a 16-bit word whose
@@ -60,13 +77,9 @@ constexpr uint32_t SLOT_MIRROR = 0x8000u;
 constexpr int32_t MBIT = 0x40000000;  // list entry: mirror of the real id
 constexpr int32_t NOID = 0x7FFFFFFF;
 // per-particle stencil record (int32 fields, field f of particle i at
-// f*n + i): kept rows, ghost mask, mode; the kept list entries themselves
+// f*n + i): kept rows, ghost mask; the kept list entries themselves
 // are a bitmask over the particle's neighbour list (word q at q*n + i)
-constexpr int REC_M = 0, REC_GM = 1, REC_MODE = 2, REC_FIELDS = 3;
-constexpr int MODE_ALL = 1, MODE_SORTED = 8;
-constexpr uint8_t NO_CAND = 0xFF; // key code of a list entry outside R
-constexpr int HARD_CAP = 256;     // candidates the sorted stencil path holds
-constexpr int HARD_BLOCKS = 1024; // blocks of the sorted path (a wave per particle)
+constexpr int REC_M = 0, REC_GM = 1, REC_FIELDS = 2;
 constexpr int HAND = 37;          // pass-1 -> pass-2 handoff doubles
 // stencil size classes of the fits (rows, ghosts included): at most 16,
 // at most 32, more
@@ -158,13 +171,9 @@ struct View {
     const int32_t* tile_src;
     const int32_t* tile_cnt;
     const uint16_t* vs;
-    uint32_t* code;             // r^2 buckets of the list entries, four per word
-                                // (entry k: byte k % 4 of word (k / 4) n + i;
-                                // NO_CAND: outside R)
-    // stencil records, keep bitmasks and explicit stencils of the sorted path
+    // stencil records and keep bitmasks
     int32_t* rec;
     uint64_t* kmask;            // MASK_WORDS x n
-    int32_t* hsten;             // m_max x n
     double ghost_margin;
     double fallback_tol;
     double redo_ratio;          // Gram pivot ratio that triggers a QR refit
@@ -208,10 +217,8 @@ struct Work {
     int32_t* tile_src = nullptr;          // tiles x STAGE_CAP
     int32_t* tile_cnt = nullptr;          // tiles
     uint16_t* vs = nullptr;               // VCAP x n
-    uint32_t* code = nullptr;             // VCAP / 4 x n
     int32_t* rec = nullptr;
     uint64_t* kmask = nullptr;            // MASK_WORDS x n
-    int32_t* hsten = nullptr;
     int32_t* hard = nullptr;
     unsigned int* hard_n = nullptr;
     // fits
@@ -272,9 +279,8 @@ constexpr void work_layout(Work& w, int64_t n_max, int64_t cells_max, int mm,
     A(w.tile_src, (int64_t)STAGE_CAP * tiles);
     A(w.tile_cnt, tiles);
     A(w.vs, (int64_t)VCAP * n_max);
-    A(w.code, (int64_t)(VCAP / 4) * n_max);
     A(w.kmask, (int64_t)MASK_WORDS * n_max);
-    A(w.rec, (int64_t)REC_FIELDS * n_max); A(w.hsten, (int64_t)mm * n_max);
+    A(w.rec, (int64_t)REC_FIELDS * n_max); 
     A(w.hard, n_max); A(w.hard_n, 1);
     A(w.redo, n_max); A(w.redo_n, 1);
     A(w.P, n_max); A(w.eta, n_max); A(w.hand, (int64_t)HAND * n_max);
@@ -344,6 +350,7 @@ struct lp_ctx {
     // selection, which do not read it; the fits wait for map_join
     hipStream_t map_stream = nullptr;
     hipEvent_t map_fork = nullptr, map_join = nullptr;
+    bool map_forked = false;    // the map is being built on the side stream
     bool map_side = true;       // false: the allocation-free step's context
                                 // (which creates no stream) builds it in line
     // captured step sequence (lp_step_graph) and what it was captured for
@@ -504,7 +511,7 @@ lp_status list_check_wait(lp_ctx* c, double* ratio);
 // (written by the step's state copy or re-sort).  part: STENCIL_ALL, or
 // STENCIL_HEAD (mirrors and the histogram selection, which a step enqueues
 // before it knows whether the list must be rebuilt) and then STENCIL_TAIL
-// (the exact path for the particles the selection handed over).
+// (the particles the selection handed over to its second kernel).
 enum { STENCIL_ALL = 0, STENCIL_HEAD = 1, STENCIL_TAIL = 2 };
 lp_status stencils_build(lp_ctx* c, const double* const st[7], bool packed = false,
                          int part = STENCIL_ALL);

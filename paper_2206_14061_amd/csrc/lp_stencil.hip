@@ -13,38 +13,21 @@
 // lists and serves as the check of the former.
 //
 // Stencil selection (nearest candidate of each octant, then the nearest
-// others by key (r^2, id), m_max in all), one thread per particle, without
-// storing or sorting the candidates:
-//   pass 1: exact test of every list entry, count, octant coverage bits,
-//           a histogram of r^2 in 64 buckets of R^2/64 (byte counters in
-//           LDS) and the lowest bucket of each octant (which holds the
-//           octant's first); each entry's bucket is stored as one byte;
-//           the bucket holding the cut follows from the histogram;
-//   pass 2: entries of lower buckets are kept (with them every octant
-//           first below the cut); when the cut falls inside its bucket,
-//           that bucket's few members are collected in a per-thread LDS
-//           list, the firsts among them found and the rest ranked exactly
-//           by key; an octant whose first lies above the cut (rare) gets
-//           it from a scan of that one bucket.
-// The result is a keep bitmask over the list entries (plus row count and
-// ghost mask); the fits walk its set bits.  Bucketing is monotone in r^2,
-// so the kept set equals the one a full sort by (r^2, id) gives.
-// Particles whose cut bucket holds more members than the LDS list, or with
-// more than 255 candidates, take a slower path that sorts all candidates.
-#include "lp_visit.h"
+// others by key (r^2, id), m_max in all), a few adjacent lanes per particle,
+// without storing or sorting the candidates: every list entry's exact test
+// leaves a 16-bit key (r^2 in units of R^2/65534; monotone) and its octant
+// in the lanes' registers, and the cut is the key value below which exactly
+// m_max candidates lie, found by counting (k_select).  The result is a keep
+// bitmask over the list entries (plus row count and ghost mask); the fits
+// walk its set bits.
+#include <algorithm>
+#include <type_traits>
 
-#ifndef LP_SEL_BATCH
-#define LP_SEL_BATCH 8
-#endif
+#include "lp_visit.h"
 
 namespace lp {
 
 namespace {
-
-// List entries whose positions the selection gathers together.
-constexpr int SEL_BATCH = LP_SEL_BATCH;
-static_assert(SEL_BATCH % 4 == 0 && SEL_BATCH <= 8 && VCAP % SEL_BATCH == 0,
-              "selection batches cover whole bucket-code words and one mask byte");
 
 inline unsigned int blocks_for(int64_t n, int per = BLOCK)
 {
@@ -474,7 +457,7 @@ constexpr int MIRROR_WAVES = BLOCK / 64;
 static_assert(SORT_TILE == MIRROR_WAVES * 64 * SORT_ITEMS, "a tile per block");
 
 // Also clears the step's counters: the selection's list of particles for
-// the sorted path, the fits' refit list and the displacement maximum of
+// its second kernel, the fits' refit list and the displacement maximum of
 // the next list check (read by the host before this kernel is enqueued).
 __global__ void k_mirror_count(int64_t n, int n_sys, const int64_t* off,
                                const GridInfo* grid, const double* z,
@@ -588,89 +571,7 @@ __global__ void k_mirror_write(int64_t n, int n_sys, const int64_t* off,
     }
 }
 
-// ---- stencil selection ---------------------------------------------------
-
-__device__ __forceinline__ int hist_get(const uint32_t (*hist)[BLOCK], int b, int t)
-{
-    return (int)((hist[b >> 2][t] >> (8 * (b & 3))) & 255u);
-}
-
-__device__ __forceinline__ void hist_add(uint32_t (*hist)[BLOCK], int b, int t,
-                                         int d)
-{
-    hist[b >> 2][t] += (uint32_t)d << (8 * (b & 3));
-}
-
-// First bucket whose cumulative count reaches K; need = how many of its
-// members are kept, hc = its count.
-__device__ __forceinline__ int cut_bucket(const uint32_t (*hist)[BLOCK], int t,
-                                          int K, int& need, int& hc)
-{
-    int cum = 0;
-    for (int b = 0; b < HIST_BUCKETS; ++b) {
-        hc = hist_get(hist, b, t);
-        if (cum + hc >= K) {
-            need = K - cum;
-            return b;
-        }
-        cum += hc;
-    }
-    need = 0;
-    hc = 0;
-    return HIST_BUCKETS;
-}
-
-// keep mask over the list entries of one particle (VCAP bits)
-struct Mask4 {
-    uint64_t w0 = 0, w1 = 0, w2 = 0, w3 = 0;
-    __device__ __forceinline__ void set(int k)
-    {
-        const uint64_t b = 1ull << (k & 63);
-        if (k < 64)
-            w0 |= b;
-        else if (k < 128)
-            w1 |= b;
-        else if (k < 192)
-            w2 |= b;
-        else
-            w3 |= b;
-    }
-    // bits of `bits` at entries k0, k0 + 1, ... (W bits, k0 a multiple
-    // of W, W dividing 64)
-    template <int W = 8>
-    __device__ __forceinline__ void set_bits(int k0, uint32_t bits)
-    {
-        const uint64_t b = (uint64_t)(bits & ((1u << W) - 1u)) << (k0 & 63);
-        if (k0 < 64)
-            w0 |= b;
-        else if (k0 < 128)
-            w1 |= b;
-        else if (k0 < 192)
-            w2 |= b;
-        else
-            w3 |= b;
-    }
-    __device__ __forceinline__ bool has(int k) const
-    {
-        const uint64_t w = k < 64 ? w0 : (k < 128 ? w1 : (k < 192 ? w2 : w3));
-        return (w >> (k & 63)) & 1ull;
-    }
-};
-
-__device__ __forceinline__ void write_rec(const View& v, int64_t i, int m, int gm,
-                                          int mode, const Mask4& mk)
-{
-    static_assert(MASK_WORDS == 4, "four keep-mask words");
-    const int64_t n = v.n;
-    int32_t* q = v.rec;
-    q[REC_M * n + i] = m;
-    q[REC_GM * n + i] = gm;
-    q[REC_MODE * n + i] = mode;
-    v.kmask[i] = mk.w0;
-    v.kmask[n + i] = mk.w1;
-    v.kmask[2 * n + i] = mk.w2;
-    v.kmask[3 * n + i] = mk.w3;
-}
+// ---- exact candidates of a particle ------------------------------------
 
 // Calls f(pt, dx, dy, dz, r2) for every candidate of particle i.
 template <class F>
@@ -690,400 +591,711 @@ __device__ __forceinline__ void for_candidates(const View& v, const GridInfo& g,
     }
 }
 
-// The points of the SEL_BATCH list entries k0, k0 + 1, ... of particle i
-// for the exact candidate test: positions from the 32-byte records, a
-// mirror's position reflected and its existence taken from its source's
-// height (a mirror exists while the source lies within R of the wall, the
-// rule that sets mirror_of); no ids.  Entries past cnt are read (every
-// particle holds VCAP list slots, so every read is in bounds) but stand
-// for i itself and are not candidates.  The record offset j * 32 stays below 2^32 (j < 2^27).
-template <bool PERIODIC>
-__device__ __forceinline__ void select_gather(const View& v, const Seen& s,
-                                              const GridInfo& g, int64_t i, int k0,
-                                              int cnt, Pt (&p)[SEL_BATCH])
+// ---- stencil selection ---------------------------------------------------
+//
+// L adjacent lanes per particle; lane `sub` takes the list entries
+// 4 L c + 4 sub + u (chunk c, u = 0..3): one 16-byte load of list words (8
+// bytes of slot words) per chunk, and an entry's bit of the keep mask is
+// 4 L c + 4 sub + u as well.  Every entry is tested exactly once and leaves
+//   - a 15-bit key, r^2 rounded down to units of R^2/32766 (0x7FFF: not a
+//     candidate), two to a register,
+//   - its octant, a nibble;
+// and the group's OR over its entries gives the octants that hold
+// candidates, those that hold one below half of R^2, and those covered.
+// The cut is a key value T with exactly m_max keys below it, found by
+// counting keys below trial values (three packed 16-bit operations per two
+// entries; the first trial from count ~ r^3, then bisection).  The m_max
+// nearest are the stencil when every octant with candidates has one below
+// T, which one below half of R^2 shows for nearly every particle.  Otherwise
+//   - the first of an octant without a candidate below the cut is kept for
+//     itself (forced) and the others are cut again, until no octant is
+//     missing (no particle of a column, 1 % of a sheared one);
+//   - candidates tied at the cut (or for an octant's first) are ranked by
+//     their exact keys (r^2, id) (0.2 % of the particles).
+//
+// What bounds it: a thread per particle (r^2 buckets in LDS, two passes)
+// waited for memory up to 131,072 particles (54 us at 4,096, 60 at 33,263,
+// 73 at 131,072), and above for its uncoalesced gathers and 7,300 VALU
+// instructions per wavefront (106 us at 262,144, 188 at 524,288, 781 on the
+// sheared 1,048,576).  With L lanes the chains are L times shorter and the
+// lists are read coalesced: 11 us (L = 16), 20 (L = 8), 47 (L = 8).  Above
+// that the vector ALU bounds it (L = 4: 1,840 instructions per 16 particles,
+// 98 us of issue at 524,288) once the gathers go to the tile's sources in
+// LDS: 66, 119 and 394 us (76, 136 and 427 from the records).  There the rare
+// cases take a kernel of their own (k_select_rest, 13 us): with them the
+// four-lane form needs 150 registers and 87 us at 262,144.
+typedef short s16x2 __attribute__((ext_vector_type(2)));
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t x)
 {
-    const int64_t n = v.n;
-    int32_t e[SEL_BATCH];
-    vl_load(v.vl, n, i, k0, e);
-#pragma unroll
-    for (int u = 0; u < SEL_BATCH; ++u) e[u] = k0 + u < cnt ? e[u] : (int32_t)i;
-    const char* base = reinterpret_cast<const char*>(v.p4);
-#pragma unroll
-    for (int u = 0; u < SEL_BATCH; ++u) {
-        const uint32_t off = (uint32_t)(e[u] & ~MBIT) << 5;
-        const double* r = reinterpret_cast<const double*>(base + off);
-        const double2 xy = *reinterpret_cast<const double2*>(r);
-        p[u].x = xy.x;
-        p[u].y = xy.y;
-        p[u].z = r[2];
-        p[u].mirror = (e[u] & MBIT) != 0;
-    }
-#pragma unroll
-    for (int u = 0; u < SEL_BATCH; ++u) {
-        const double zs = p[u].z;
-        p[u].valid = !p[u].mirror || dsub(zs, g.wall) < g.R;
-        p[u].z = p[u].mirror ? dsub(s.wall2, zs) : zs;
-        if (PERIODIC) {
-            p[u].x = image_coord(p[u].x, s.xi, s.Lx, s.hLx);
-            p[u].y = image_coord(p[u].y, s.yi, s.Ly, s.hLy);
-        }
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, false);
+}
+
+// f over the L lanes of a group, the same value in every lane: swaps of
+// neighbours and pairs inside quads, then the half-row and row mirrors.
+template <int L, class F>
+__device__ __forceinline__ uint32_t group_red(uint32_t x, F&& f)
+{
+    static_assert(L == 2 || L == 4 || L == 8 || L == 16, "lanes of one DPP row");
+    x = f(x, dpp_u32<0xB1>(x));
+    if (L >= 4) x = f(x, dpp_u32<0x4E>(x));
+    if (L >= 8) x = f(x, dpp_u32<0x141>(x));
+    if (L >= 16) x = f(x, dpp_u32<0x140>(x));
+    return x;
+}
+template <int L>
+__device__ __forceinline__ uint32_t group_add(uint32_t x)
+{
+    return group_red<L>(x, [](uint32_t a, uint32_t b) { return a + b; });
+}
+template <int L>
+__device__ __forceinline__ uint32_t group_or(uint32_t x)
+{
+    return group_red<L>(x, [](uint32_t a, uint32_t b) { return a | b; });
+}
+template <int L>
+__device__ __forceinline__ uint32_t group_min(uint32_t x)
+{
+    return group_red<L>(x, [](uint32_t a, uint32_t b) { return a < b ? a : b; });
+}
+
+// f(integral_constant<int, K>) for K = B .. E-1, in order
+template <int B, int E, class F>
+__device__ __forceinline__ void static_for(F&& f)
+{
+    if constexpr (B < E) {
+        f(std::integral_constant<int, B>{});
+        static_for<B + 1, E>(f);
     }
 }
 
-template <bool PERIODIC>
-__global__ __launch_bounds__(BLOCK) void k_select(View v, int32_t* hard,
-                                                  unsigned int* hard_n,
-                                                  int force_sorted)
+// A value that is the same in all active lanes, as a scalar.
+__device__ __forceinline__ double scalar(double x)
 {
-    __shared__ uint32_t hist[HIST_BUCKETS / 4][BLOCK];
-    // cut-bucket members, one word each: r^2 rounded to float with its
-    // low 8 bits replaced by the list index.  Rounding and truncation are
-    // monotone, so a smaller word means a smaller r^2; equal truncated
-    // keys take the exact keys again.  loct: their octants (bit 7: the
-    // member is its octant's first).
-    __shared__ uint32_t lkey[LIST_CAP][BLOCK];
-    __shared__ uint8_t loct[LIST_CAP][BLOCK];
-    const int t = threadIdx.x;
-    const int64_t i = xcd_block(blockIdx.x, gridDim.x) * BLOCK + t;
-    if (i >= v.n) return;
+    return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(x)),
+                            __builtin_amdgcn_readfirstlane(__double2loint(x)));
+}
+
+// Hides a value's origin from the compiler.
+__device__ __forceinline__ void hide(uint32_t& x) { asm volatile("" : "+v"(x)); }
+
+constexpr uint32_t NO_KEY = 0x7FFFu;     // key of an entry that is no candidate
+constexpr uint32_t HALF_KEY = 0x4000u;   // keys below: r^2 < R^2/2 (about)
+
+// -1 in each half whose key is below T's (both in [0, 0x7FFF])
+__device__ __forceinline__ s16x2 key_below(uint32_t pair, s16x2 T)
+{
+    return (__builtin_bit_cast(s16x2, pair) - T) >> 15;
+}
+
+// LDS for the tied candidates of one group (cap >= 16).
+struct TieList {
+    double* r2;
+    int32_t* id;
+    int cap;
+};
+
+// The selection of particle i by a group of L lanes (lane `sub`).  STAGED:
+// the positions of the tile's list sources are in (sx, sy, sz), and an
+// entry's is read through its slot word; else they are gathered from the
+// 32-byte records.  FULL: with every case of the rule; else a particle that
+// needs that is appended to `hard`.
+template <int L, bool STAGED, bool PERIODIC, bool FULL>
+__device__ __forceinline__ void select_particle(const View& v, int64_t i, int sub,
+                                                const double* sx, const double* sy,
+                                                const double* sz, TieList ties, int32_t* hard,
+                                                unsigned int* hard_n, int force_rest)
+{
+    constexpr int NCH = VCAP / (4 * L);      // chunks of a full list
     const int64_t n = v.n;
-    const GridInfo& g = v.grid[sys_of(v.off, v.n_sys, i)];
-    const double margin = dmul(v.ghost_margin, g.h);
-    const double scale = (double)HIST_BUCKETS / g.R2;
-    const double R2 = g.R2;
-    uint32_t* __restrict__ code = v.code;
-    const Seen s = seen_from(v, g, i);
+    // One system after another where a wavefront's particles lie in several
+    // (a group's lanes share theirs), so that its constants are scalars.
+    const int sys = sys_of(v.off, v.n_sys, i);
+    for (bool todo = true; todo;) {
+    const int s0 = __builtin_amdgcn_readfirstlane(sys);
+    if (sys != s0) continue;
+    todo = false;
+    const GridInfo& g = v.grid[s0];
+    const double margin = scalar(dmul(v.ghost_margin, g.h));
+    const double R = scalar(g.R), R2 = scalar(g.R2), wall = scalar(g.wall);
+    const double kscale = scalar((1.0 - 1.0 / 16384.0) / g.R2);
+    // no -0 among these (nor in the records), so that no difference is -0 and
+    // an octant follows from sign bits
+    Seen s;
+    s.xi = v.x[i] + 0.0;
+    s.yi = v.y[i] + 0.0;
+    s.zi = v.z[i] + 0.0;
+    s.wall2 = scalar(dmul(2.0, g.wall) + 0.0);
+    s.Lx = scalar(g.Lx);
+    s.hLx = scalar(g.hLx);
+    s.Ly = scalar(g.Ly);
+    s.hLy = scalar(g.hLy);
     const double xi = s.xi, yi = s.yi, zi = s.zi;
-    const int cnt = v.vcnt[i];
-#pragma unroll
-    for (int q = 0; q < HIST_BUCKETS / 4; ++q) hist[q][t] = 0u;
+    // entry 4 L c + 4 sub + u is in the list when left > 4 L c + u
+    const int left = v.vcnt[i] - 4 * sub;
 
-    // ---- pass 1: exact test of every list entry, SEL_BATCH entries at a
-    // time (their list words, then their positions, all in flight
-    // together); the buckets are stored four to a word (word k / 4 of all
-    // lanes at once: coalesced).  Per octant only the lowest bucket is
-    // tracked: it holds the octant's first.  Those minima are LDS words
-    // of the thread's member column (unused until the keep pass), lowered
-    // with no-return atomic minima.
-    int nc = 0, covered = 0;
-    Mask4 cm;                          // candidate entries
+    // ---- exact test of every entry
+    uint32_t key[2 * NCH];               // entries (0, 1) and (2, 3) of a chunk
+    uint32_t octs[(NCH + 1) / 2];        // octant nibbles, eight entries each
 #pragma unroll
-    for (int o = 0; o < 8; ++o) lkey[o][t] = 0xFFu;
-    for (int k0 = 0; k0 < cnt; k0 += SEL_BATCH) {
-        Pt pb[SEL_BATCH];
-        select_gather<PERIODIC>(v, s, g, i, k0, cnt, pb);
-        uint32_t cw[SEL_BATCH / 4];
+    for (int c = 0; c < (NCH + 1) / 2; ++c) octs[c] = 0u;
+    // octants: bits 0-7 with candidates, 8-15 with one below HALF_KEY, 16-23
+    // covered (a candidate farther than margin on every axis)
+    uint32_t seen = 0u;
+    int nact = 0;                        // chunks in use in this wavefront
+    // a mirror exists while its source lies within R of the wall (the rule
+    // that sets mirror_of) and sits at its reflection
+    auto reflect = [&](double z) {
+        return dsub(z, wall) < R ? dsub(s.wall2, z) : (double)INFINITY;
+    };
+    // the entries 2 h, 2 h + 1 of chunk c at positions (px, py, pz) of the
+    // sources (infinite: no entry).  Every entry takes the same instructions
+    // (no divergent branches).
+    auto test2 = [&](auto C, auto Hh, const double* px, const double* py, const double* pz) {
+        constexpr int c = decltype(C)::value, h = decltype(Hh)::value;
+        uint32_t kk[2];
 #pragma unroll
-        for (int w = 0; w < SEL_BATCH / 4; ++w) cw[w] = 0xFFFFFFFFu;
-        // Every entry of the batch takes the same instructions, predicated
-        // on being a candidate (no divergent branches): the histogram gets
-        // a no-return LDS add of 0 or 1, the other updates are selects.
-        uint32_t bm = 0;               // candidates among the batch
-#pragma unroll
-        for (int u = 0; u < SEL_BATCH; ++u) {
-            const Pt& p = pb[u];
-            const double dx = dsub(p.x, xi), dy = dsub(p.y, yi), dz = dsub(p.z, zi);
+        for (int u = 0; u < 2; ++u) {
+            const double x = PERIODIC ? image_coord(px[u], xi, s.Lx, s.hLx) : px[u];
+            const double y = PERIODIC ? image_coord(py[u], yi, s.Ly, s.hLy) : py[u];
+            const double dx = dsub(x, xi), dy = dsub(y, yi), dz = dsub(pz[u], zi);
             const double d2 = dist2(dx, dy, dz);
-            const bool c = k0 + u < cnt && p.valid && d2 < R2;
-            nc += c ? 1 : 0;
-            bm |= c ? 1u << u : 0u;
-            // a candidate farther than margin (>= 0) from i on every axis
-            // covers its octant (no zero component, so octant_of is exact)
-            const int oct = octant_of(dx, dy, dz);
-            const bool far = fabs(dx) > margin && fabs(dy) > margin && fabs(dz) > margin;
-            covered |= (c && far) ? 1 << oct : 0;
-            const int bi = bucket_of(d2, scale);
-            const uint32_t b = (uint32_t)(bi < 0 ? 0 : bi);
-            atomicMin(&lkey[oct][t], c ? b : 0xFFu);
-            atomicAdd(&hist[b >> 2][t], (c ? 1u : 0u) << (8u * (b & 3u)));
-            const uint32_t cs = 8u * (uint32_t)(u & 3);
-            cw[u >> 2] = c ? (cw[u >> 2] & ~(0xFFu << cs)) | (b << cs) : cw[u >> 2];
+            const bool cand = d2 < R2;
+            // octant_of, complemented (the sign bits)
+            const uint32_t no = (uint32_t)__double2hiint(dx) >> 31 |
+                                ((uint32_t)__double2hiint(dy) >> 31) << 1 |
+                                ((uint32_t)__double2hiint(dz) >> 31) << 2;
+            const bool far = (int)cand & (int)(fabs(dx) > margin) & (int)(fabs(dy) > margin) &
+                             (int)(fabs(dz) > margin);
+            const uint32_t hi = (uint32_t)__double2hiint(__builtin_fma(d2, kscale, 1.0));
+            const uint32_t kq = (hi >> 5) & 0x7FFFu;
+            kk[u] = cand ? kq : NO_KEY;
+            uint32_t w = cand ? 1u : 0u;
+            w = kk[u] < HALF_KEY ? 0x101u : w;
+            seen |= w << no;
+            seen |= (far ? 0x10000u : 0u) << no;
+            octs[c / 2] |= no << (16 * (c & 1) + 8 * h + 4 * u);
         }
-        cm.set_bits(k0, bm);
+        key[2 * c + h] = kk[0] | (kk[1] << 16);
+    };
+    if constexpr (STAGED) {
+        // every chunk's slot words are in flight before the first is used
+        const uint2* vs0 = reinterpret_cast<const uint2*>(v.vs + vs_at(n, i, 4 * sub));
+        uint2 w[NCH];
 #pragma unroll
-        for (int w = 0; w < SEL_BATCH / 4; ++w)
-            if (k0 + 4 * w < cnt) code[(int64_t)((k0 >> 2) + w) * n + i] = cw[w];
+        for (int c = 0; c < NCH; ++c) {
+            w[c] = make_uint2(0u, 0u);
+            if (__ballot(left > 4 * L * c) == 0ull) continue;
+            nact = c + 1;
+            w[c] = vs0[(int64_t)c * L * n];
+        }
+        nact = __builtin_amdgcn_readfirstlane(nact);
+        // does some entry of the wavefront stand for a mirror?
+        uint32_t any = 0u;
+        static_for<0, NCH>([&](auto C) {
+            constexpr int c = decltype(C)::value;
+            // a list's last chunk is padded with STAGE_CAP, the words of
+            // chunks past it are arbitrary
+            constexpr uint32_t PAD = (uint32_t)STAGE_CAP | ((uint32_t)STAGE_CAP << 16);
+            if (c < nact) {
+                const bool none = left <= 4 * L * c;
+                w[c].x = none ? PAD : w[c].x;
+                w[c].y = none ? PAD : w[c].y;
+                any |= w[c].x | w[c].y;
+            }
+        });
+        const bool mirrors = __ballot((any & (SLOT_MIRROR | (SLOT_MIRROR << 16))) != 0u) != 0ull;
+        auto run = [&](auto MIR) {
+            static_for<0, NCH>([&](auto C) {
+                constexpr int c = decltype(C)::value;
+                if (c >= nact) {
+                    key[2 * c] = key[2 * c + 1] = NO_KEY | (NO_KEY << 16);
+                    return;
+                }
+                static_for<0, 2>([&](auto Hh) {
+                    const uint32_t ww = Hh.value ? w[c].y : w[c].x;
+                    double px[2], py[2], pz[2];
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        const uint32_t e = u ? ww >> 16 : ww & 0xFFFFu;
+                        const uint32_t q = MIR.value ? e & (SLOT_MIRROR - 1u) : e;
+                        px[u] = sx[q];
+                        py[u] = sy[q];
+                        pz[u] = sz[q];
+                        if (MIR.value) pz[u] = e & SLOT_MIRROR ? reflect(pz[u]) : pz[u];
+                    }
+                    test2(C, Hh, px, py, pz);
+                });
+            });
+        };
+        if (mirrors) run(std::true_type{});
+        else run(std::false_type{});
+    } else {
+        const char* base = reinterpret_cast<const char*>(v.p4);
+        // list words of the next chunk are loaded ahead (every particle
+        // holds VCAP list slots, so every read is in bounds)
+        // (entries 4 sub + 8 a come 8 a n words after entries 4 sub)
+        static_assert(4 * L % VCHUNK == 0 || L == 1, "chunks of whole list chunks");
+        const int4* vl0 = reinterpret_cast<const int4*>(v.vl + vl_at(n, i, 4 * sub));
+        int4 e = vl0[0];
+        static_for<0, NCH>([&](auto C) {
+            constexpr int c = decltype(C)::value;
+            if (__ballot(left > 4 * L * c) == 0ull) {
+                key[2 * c] = key[2 * c + 1] = NO_KEY | (NO_KEY << 16);
+                return;
+            }
+            nact = c + 1;
+            double px[4], py[4], pz[4];
+            bool mir[4];
+            const int32_t ev[4] = {e.x, e.y, e.z, e.w};
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                // entries past the list's end read the particle's own record;
+                // the record offset j * 32 stays below 2^32 (j < 2^27)
+                const int32_t ee = left > 4 * L * c + u ? ev[u] : (int32_t)i;
+                const double* r = reinterpret_cast<const double*>(
+                    base + ((uint32_t)(ee & ~MBIT) << 5));
+                const double2 xy = *reinterpret_cast<const double2*>(r);
+                px[u] = xy.x;
+                py[u] = xy.y;
+                pz[u] = r[2];
+                mir[u] = (ee & MBIT) != 0;
+            }
+            if (c + 1 < NCH) e = vl0[(int64_t)(c + 1) * L * n];
+            if (__ballot(mir[0] || mir[1] || mir[2] || mir[3]))
+#pragma unroll
+                for (int u = 0; u < 4; ++u) pz[u] = mir[u] ? reflect(pz[u]) : pz[u];
+            if (__ballot(left < 4 * L * c + 4))
+#pragma unroll
+                for (int u = 0; u < 4; ++u) pz[u] = left > 4 * L * c + u ? pz[u] : INFINITY;
+            static_for<0, 2>([&](auto Hh) {
+                test2(C, Hh, px + 2 * Hh.value, py + 2 * Hh.value, pz + 2 * Hh.value);
+            });
+        });
+        nact = __builtin_amdgcn_readfirstlane(nact);
     }
-    const int gm = ~covered & 0xFF;
+    seen = group_or<L>(seen);
+    const uint32_t allo = seen & 0xFFu;
+    // (octants count from the sign bits here: octant o is bit 7 - o)
+    const int gm = (int)(__brev(~(seen >> 16) & 0xFFu) >> 24);
+    // f over the chunks in use (and some empty ones): the first TIER chunks
+    // without a branch per chunk, which lists of ordinary length fit in
+    constexpr int TIER = (3 * NCH + 7) / 8;
+    auto chunks = [&](auto&& f) {
+        static_for<0, TIER>(f);
+        if (nact > TIER) static_for<TIER, NCH>(f);
+    };
+    // f(bit 4 c + u, key, octant) for this lane's entries.  For the rare
+    // passes: the words are unpacked each time, as copies whose origin the
+    // compiler does not see (it would keep every unpacked entry in registers
+    // from one pass to the next).
+    auto entries = [&](auto&& f) {
+        chunks([&](auto C) {
+            constexpr int c = decltype(C)::value;
+            uint32_t k0 = key[2 * c], k1 = key[2 * c + 1], oo = octs[c / 2];
+            hide(k0);
+            hide(k1);
+            hide(oo);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                f(4 * c + u, ((u < 2 ? k0 : k1) >> (16 * (u & 1))) & 0xFFFFu,
+                  (oo >> (16 * (c & 1) + 4 * u)) & 7u);
+        });
+    };
+    // keys of the group below T
+    auto below = [&](uint32_t T) -> int {
+        const s16x2 t2 = {(short)T, (short)T};
+        s16x2 acc = {0, 0};
+        chunks([&](auto C) {
+            constexpr int c = decltype(C)::value;
+            acc += key_below(key[2 * c], t2);
+            acc += key_below(key[2 * c + 1], t2);
+        });
+        return (int)group_add<L>((uint32_t)(-(int)acc.x - (int)acc.y));
+    };
+    int nc = below(NO_KEY);
     const int m_max = v.m_max;
-    if (force_sorted || nc > 255) {
-        write_rec(v, i, 0, gm, MODE_SORTED, Mask4());
-        hard[atomicAdd(hard_n, 1u)] = (int32_t)i;
-        return;
-    }
-    if (nc <= m_max) {
-        write_rec(v, i, nc, gm, MODE_ALL, cm);
-        return;
-    }
-    uint32_t mbv[8];
-#pragma unroll
-    for (int o = 0; o < 8; ++o) mbv[o] = lkey[o][t];
-    auto minb = [&](int o) -> uint32_t { return mbv[o]; };
-    int n_oct = 0;
-#pragma unroll
-    for (int o = 0; o < 8; ++o)
-        if (minb(o) != 0xFFu) {
-            ++n_oct;
-            hist_add(hist, (int)minb(o), t, -1);
+    const int m = nc < m_max ? nc : m_max;
+    int K = m_max;                       // candidates to keep below the cut
+    uint32_t T = NO_KEY;                 // the cut
+    int tied = 0, need = 0;              // candidates with key T, those kept
+    auto cut = [&](bool on) {
+        // invariant: below(lo) = cl < K < ch = below(hi)
+        uint32_t lo = 0u, hi = NO_KEY;
+        int cl = 0, ch = nc;
+        bool open = on && nc > K;
+        if (on) {
+            T = nc <= K ? NO_KEY : 0u;
+            tied = need = 0;
         }
-    const int K = m_max - n_oct;
-    int need = 0, hc = 0;
-    const int bstar = K < 0 ? 0 : cut_bucket(hist, t, K, need, hc);
-    // octants whose first lies in the cut bucket (B) or above it (C); the
-    // others' firsts lie below the cut and are kept with their buckets
-    uint32_t octB = 0, octC = 0;
+        if (open && K == 0) open = false;            // T = 0: none
+        uint32_t tr = (uint32_t)(32766.0f * exp2f(0.6666667f * __log2f((float)K / (float)nc)));
+        for (int it = 0; __ballot(open) != 0ull; ++it) {
+            if (it > 0) tr = (lo + hi) >> 1;
+            tr = tr <= lo ? lo + 1u : (tr >= hi ? hi - 1u : tr);
+            const int c = below(tr);
+            if (!open) continue;
+            if (c == K) {
+                T = tr;
+                open = false;
+            } else if (c < K) {
+                lo = tr;
+                cl = c;
+            } else {
+                hi = tr;
+                ch = c;
+            }
+            if (open && hi - lo <= 1u) {
+                T = lo;
+                need = K - cl;
+                tied = ch - cl;
+                open = false;
+            }
+        }
+    };
+    // fewer rows than octants with candidates: their firsts, in octant order
+    const bool few = nc > m_max && __popc(allo) > m_max;
+    if (few) T = 0u;
+    if (__ballot(!few && nc > K)) cut(!few);
+
+    uint64_t kept = 0;                   // this lane's entries kept for themselves
+    if constexpr (!FULL) {
+        bool rest = force_rest || few || tied > 0;
+        // is there an octant whose candidates all lie above the cut?
+        const bool doubt = nc > m_max && (T < HALF_KEY || ((seen >> 8) & 0xFFu) != allo);
+        if (__ballot(doubt) != 0ull) {
+            uint32_t ko = 0u;
+            entries([&](int, uint32_t k, uint32_t o) { ko |= k < T ? 1u << o : 0u; });
+            rest = rest || (doubt && group_or<L>(ko) != allo);
+        }
+        // one atomic per wavefront
+        const uint64_t rb = __ballot(rest && sub == 0);
+        if (rb) {
+            const int lane = (int)(threadIdx.x & 63u), lead = __builtin_ctzll(rb);
+            uint32_t at = 0u;
+            if (lane == lead) at = atomicAdd(hard_n, (uint32_t)__popcll(rb));
+            at = __shfl(at, lead);
+            if (rest && sub == 0)
+                hard[at + (uint32_t)__popcll(rb & ((1ull << lane) - 1ull))] = (int32_t)i;
+            if (rest) continue;
+        }
+    } else {
+
+    // of the group's cnt_mem entries `mem` (this lane's),
+    // those of this lane among the `need_mem` smallest exact keys (r^2, id)
+    auto smallest = [&](uint64_t mem, int cnt_mem, int need_mem) -> uint64_t {
+        const int own = __popcll(mem);
+        int at = own;
 #pragma unroll
-    for (int o = 0; o < 8; ++o) {
-        const uint32_t mo = minb(o);
-        if (mo == (uint32_t)bstar) octB |= 1u << o;
-        else if (mo != 0xFFu && mo > (uint32_t)bstar) octC |= 1u << o;
-    }
-    const int nB = __popc(octB);
-    const bool partial = need < hc;
-    if (K < 0 || (partial && hc + nB > LIST_CAP)) {
-        write_rec(v, i, 0, gm, MODE_SORTED, Mask4());
-        hard[atomicAdd(hard_n, 1u)] = (int32_t)i;
-        return;
+        for (int d = 1; d < L; d <<= 1) {
+            const int o = __shfl_up(at, d, L);
+            if (sub >= d) at += o;
+        }
+        at -= own;
+        // (this is rare: the particle's own values are read again here)
+        const Seen own_s = seen_from(v, g, i);
+        // exact key of this group's lane ln's entry e
+        auto exact = [&](int ln, int e, double& r2, int32_t& id) {
+            const int32_t le[1] = {v.vl[vl_at(n, i, 4 * L * (e >> 2) + 4 * ln + (e & 3))]};
+            Pt p[1];
+            gather_list(v, own_s, le, p);
+            r2 = dist2(dsub(p[0].x, own_s.xi), dsub(p[0].y, own_s.yi),
+                       dsub(p[0].z, own_s.zi));
+            id = p[0].id;
+        };
+        uint64_t out = 0;
+        if (__ballot(cnt_mem > ties.cap) != 0ull) {
+            // too many for the list (points at equal distances): every
+            // member against every other, the members named in LDS
+            wave_sync();
+            ties.r2[sub] = __longlong_as_double((long long)mem);
+            wave_sync();
+            for (uint64_t b = mem; b; b &= b - 1) {
+                double ra, rb;
+                int32_t ia, ib;
+                exact(sub, __builtin_ctzll(b), ra, ia);
+                int less = 0;
+                for (int ln = 0; ln < L; ++ln)
+                    for (uint64_t o = (uint64_t)__double_as_longlong(ties.r2[ln]); o;
+                         o &= o - 1) {
+                        exact(ln, __builtin_ctzll(o), rb, ib);
+                        less += key_less(rb, ib, ra, ia) ? 1 : 0;
+                    }
+                if (less < need_mem) out |= b & (0ull - b);
+            }
+            wave_sync();
+            return out;
+        }
+        int q = at;
+        for (uint64_t b = mem; b; b &= b - 1, ++q) {
+            double r2;
+            int32_t id;
+            exact(sub, __builtin_ctzll(b), r2, id);
+            ties.r2[q] = r2;
+            ties.id[q] = id;
+        }
+        wave_sync();
+        q = at;
+        for (uint64_t b = mem; b; b &= b - 1, ++q) {
+            const double r2 = ties.r2[q];
+            const int32_t id = ties.id[q];
+            int less = 0;
+            for (int o = 0; o < cnt_mem; ++o)
+                less += key_less(ties.r2[o], ties.id[o], r2, id) ? 1 : 0;
+            if (less < need_mem) out |= b & (0ull - b);
+        }
+        wave_sync();
+        return out;
+    };
+
+    // ---- octants without a candidate below the cut: force their first
+    uint32_t fo = 0u;
+    bool open = nc > m_max;
+    while (__ballot(open) != 0ull) {
+        uint32_t ko = 0u;
+        entries([&](int, uint32_t k, uint32_t o) { ko |= k < T ? 1u << o : 0u; });
+        ko = group_or<L>(ko);
+        const uint32_t miss = open ? allo & ~(ko | fo) : 0u;
+        open = miss != 0u && K > 0;
+        if (__ballot(open) == 0ull) break;
+        // (octant o is bit 7 - o here: the highest bit is the first octant)
+        const uint32_t mo = open ? 31u - (uint32_t)__builtin_clz(miss) : 8u;
+        uint32_t mk = NO_KEY;
+        entries([&](int, uint32_t k, uint32_t o) { mk = o == mo && k < mk ? k : mk; });
+        mk = group_min<L>(mk);
+        uint64_t hit = 0;
+        entries([&](int b, uint32_t k, uint32_t o) {
+            hit |= open && o == mo && k == mk ? 1ull << b : 0ull;
+        });
+        const int hits = (int)group_add<L>((uint32_t)__popcll(hit));
+        if (__ballot(open && hits > 1)) {
+            const uint64_t f = smallest(open && hits > 1 ? hit : 0ull, hits, 1);
+            if (open && hits > 1) hit = f;
+        }
+        if (open) {
+            kept |= hit;
+            fo |= 1u << mo;
+            --K;
+        }
+        // (T falls with K, so a forced entry's key stays at or above it)
+        cut(open && !few);
     }
 
-    // ---- pass 2: keep every lower bucket; the cut bucket whole, or its
-    // members collected for exact ranking
-    // Sixteen entries at a time: their keep and member bits are formed
-    // with selects (no divergent branch per entry); the few members are
-    // then listed from their bits.
-    Mask4 mk;
-    int nl = 0;
-    const uint32_t ub = (uint32_t)bstar;
-    for (int k0 = 0; k0 < cnt; k0 += 16) {
-        uint32_t cw[4];
-#pragma unroll
-        for (int w = 0; w < 4; ++w)
-            cw[w] = k0 + 4 * w < cnt ? code[(int64_t)((k0 >> 2) + w) * n + i] : 0xFFFFFFFFu;
-        uint32_t keep = 0, memb = 0;
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            const uint32_t kc = (cw[u >> 2] >> (8 * (u & 3))) & 0xFFu;
-            keep |= (kc < ub || (kc == ub && !partial)) ? 1u << u : 0u;
-            memb |= (kc == ub && partial) ? 1u << u : 0u;
-        }
-        mk.set_bits<16>(k0, keep);
-        while (memb) {
-            lkey[nl][t] = (uint32_t)(k0 + __builtin_ctz(memb));
-            ++nl;
-            memb &= memb - 1;
-        }
+    // ---- candidates tied at the cut: the `need` smallest exact keys
+    if (__ballot(tied > 0) != 0ull) {
+        uint64_t mem = 0;
+        entries([&](int b, uint32_t k, uint32_t) {
+            mem |= tied > 0 && k == T ? 1ull << b : 0ull;
+        });
+        mem &= ~kept;
+        const int cm = (int)group_add<L>((uint32_t)__popcll(mem));
+        kept |= smallest(mem, cm, need);
     }
-    // keys of the members: r^2 rounded to float with its low 8 bits
-    // replaced by the list index, and their octants
-    for (int a0 = 0; a0 < nl; a0 += 4) {
-        int32_t e[4];
+    }
+
+    // ---- keep mask: the keys below the cut, and `kept`
+    uint32_t mw[2 * MASK_WORDS];
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            e[u] = a0 + u < nl ? v.vl[vl_at(n, i, lkey[a0 + u][t])] : (int32_t)i;
-        Pt pb[4];
-        gather_list(v, s, e, pb);
+    for (int w = 0; w < 2 * MASK_WORDS; ++w) mw[w] = 0u;
+    {
+        const s16x2 t2 = {(short)T, (short)T};
+        // first bit of a chunk in the mask, less 4 sub
+        constexpr int STEP = 4 * L;
+        chunks([&](auto C) {
+            constexpr int c = decltype(C)::value;
+            // (both halves of a pair are 0 or -1)
+            const uint32_t d0 = __builtin_bit_cast(uint32_t, key_below(key[2 * c], t2));
+            const uint32_t d1 = __builtin_bit_cast(uint32_t, key_below(key[2 * c + 1], t2));
+            const uint32_t nib = (d0 & 1u) | ((d0 >> 16) & 2u) | (d1 & 4u) | ((d1 >> 16) & 8u);
+            mw[STEP * c / 32] |= nib << (STEP * c % 32);
+        });
+        if (FULL && __ballot(kept != 0ull) != 0ull)
+            chunks([&](auto C) {
+                constexpr int c = decltype(C)::value;
+                mw[STEP * c / 32] |= ((uint32_t)(kept >> (4 * c)) & 0xFu) << (STEP * c % 32);
+            });
+    }
+    // (4 sub stays inside the chunk's 4 L bits; L = 16: across two words)
+    if (L == 16) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (a0 + u >= nl) continue;
-            const Pt& p = pb[u];
-            const double dx = dsub(p.x, xi), dy = dsub(p.y, yi), dz = dsub(p.z, zi);
-            const float f = (float)dist2(dx, dy, dz);
-            lkey[a0 + u][t] = (__float_as_uint(f) & ~0xFFu) | lkey[a0 + u][t];
-            loct[a0 + u][t] = (uint8_t)octant_of(dx, dy, dz);
+        for (int w = 0; w < MASK_WORDS; ++w) {
+            const uint32_t x = mw[2 * w];
+            mw[2 * w] = sub < 8 ? x << (4 * (sub & 7)) : 0u;
+            mw[2 * w + 1] = sub < 8 ? 0u : x << (4 * (sub & 7));
         }
+    } else {
+#pragma unroll
+        for (int w = 0; w < 2 * MASK_WORDS; ++w) mw[w] <<= 4 * sub;
     }
-    auto exact_key = [&](int k, double& r2, int32_t& id) {
-        const int32_t e[1] = {v.vl[vl_at(n, i, k)]};
-        Pt p[1];
-        gather_list(v, s, e, p);
-        r2 = dist2(dsub(p[0].x, xi), dsub(p[0].y, yi), dsub(p[0].z, zi));
-        id = p[0].id;
-    };
-    // is member b's key (r^2, id) below member a's?
-    auto below = [&](int b, int a) {
-        const uint32_t ka = lkey[a][t], kb = lkey[b][t];
-        if ((kb >> 8) != (ka >> 8)) return (kb >> 8) < (ka >> 8);
-        double ra, rb;
-        int32_t ia, ib;
-        exact_key((int)(ka & 0xFFu), ra, ia);
-        exact_key((int)(kb & 0xFFu), rb, ib);
-        return key_less(rb, ib, ra, ia);
-    };
-    if (partial) {
-        // firsts of the B octants among the members: kept, not ranked
-        if (octB) {
-            for (int a = 0; a < nl; ++a) {
-                const int o = loct[a][t];
-                if (!((octB >> o) & 1u)) continue;
-                bool first = true;
-                for (int b = 0; b < nl && first; ++b)
-                    if (b != a && (loct[b][t] & 7) == o && below(b, a)) first = false;
-                if (first) {
-                    loct[a][t] = (uint8_t)(o | 0x80);
-                    mk.set((int)(lkey[a][t] & 0xFFu));
-                }
-            }
-        }
-        // the `need` smallest keys of the other members
-        for (int a = 0; a < nl; ++a) {
-            if (loct[a][t] & 0x80) continue;
-            int rank = 0;
-            for (int b = 0; b < nl; ++b)
-                if (b != a && !(loct[b][t] & 0x80) && below(b, a)) ++rank;
-            if (rank < need) mk.set((int)(lkey[a][t] & 0xFFu));
-        }
+#pragma unroll
+    for (int w = 0; w < 2 * MASK_WORDS; ++w) mw[w] = group_or<L>(mw[w]);
+    if (sub == 0) {
+        v.rec[REC_M * n + i] = m;
+        v.rec[REC_GM * n + i] = gm;
     }
-    // firsts of the C octants (rare): the smallest key of the octant in
-    // its lowest bucket
-    if (octC) {
-        for (int o = 0; o < 8; ++o) {
-            if (!((octC >> o) & 1u)) continue;
-            const int mo = (int)minb(o);
-            double br = INFINITY;
-            int32_t bi = NOID;
-            int bk = -1;
-            for (int k = 0; k < cnt; ++k) {
-                if ((int)((code[(int64_t)(k >> 2) * n + i] >> (8 * (k & 3))) & 0xFFu) != mo)
-                    continue;
-                const Pt p = list_point(v, g, v.vl[vl_at(n, i, k)], xi, yi);
-                const double dx = dsub(p.x, xi), dy = dsub(p.y, yi), dz = dsub(p.z, zi);
-                if (octant_of(dx, dy, dz) != o) continue;
-                const double r2 = dist2(dx, dy, dz);
-                if (key_less(r2, p.id, br, bi)) {
-                    br = r2;
-                    bi = p.id;
-                    bk = k;
-                }
-            }
-            if (bk >= 0) mk.set(bk);
-        }
+#pragma unroll
+    for (int w = 0; w < MASK_WORDS; ++w)
+        if (sub == w % L)
+            v.kmask[w * n + i] = (uint64_t)mw[2 * w] | ((uint64_t)mw[2 * w + 1] << 32);
     }
-    write_rec(v, i, m_max, gm, 0, mk);
 }
 
-// Exact path, one wavefront per particle: the candidates are collected
-// into LDS, each is ranked by key (r^2, id) against all others, and the
-// stencil rule is applied directly (octant-firsts in octant order, then
-// the others in key order, m_max in all).
-__global__ __launch_bounds__(BLOCK) void k_select_sorted(
-    View v, const int32_t* hard, const unsigned int* hard_n, ErrWord* err,
-    Counters* cnt)
+// Threads per block of the selection: with staging, half a tile at L = 4.
+constexpr int sel_threads(bool staged) { return staged ? 512 : 256; }
+
+// Gathers from the records, every case of the rule in one kernel.
+template <int L, bool PERIODIC>
+__global__ __launch_bounds__(BLOCK, 4) void k_select_full(View v)
 {
-    constexpr int WPB = BLOCK / 64;
-    constexpr int PER_LANE = HARD_CAP / 64;
-    __shared__ double sr2[WPB][HARD_CAP];
-    __shared__ int32_t sid[WPB][HARD_CAP];   // id | octant << 28
-    __shared__ double fr2[WPB][8];
-    __shared__ int32_t fid[WPB][8];
-    const int lane = threadIdx.x & 63;
-    const int wv = threadIdx.x >> 6;
+    constexpr int P = BLOCK / L;
+    constexpr int TIE_CAP = 64;
+    __shared__ double tie_r2[P][TIE_CAP];
+    __shared__ int32_t tie_id[P][TIE_CAP];
+    const int grp = threadIdx.x / L;
+    const int64_t i = xcd_block(blockIdx.x, gridDim.x) * P + grp;
+    if (i >= v.n) return;
+    select_particle<L, false, PERIODIC, true>(v, i, threadIdx.x % L, nullptr, nullptr, nullptr,
+                                              TieList{tie_r2[grp], tie_id[grp], TIE_CAP},
+                                              nullptr, nullptr, 0);
+}
+
+// Leaves the rare cases to k_select_rest.  STAGED: from the tile's list
+// sources staged in LDS; a tile that is not staged gathers from the records,
+// as every block does without STAGED.
+template <int L, bool STAGED, bool PERIODIC>
+__global__ __launch_bounds__(sel_threads(STAGED), 4) void k_select(View v, int32_t* hard,
+                                                                   unsigned int* hard_n,
+                                                                   int force_rest)
+{
+    constexpr int NT = sel_threads(STAGED);
+    constexpr int P = NT / L;                // particles per block
+    static_assert(BLOCK % P == 0, "a block lies in one tile");
+    // slot STAGE_CAP: the source of an entry past a list's end, infinitely
+    // far away
+    constexpr int NS = STAGED ? STAGE_CAP + 1 : 1;
+    __shared__ double sx[NS], sy[NS], sz[NS];
+    const int t = threadIdx.x;
+    const int64_t i0 = xcd_block(blockIdx.x, gridDim.x) * P;
+    const int64_t i = i0 + t / L;
+    int S = -1;                              // staged sources, -1: none
+    if (STAGED) {
+        const int64_t tile = i0 / BLOCK;
+        const int tc = v.tile_cnt[tile];
+        S = tc <= STAGE_CAP ? tc : -1;
+        if (S >= 0) {
+            constexpr int SP = (STAGE_CAP + NT - 1) / NT;
+            const int32_t* src = v.tile_src + tile * STAGE_CAP;
+            int32_t js[SP];
+#pragma unroll
+            for (int u = 0; u < SP; ++u) js[u] = t + u * NT < S ? src[t + u * NT] : -1;
+            double q[3][SP];
+#pragma unroll
+            for (int u = 0; u < SP; ++u)
+                packed_pos(v, js[u] < 0 ? 0 : js[u], q[0][u], q[1][u], q[2][u]);
+#pragma unroll
+            for (int u = 0; u < SP; ++u) {
+                if (js[u] < 0) continue;
+                sx[t + u * NT] = q[0][u];
+                sy[t + u * NT] = q[1][u];
+                sz[t + u * NT] = q[2][u];
+            }
+            if (t == 0) sx[STAGE_CAP] = sy[STAGE_CAP] = sz[STAGE_CAP] = INFINITY;
+            __syncthreads();
+        }
+    }
+    if (i >= v.n) return;
+    const TieList none{nullptr, nullptr, 0};
+    if (STAGED && S >= 0)
+        select_particle<L, STAGED, PERIODIC, false>(v, i, t % L, sx, sy, sz, none, hard,
+                                                    hard_n, force_rest);
+    else
+        select_particle<L, false, PERIODIC, false>(v, i, t % L, sx, sy, sz, none, hard,
+                                                   hard_n, force_rest);
+}
+
+// The particles k_select has listed, with every case of the rule.
+constexpr int REST_LANES = 16;
+constexpr int REST_BLOCKS = 1024;
+
+template <bool PERIODIC>
+__global__ __launch_bounds__(BLOCK) void k_select_rest(View v, const int32_t* hard,
+                                                       const unsigned int* hard_n,
+                                                       Counters* cnt)
+{
+    constexpr int P = BLOCK / REST_LANES;
+    __shared__ double tie_r2[P][VCAP];
+    __shared__ int32_t tie_id[P][VCAP];
+    const int grp = threadIdx.x / REST_LANES, sub = threadIdx.x % REST_LANES;
     const unsigned int total = *hard_n;
     if (blockIdx.x == 0 && threadIdx.x == 0)
         atomicAdd(&cnt->hard_stencils, (unsigned long long)total);
-    const int64_t n = v.n;
-    const int m_max = v.m_max;
-    const uint64_t below = (1ull << lane) - 1;
-    for (int64_t tt = (int64_t)blockIdx.x * WPB + wv; tt < (int64_t)total;
-         tt += (int64_t)gridDim.x * WPB) {
-        const int64_t i = hard[tt];
-        const GridInfo& g = v.grid[sys_of(v.off, v.n_sys, i)];
-        const double xi = v.x[i], yi = v.y[i], zi = v.z[i];
-        const double R2 = g.R2;
-        const int cnt_i = v.vcnt[i];
-        // ---- collect (ballot compaction, list order)
-        int nc = 0;
-        for (int k0 = 0; k0 < cnt_i; k0 += 64) {
-            const int k = k0 + lane;
-            bool cand = false;
-            double r2 = 0.0;
-            int32_t key = 0;
-            if (k < cnt_i) {
-                const Pt p = list_point(v, g, v.vl[vl_at(n, i, k)], xi, yi);
-                if (p.valid) {
-                    const double dx = dsub(p.x, xi), dy = dsub(p.y, yi),
-                                 dz = dsub(p.z, zi);
-                    r2 = dist2(dx, dy, dz);
-                    cand = r2 < R2;
-                    key = p.id | (octant_of(dx, dy, dz) << 28);
-                }
-            }
-            const uint64_t bal = __ballot(cand);
-            const int pos = nc + __popcll(bal & below);
-            if (cand && pos < HARD_CAP) {
-                sr2[wv][pos] = r2;
-                sid[wv][pos] = key;
-            }
-            nc += __popcll(bal);
-        }
-        if (nc > HARD_CAP) {
-            if (lane == 0) {
-                raise_error(err, ERR_CAPACITY, i);
-                v.rec[REC_M * n + i] = 0;
-            }
-            continue;
-        }
-        if (lane < 8) {
-            fr2[wv][lane] = INFINITY;
-            fid[wv][lane] = -1;
-        }
-        wave_sync();
-        // ---- rank of each candidate, overall and within its octant
-        int rk[PER_LANE], ork[PER_LANE];
-#pragma unroll
-        for (int q = 0; q < PER_LANE; ++q) {
-            const int c = lane + 64 * q;
-            rk[q] = 0;
-            ork[q] = 1;
-            if (c < nc) {
-                const double rc = sr2[wv][c];
-                const int32_t kc = sid[wv][c];
-                const int32_t idc = kc & 0x0FFFFFFF;
-                const int oc = (kc >> 28) & 7;
-                int r = 0, o = 0;
-                for (int j = 0; j < nc; ++j) {
-                    const int32_t kj = sid[wv][j];
-                    const bool less = key_less(sr2[wv][j], kj & 0x0FFFFFFF, rc, idc);
-                    r += less ? 1 : 0;
-                    o += (less && ((kj >> 28) & 7) == oc) ? 1 : 0;
-                }
-                rk[q] = r;
-                ork[q] = o;
-                if (o == 0) {
-                    fr2[wv][oc] = rc;
-                    fid[wv][oc] = idc;
-                }
-            }
-        }
-        wave_sync();
-        // ---- output slot of each candidate
-        int octmask = 0;
-#pragma unroll
-        for (int o = 0; o < 8; ++o)
-            if (fid[wv][o] >= 0) octmask |= 1 << o;
-        const int n_oct = __popc(octmask);
-#pragma unroll
-        for (int q = 0; q < PER_LANE; ++q) {
-            const int c = lane + 64 * q;
-            if (c >= nc) continue;
-            const double rc = sr2[wv][c];
-            const int32_t kc = sid[wv][c];
-            const int32_t idc = kc & 0x0FFFFFFF;
-            const int oc = (kc >> 28) & 7;
-            int slot;
-            if (ork[q] == 0) {
-                slot = __popc(octmask & ((1 << oc) - 1));
-            } else {
-                int fl = 0;
-#pragma unroll
-                for (int o = 0; o < 8; ++o)
-                    if (fid[wv][o] >= 0 && key_less(fr2[wv][o], fid[wv][o], rc, idc)) ++fl;
-                slot = n_oct + rk[q] - fl;
-            }
-            if (slot < m_max) v.hsten[(int64_t)slot * n + i] = idc;
-        }
-        if (lane == 0) v.rec[REC_M * n + i] = nc < m_max ? nc : m_max;
-        wave_sync();
+    for (int64_t q = (int64_t)blockIdx.x * P + grp; q < (int64_t)total;
+         q += (int64_t)gridDim.x * P)
+        select_particle<REST_LANES, false, PERIODIC, true>(
+            v, hard[q], sub, nullptr, nullptr, nullptr, TieList{tie_r2[grp], tie_id[grp], VCAP},
+            nullptr, nullptr, 0);
+}
+
+template <int L>
+void launch_select_full(lp_ctx* c, const View& v)
+{
+    const dim3 gb(blocks_for(c->n, BLOCK / L)), bb(BLOCK);
+    if (c->periodic)
+        hipLaunchKernelGGL((k_select_full<L, true>), gb, bb, 0, c->stream, v);
+    else
+        hipLaunchKernelGGL((k_select_full<L, false>), gb, bb, 0, c->stream, v);
+}
+
+template <int L, bool STAGED>
+void launch_select_as(lp_ctx* c, const View& v, int force)
+{
+    Work& w = c->w;
+    constexpr int NT = sel_threads(STAGED);
+    const dim3 gb(blocks_for(c->n, NT / L)), bb(NT);
+    if (c->periodic)
+        hipLaunchKernelGGL((k_select<L, STAGED, true>), gb, bb, 0, c->stream, v, w.hard,
+                           w.hard_n, force);
+    else
+        hipLaunchKernelGGL((k_select<L, STAGED, false>), gb, bb, 0, c->stream, v, w.hard,
+                           w.hard_n, force);
+}
+
+// The selection in one kernel (k_select_full) up to SELECT_FULL_MAX
+// particles, above by k_select and k_select_rest (LP_DEBUG_SORTED_STENCIL:
+// always, every particle through the rest).  Measured, us: 131,072
+// particles 47 in one, 38 + 13 in two; 262,144 88 and 66 + 13.  16 lanes
+// against 8: 4,096 particles 11.0 and 12.1, 12,075 14.3 and 14.0.
+constexpr int64_t SELECT_L16_MAX = 8192, SELECT_FULL_MAX = 163840;
+
+bool select_in_one(const lp_ctx* c)
+{
+    return c->n <= SELECT_FULL_MAX && !(c->cfg.debug_flags & LP_DEBUG_SORTED_STENCIL);
+}
+
+void launch_select(lp_ctx* c, const View& v)
+{
+    if (select_in_one(c)) {
+        if (c->n <= SELECT_L16_MAX) launch_select_full<16>(c, v);
+        else launch_select_full<8>(c, v);
+        return;
     }
+    const int force = (c->cfg.debug_flags & LP_DEBUG_SORTED_STENCIL) ? 1 : 0;
+    if (c->map_ok && !c->map_forked) launch_select_as<4, true>(c, v, force);
+    else launch_select_as<4, false>(c, v, force);
+}
+
+void launch_select_rest(lp_ctx* c, const View& v)
+{
+    if (select_in_one(c)) return;
+    Work& w = c->w;
+    const unsigned nb = std::min(blocks_for(c->n, BLOCK / REST_LANES), (unsigned)REST_BLOCKS);
+    if (c->periodic)
+        hipLaunchKernelGGL(k_select_rest<true>, dim3(nb), dim3(BLOCK), 0, c->stream, v,
+                           w.hard, w.hard_n, w.cnt);
+    else
+        hipLaunchKernelGGL(k_select_rest<false>, dim3(nb), dim3(BLOCK), 0, c->stream, v,
+                           w.hard, w.hard_n, w.cnt);
 }
 
 // ---- exports -----------------------------------------------------------
@@ -1226,8 +1438,10 @@ __global__ __launch_bounds__(BLOCK) void k_tile_map(
         if (*(volatile int*)&full) break;
         int32_t jb[MAP_BATCH];
         vl_load(vl, n, i, k0, jb);
+        uint32_t hb[MAP_BATCH];
 #pragma unroll
         for (int u = 0; u < MAP_BATCH; ++u) {
+            hb[u] = (uint32_t)STAGE_CAP;     // pads the last chunk
             if (k0 + u >= cnt) continue;
             const int32_t j = jb[u] & ~MBIT;
             uint32_t h = src_hash(j);
@@ -1240,9 +1454,10 @@ __global__ __launch_bounds__(BLOCK) void k_tile_map(
             if (probe == HASH_SIZE) full = 1;
             // the entry's hash slot (and mirror bit) until its source's
             // place in the sorted set is known
-            vs[(int64_t)(k0 + u) * n + i] =
-                (uint16_t)(h | ((jb[u] & MBIT) ? SLOT_MIRROR : 0u));
+            hb[u] = h | ((jb[u] & MBIT) ? SLOT_MIRROR : 0u);
         }
+#pragma unroll
+        for (int u = 0; u < MAP_BATCH; u += 4) vs_store4(vs, n, i, k0 + u, hb + u);
     }
     __syncthreads();
     // compact: thread t takes hash slots [t PER, (t + 1) PER)
@@ -1305,14 +1520,18 @@ __global__ __launch_bounds__(BLOCK) void k_tile_map(
     for (int k0 = 0; k0 < cnt; k0 += MAP_BATCH) {
         uint32_t hb[MAP_BATCH];
 #pragma unroll
-        for (int u = 0; u < MAP_BATCH; ++u)
-            hb[u] = k0 + u < cnt ? vs[(int64_t)(k0 + u) * n + i] : 0u;
+        for (int u = 0; u < MAP_BATCH; u += 4) vs_load4(vs, n, i, k0 + u, hb + u);
 #pragma unroll
         for (int u = 0; u < MAP_BATCH; ++u) {
-            if (k0 + u >= cnt) continue;
+            if (k0 + u >= cnt) {
+                hb[u] = (uint32_t)STAGE_CAP;
+                continue;
+            }
             const uint32_t q = (uint32_t)hkey[hb[u] & (HASH_SIZE - 1)];
-            vs[(int64_t)(k0 + u) * n + i] = (uint16_t)(q | (hb[u] & SLOT_MIRROR));
+            hb[u] = q | (hb[u] & SLOT_MIRROR);
         }
+#pragma unroll
+        for (int u = 0; u < MAP_BATCH; u += 4) vs_store4(vs, n, i, k0 + u, hb + u);
     }
 }
 
@@ -1326,8 +1545,9 @@ __global__ __launch_bounds__(BLOCK) void k_pack_pos(int64_t n, const double* x,
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     double2* r = reinterpret_cast<double2*>(p4 + 4 * i);
-    r[0] = make_double2(x[i], y[i]);
-    r[1] = make_double2(z[i], 0.0);
+    // (+ 0.0: no -0 in a record)
+    r[0] = make_double2(x[i] + 0.0, y[i] + 0.0);
+    r[1] = make_double2(z[i] + 0.0, 0.0);
 }
 
 }  // namespace
@@ -1424,21 +1644,14 @@ lp_status stencils_build(lp_ctx* c, const double* const st[7], bool packed, int 
         hipLaunchKernelGGL(k_mirror_write, dim3((unsigned)nb), dim3(BLOCK), 0, s, n,
                            c->n_sys, w.off, w.grid, w.bsum, scanned, &w.summary->n_mirror,
                            st[2], w.mirror_of, w.msrc);
-        const int force = (c->cfg.debug_flags & LP_DEBUG_SORTED_STENCIL) ? 1 : 0;
         // the select phase times the selection kernel alone
         prof_mark(c, 1, false);
-        if (c->periodic)
-            hipLaunchKernelGGL(k_select<true>, dim3(blocks_for(n)), dim3(BLOCK), 0, s, v,
-                               w.hard, w.hard_n, force);
-        else
-            hipLaunchKernelGGL(k_select<false>, dim3(blocks_for(n)), dim3(BLOCK), 0, s, v,
-                               w.hard, w.hard_n, force);
+        launch_select(c, v);
         prof_mark(c, 1, true);
     }
     if (n > 0 && part != STENCIL_HEAD) {
         prof_mark(c, 2, false);
-        hipLaunchKernelGGL(k_select_sorted, dim3(HARD_BLOCKS), dim3(BLOCK), 0, s, v,
-                           w.hard, w.hard_n, w.err, w.cnt);
+        launch_select_rest(c, v);
         prof_mark(c, 2, true);
     }
     hipError_t e = hipGetLastError();

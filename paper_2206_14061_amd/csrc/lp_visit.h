@@ -126,32 +126,6 @@ __device__ __forceinline__ void gather_list(const View& v, const Seen& s,
     }
 }
 
-// Point of a stencil id (real id, or n + k for mirror k), seen from
-// (xi, yi).
-__device__ __forceinline__ Pt id_point(const View& v, const GridInfo& g,
-                                       int32_t id, double xi, double yi)
-{
-    Pt p;
-    p.valid = true;
-    p.id = id;
-    if (id < v.n) {
-        p.x = v.x[id];
-        p.y = v.y[id];
-        p.z = v.z[id];
-        p.src = id;
-        p.mirror = false;
-    } else {
-        const int32_t j = v.msrc[id - v.n];
-        p.x = v.x[j];
-        p.y = v.y[j];
-        p.z = dsub(dmul(2.0, g.wall), v.z[j]);
-        p.src = j;
-        p.mirror = true;
-    }
-    to_image(v, g, p, xi, yi);
-    return p;
-}
-
 __device__ __forceinline__ bool key_less(double ra, int32_t ia, double rb,
                                          int32_t ib)
 {
@@ -163,17 +137,10 @@ __device__ __forceinline__ int octant_of(double dx, double dy, double dz)
     return (dx >= 0.0 ? 1 : 0) + (dy >= 0.0 ? 2 : 0) + (dz >= 0.0 ? 4 : 0);
 }
 
-// bucket of r^2 in the selection histogram: floor(r2 * scale), clamped
-__device__ __forceinline__ int bucket_of(double r2, double scale)
-{
-    const int b = (int)dmul(r2, scale);
-    return b > HIST_BUCKETS - 1 ? HIST_BUCKETS - 1 : b;
-}
-
-// Stencil record of one particle, in registers: kept rows, ghost mask,
-// mode and the keep bitmask over its neighbour-list entries.
+// Stencil record of one particle, in registers: kept rows, ghost mask and
+// the keep bitmask over its neighbour-list entries.
 struct Rec {
-    int m, gm, mode;
+    int m, gm;
     uint64_t mask[MASK_WORDS];
 };
 
@@ -184,7 +151,6 @@ __device__ __forceinline__ Rec load_rec(const View& v, int64_t i)
     const int32_t* q = v.rec;
     r.m = q[REC_M * n + i];
     r.gm = q[REC_GM * n + i];
-    r.mode = q[REC_MODE * n + i];
 #pragma unroll
     for (int w = 0; w < MASK_WORDS; ++w) r.mask[w] = v.kmask[w * n + i];
     return r;
@@ -243,13 +209,6 @@ __device__ __forceinline__ void visit_stencil(const View& v, const GridInfo& g,
     const int64_t n = v.n;
     const Seen s = seen_from(v, g, i);
     const double xi = s.xi, yi = s.yi, zi = s.zi;
-    if (r.mode & MODE_SORTED) {
-        for (int k = 0; k < r.m; ++k) {
-            const Pt p = id_point(v, g, v.hsten[(int64_t)k * n + i], xi, yi);
-            f(p, dsub(p.x, xi), dsub(p.y, yi), dsub(p.z, zi));
-        }
-        return;
-    }
     MaskWalk mw(r);
     int t = 0;
     for (; t + B <= r.m; t += B) {
@@ -277,14 +236,6 @@ template <int B = 8, class F>
 __device__ __forceinline__ void visit_sources(const View& v, int64_t i, const Rec& r, F&& f)
 {
     const int64_t n = v.n;
-    if (r.mode & MODE_SORTED) {
-        for (int k = 0; k < r.m; ++k) {
-            const int32_t id = v.hsten[(int64_t)k * n + i];
-            if (id < n) f(id, false);
-            else f(v.msrc[id - n], true);
-        }
-        return;
-    }
     MaskWalk mw(r);
     int t = 0;
     for (; t + B <= r.m; t += B) {
@@ -300,7 +251,7 @@ __device__ __forceinline__ void visit_sources(const View& v, int64_t i, const Re
     }
 }
 
-// visit_stencil for a particle of a staged tile (not on the sorted path):
+// visit_stencil for a particle of a staged tile:
 // the fields of the tile's list sources sit in LDS in slot order, and a
 // row's point is read from there through the slot word of its list entry.
 // The Pt handed to f carries the slot in `src` (and no id).  Rows come in
@@ -332,11 +283,11 @@ __device__ __forceinline__ void visit_staged(const View& v, const Seen& s, int64
     for (; t + B <= r.m; t += B) {
         uint32_t w[B];
 #pragma unroll
-        for (int u = 0; u < B; ++u) w[u] = v.vs[(int64_t)mw.pop() * n + i];
+        for (int u = 0; u < B; ++u) w[u] = v.vs[vs_at(n, i, mw.pop())];
 #pragma unroll
         for (int u = 0; u < B; ++u) row(w[u]);
     }
-    for (; t < r.m; ++t) row(v.vs[(int64_t)mw.pop() * n + i]);
+    for (; t < r.m; ++t) row(v.vs[vs_at(n, i, mw.pop())]);
 }
 
 // visit_staged with the rows of particle i spread over LPP adjacent lanes:
@@ -379,11 +330,11 @@ __device__ __forceinline__ void visit_staged_sub(const View& v, const Seen& s, i
     for (; t + B <= mine; t += B) {
         uint32_t w[B];
 #pragma unroll
-        for (int u = 0; u < B; ++u) w[u] = v.vs[(int64_t)next() * n + i];
+        for (int u = 0; u < B; ++u) w[u] = v.vs[vs_at(n, i, next())];
 #pragma unroll
         for (int u = 0; u < B; ++u) row(w[u]);
     }
-    for (; t < mine; ++t) row(v.vs[(int64_t)next() * n + i]);
+    for (; t < mine; ++t) row(v.vs[vs_at(n, i, next())]);
 }
 
 // visit_stencil with the rows of particle i spread over LPP adjacent
@@ -398,13 +349,6 @@ __device__ __forceinline__ void visit_stencil_sub(const View& v, const GridInfo&
     }
     const int64_t n = v.n;
     const double xi = v.x[i], yi = v.y[i], zi = v.z[i];
-    if (r.mode & MODE_SORTED) {
-        for (int k = sub; k < r.m; k += LPP) {
-            const Pt p = id_point(v, g, v.hsten[(int64_t)k * n + i], xi, yi);
-            f(p, dsub(p.x, xi), dsub(p.y, yi), dsub(p.z, zi));
-        }
-        return;
-    }
     MaskWalk mw(r);
     for (int t = 0; t < sub && t < r.m; ++t) mw.pop();
     for (int t = sub; t < r.m; t += LPP) {
