@@ -385,6 +385,7 @@ __global__ __launch_bounds__(BLOCK) void k_list_cells(
 
 // ---- mirrors of the current state --------------------------------------
 
+template <int NT>
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* wsum,
                                                     uint32_t& total)
 {
@@ -397,7 +398,7 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* wsum,
     if (lane == 63) wsum[wave] = inc;
     __syncthreads();
     uint32_t pre = 0, tot = 0;
-    for (int w = 0; w < BLOCK / 64; ++w) {
+    for (int w = 0; w < NT / 64; ++w) {
         if (w < wave) pre += wsum[w];
         tot += wsum[w];
     }
@@ -1281,7 +1282,7 @@ void launch_select(lp_ctx* c, const View& v)
         return;
     }
     const int force = (c->cfg.debug_flags & LP_DEBUG_SORTED_STENCIL) ? 1 : 0;
-    if (c->map_ok && !c->map_forked) launch_select_as<4, true>(c, v, force);
+    if (c->map_ok) launch_select_as<4, true>(c, v, force);
     else launch_select_as<4, false>(c, v, force);
 }
 
@@ -1382,153 +1383,184 @@ __global__ void k_export_stencils(View v, int32_t* cnt_out, int32_t* idx_out,
 
 // ---- tile map: the distinct list sources of each tile ------------------
 //
-// One block per tile of BLOCK consecutive particles.  The sources of all
-// list entries of the tile are inserted in an LDS hash set, compacted,
-// sorted ascending (bitonic, SORT_N keys) and stored; every list entry
-// then gets the slot of its source in that order (a 16-bit word, with
-// SLOT_MIRROR for a mirror entry).  A tile with more than STAGE_CAP
-// sources, or whose hash set fills, is marked -1 (not staged).
+// One block per tile of BLOCK consecutive particles, MAP_SPLIT threads per
+// particle (each takes every MAP_SPLIT-th batch of its list: the chains are
+// that much shorter).  Sources are found in
+// granules of 16 consecutive ids: a list holds runs of consecutive ids
+// (the particles of a cell), so a thread looks a granule up in an LDS hash
+// table only where its id's granule changes (about 40 times in 77 entries)
+// and marks each source by a plain byte store, which many threads may do at
+// once.  The granules present are ranked by id, a prefix sum of their marks
+// numbers the sources in ascending order, and every list entry then gets the
+// slot of its source (a 16-bit word, with SLOT_MIRROR for a mirror entry).
+// A tile with more than STAGE_CAP sources, or more granules than the table
+// holds, is marked -1 (not staged).
+//
+// What bounds it: one tile's chain up to 131,072 particles, the list's bytes
+// in and the words' bytes out (twice) above.  Inserting every entry by LDS
+// compare-and-swap and sorting the sources (66 bitonic steps) took 75 us at
+// 4,096 particles, 87 at 32,768, 100 at 131,072, 146 at 262,144 and 230 at
+// 524,288; by granules it is 16, 19, 29, 52 and 108 (about 400 MB there,
+// 80 us at the copy rate).  The map is built before the selection, which
+// then reads staged positions in the passes that rebuild too; on a second
+// stream beside the selection the two took longer than in line (114 us at
+// 262,144 for the map alone).
 
-constexpr int HASH_SIZE = 4096;        // LDS hash slots per tile (power of 2)
-constexpr int SORT_N = 2048;           // keys sorted per tile (>= STAGE_CAP)
-static_assert(STAGE_CAP <= SORT_N && SORT_N <= HASH_SIZE && SORT_N % BLOCK == 0 &&
-                  HASH_SIZE % BLOCK == 0, "tile map sizes");
-static_assert(STAGE_CAP <= (int)SLOT_MIRROR, "slots fit below the mirror bit");
+constexpr int GRAN = 16;               // ids per granule
+constexpr int GRAN_SLOTS = 1024;       // granules per tile (power of 2)
+static_assert(GRAN * GRAN_SLOTS <= (int)SLOT_MIRROR && STAGE_CAP <= (int)SLOT_MIRROR,
+              "places and slots fit below the mirror bit");
+constexpr int MAP_SPLIT = 4, MAP_NT = BLOCK * MAP_SPLIT;
+static_assert(GRAN_SLOTS % MAP_NT == 0 && GRAN == 16, "tile map sizes");
 
-__device__ __forceinline__ uint32_t src_hash(int32_t j)
-{
-    return ((uint32_t)j * 2654435761u) >> 20;   // top 12 bits: HASH_SIZE
-}
-
-// hash slot holding key j (present), found within HASH_SIZE probes
-__device__ __forceinline__ int hash_find(const int32_t* hkey, int32_t j)
-{
-    uint32_t h = src_hash(j);
-    for (int probe = 0; probe < HASH_SIZE; ++probe) {
-        if (hkey[h] == j) return (int)h;
-        h = (h + 1) & (HASH_SIZE - 1);
-    }
-    return -1;
-}
-
-__global__ __launch_bounds__(BLOCK) void k_tile_map(
+__global__ __launch_bounds__(MAP_NT) void k_tile_map(
     int64_t n, const int32_t* __restrict__ vl, const int32_t* __restrict__ vcnt,
     int32_t* __restrict__ tile_src, int32_t* __restrict__ tile_cnt,
     uint16_t* __restrict__ vs, int disable, const int32_t* gate)
 {
-    static_assert(HASH_SIZE == 1 << 12, "src_hash keeps 12 bits");
     if (gate && *gate == 0) return;
-    // hkey: the set's keys, then (once sorted) each key's slot in the set
-    __shared__ int32_t hkey[HASH_SIZE];
-    __shared__ int32_t keys[SORT_N];
-    __shared__ uint32_t wsum[BLOCK / 64];
-    __shared__ int full;
+    constexpr int PER = GRAN_SLOTS / MAP_NT;
+    __shared__ int32_t gkey[GRAN_SLOTS];               // granule of a table place, -1: free
+    __shared__ uint32_t mark[GRAN_SLOTS * GRAN / 4];   // a byte per id of each place
+    __shared__ int32_t list[GRAN_SLOTS];               // the places in use
+    __shared__ int32_t lkey[GRAN_SLOTS];               // and their granules
+    __shared__ uint32_t rcnt[GRAN_SLOTS];              // marks of the granule of each rank
+    __shared__ uint32_t wsum[MAP_NT / 64];
+    __shared__ int full, ng;
     const int t = threadIdx.x;
     const int64_t tile = blockIdx.x;
-    const int64_t i = tile * BLOCK + t;
+    const int64_t i = tile * BLOCK + t % BLOCK;
+    const int part = t / BLOCK;
     const int cnt = i < n ? vcnt[i] : 0;
-    for (int h = t; h < HASH_SIZE; h += BLOCK) hkey[h] = -1;
-    if (t == 0) full = disable;
+    for (int h = t; h < GRAN_SLOTS; h += MAP_NT) gkey[h] = -1;
+    for (int h = t; h < GRAN_SLOTS * GRAN / 4; h += MAP_NT) mark[h] = 0u;
+    if (t == 0) {
+        full = disable;
+        ng = 0;
+    }
     __syncthreads();
+    uint8_t* markb = reinterpret_cast<uint8_t*>(mark);
     // list words are loaded MAP_BATCH at a time (one memory latency per
     // batch instead of per entry)
     constexpr int MAP_BATCH = 8;
-    for (int k0 = 0; k0 < cnt; k0 += MAP_BATCH) {
-        // a full set ends the insertions (the tile is not staged)
+    int32_t last = -1;                     // the granule looked up last
+    uint32_t place = 0u;                   // and its place
+    for (int k0 = part * MAP_BATCH; k0 < cnt; k0 += MAP_SPLIT * MAP_BATCH) {
+        // a full table ends the insertions (the tile is not staged)
         if (*(volatile int*)&full) break;
         int32_t jb[MAP_BATCH];
         vl_load(vl, n, i, k0, jb);
         uint32_t hb[MAP_BATCH];
 #pragma unroll
         for (int u = 0; u < MAP_BATCH; ++u) {
-            hb[u] = (uint32_t)STAGE_CAP;     // pads the last chunk
+            hb[u] = 0u;
             if (k0 + u >= cnt) continue;
             const int32_t j = jb[u] & ~MBIT;
-            uint32_t h = src_hash(j);
-            int probe = 0;
-            for (; probe < HASH_SIZE; ++probe) {
-                const int32_t old = atomicCAS(&hkey[h], -1, j);
-                if (old == -1 || old == j) break;
-                h = (h + 1) & (HASH_SIZE - 1);
+            const int32_t gr = j / GRAN;
+            if (gr != last) {
+                last = gr;
+                uint32_t h = ((uint32_t)gr * 2654435761u) >> 22;   // top 10 bits
+                static_assert(GRAN_SLOTS == 1 << 10, "hash bits");
+                int probe = 0;
+                for (; probe < GRAN_SLOTS; ++probe) {
+                    int32_t old = *(volatile int32_t*)&gkey[h];
+                    if (old == -1) old = atomicCAS(&gkey[h], -1, gr);
+                    if (old == gr) break;
+                    if (old == -1) {
+                        const int q = atomicAdd(&ng, 1);
+                        list[q] = (int32_t)h;
+                        lkey[q] = gr;
+                        break;
+                    }
+                    h = (h + 1) & (GRAN_SLOTS - 1);
+                }
+                if (probe == GRAN_SLOTS) full = 1;
+                place = h;
             }
-            if (probe == HASH_SIZE) full = 1;
-            // the entry's hash slot (and mirror bit) until its source's
-            // place in the sorted set is known
-            hb[u] = h | ((jb[u] & MBIT) ? SLOT_MIRROR : 0u);
+            const uint32_t pos = place * GRAN + (uint32_t)(j % GRAN);
+            markb[pos] = 1;
+            // the entry's place (and mirror bit) until its source's slot is
+            // known
+            hb[u] = pos | ((jb[u] & MBIT) ? SLOT_MIRROR : 0u);
         }
 #pragma unroll
         for (int u = 0; u < MAP_BATCH; u += 4) vs_store4(vs, n, i, k0 + u, hb + u);
     }
     __syncthreads();
-    // compact: thread t takes hash slots [t PER, (t + 1) PER)
-    constexpr int PER = HASH_SIZE / BLOCK;
-    uint32_t mine = 0;
-#pragma unroll
-    for (int q = 0; q < PER; ++q) mine += hkey[t * PER + q] >= 0 ? 1u : 0u;
-    uint32_t total = 0;
-    uint32_t at = block_excl_scan(mine, wsum, total);
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        const int32_t j = hkey[t * PER + q];
-        if (j >= 0) {
-            if (at < (uint32_t)SORT_N) keys[at] = j;
-            ++at;
-        }
-    }
-    const int S = (int)total;
-    if (full || S > STAGE_CAP) {
+    const int G = ng;
+    if (full) {
         if (t == 0) tile_cnt[tile] = -1;
         return;
     }
-    for (int q = S + t; q < SORT_N; q += BLOCK) keys[q] = INT32_MAX;
-    __syncthreads();
-    for (int size = 2; size <= SORT_N; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int q = t; q < SORT_N / 2; q += BLOCK) {
-                const int lo = 2 * q - (q & (stride - 1));
-                const int hi = lo + stride;
-                const bool up = (lo & size) == 0;
-                const int32_t a = keys[lo], b = keys[hi];
-                if ((a > b) == up) {
-                    keys[lo] = b;
-                    keys[hi] = a;
-                }
-            }
-            __syncthreads();
+    // thread t takes the granules t, t + MAP_NT, ... of the list: their marks
+    // as bits, and their rank among the granules
+    uint32_t bits[PER];
+    int32_t key[PER], rank[PER];
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        const int q = t + r * MAP_NT;
+        bits[r] = 0u;
+        key[r] = rank[r] = 0;
+        if (q < G) {
+            const int h = list[q];
+            key[r] = lkey[q];
+            const uint4 m = *reinterpret_cast<const uint4*>(&mark[h * GRAN / 4]);
+            // bytes of 0 or 1 -> four bits (byte k's bit moves to 28 + k)
+            auto nib = [](uint32_t x) { return (x * 0x10204080u) >> 28; };
+            bits[r] = nib(m.x) | nib(m.y) << 4 | nib(m.z) << 8 | nib(m.w) << 12;
         }
     }
-    // every key's hash slot is found before any slot is overwritten
-    constexpr int QPT = SORT_N / BLOCK;
-    int hq[QPT];
+    if (t < G)
+#pragma unroll 8
+        for (int o = 0; o < G; ++o) {
+            const int32_t k = lkey[o];
 #pragma unroll
-    for (int r = 0; r < QPT; ++r) {
-        const int q = t + r * BLOCK;
-        hq[r] = -1;
-        if (q < S) {
-            tile_src[tile * STAGE_CAP + q] = keys[q];
-            hq[r] = hash_find(hkey, keys[q]);
+            for (int r = 0; r < PER; ++r) rank[r] += k < key[r] ? 1 : 0;
         }
+#pragma unroll
+    for (int r = 0; r < PER; ++r)
+        if (t + r * MAP_NT < G) rcnt[rank[r]] = (uint32_t)__popc(bits[r]);
+    __syncthreads();
+    // exclusive prefix sum over the ranks, thread t the ranks [t PER, ...)
+    uint32_t c[PER], mine = 0u, total = 0u;
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        c[r] = t * PER + r < G ? rcnt[t * PER + r] : 0u;
+        mine += c[r];
+    }
+    uint32_t at = block_excl_scan<MAP_NT>(mine, wsum, total);
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        if (t * PER + r < G) rcnt[t * PER + r] = at;
+        at += c[r];
+    }
+    const int S = (int)total;
+    if (t == 0) tile_cnt[tile] = S > STAGE_CAP ? -1 : S;
+    if (S > STAGE_CAP) return;
+    __syncthreads();
+    // the sources, and each place's first slot with its marks
+    uint32_t* tab = mark;                  // (the marks have been read)
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        const int q = t + r * MAP_NT;
+        if (q >= G) continue;
+        const uint32_t first = rcnt[rank[r]];
+        tab[list[q]] = bits[r] | (first << 16);
+        int32_t* out = tile_src + tile * STAGE_CAP + first;
+        for (uint32_t b = bits[r]; b; b &= b - 1) *out++ = key[r] * GRAN + __builtin_ctz(b);
     }
     __syncthreads();
-#pragma unroll
-    for (int r = 0; r < QPT; ++r)
-        if (hq[r] >= 0) hkey[hq[r]] = t + r * BLOCK;
-    if (t == 0) tile_cnt[tile] = S;
-    __syncthreads();
-    // hash slots -> slots in the sorted set (the thread rereads its own
-    // words)
-    for (int k0 = 0; k0 < cnt; k0 += MAP_BATCH) {
+    // places -> slots (the thread rereads its own words); the words past the
+    // list in its last chunk stand for no source
+    for (int k0 = part * MAP_BATCH; k0 < cnt; k0 += MAP_SPLIT * MAP_BATCH) {
         uint32_t hb[MAP_BATCH];
 #pragma unroll
         for (int u = 0; u < MAP_BATCH; u += 4) vs_load4(vs, n, i, k0 + u, hb + u);
 #pragma unroll
         for (int u = 0; u < MAP_BATCH; ++u) {
-            if (k0 + u >= cnt) {
-                hb[u] = (uint32_t)STAGE_CAP;
-                continue;
-            }
-            const uint32_t q = (uint32_t)hkey[hb[u] & (HASH_SIZE - 1)];
-            hb[u] = q | (hb[u] & SLOT_MIRROR);
+            const uint32_t w = tab[(hb[u] & (SLOT_MIRROR - 1u)) / GRAN];
+            const uint32_t q = (w >> 16) + (uint32_t)__popc(w & ((1u << (hb[u] % GRAN)) - 1u));
+            hb[u] = k0 + u < cnt ? q | (hb[u] & SLOT_MIRROR) : (uint32_t)STAGE_CAP;
         }
 #pragma unroll
         for (int u = 0; u < MAP_BATCH; u += 4) vs_store4(vs, n, i, k0 + u, hb + u);
@@ -1604,7 +1636,7 @@ lp_status tile_map_build(lp_ctx* c, const int32_t* gate)
         return LP_E_STATE;
     }
     if (n > 0)
-        hipLaunchKernelGGL(k_tile_map, dim3(blocks_for(n)), dim3(BLOCK), 0, c->stream,
+        hipLaunchKernelGGL(k_tile_map, dim3(blocks_for(n)), dim3(MAP_NT), 0, c->stream,
                            n, w.vl, w.vcnt, w.tile_src, w.tile_cnt, w.vs,
                            (c->cfg.debug_flags & LP_DEBUG_GLOBAL_GATHER) ? 1 : 0, gate);
     hipError_t e = hipGetLastError();
