@@ -327,9 +327,9 @@ lp_status lp_autotune(lp_ctx* ctx, const lp_state* s, int32_t* choice);
  * quadratic fits run instead by stencil size class (rows, ghosts
  * included: at most 16, at most 32, more), one launch per class over its
  * particles; [3..5], [6..8] lanes per particle of each class in the first
- * and second fit (0 on the largest class: the one-lane kernel over whole
- * tiles of particles with their neighbours staged in LDS, skipping the
- * smaller classes); [9..11] particles per class at the last lp_autotune.
+ * and second fit (0 on the largest class: the kernel over whole tiles of
+ * particles with their neighbours staged in LDS, skipping the smaller
+ * classes); [9..11] particles per class at the last lp_autotune.
  * ms (host double[8], optional): the best times lp_autotune measured,
  * milliseconds: [0], [1] one launch of each fit, [2..4], [5..7] each
  * class of the first and second fit (0 for an empty class).  lp_autotune
@@ -441,8 +441,8 @@ lp_status lp_sync_status(lp_ctx* ctx, int64_t* index);
  * particles below the wall after updates, neighbour-list rebuilds by
  * lp_step; then resets them.  Entries 6 and 7 describe the current
  * neighbour list (0 when there is none): tiles of BLOCK = 256 consecutive
- * particles whose neighbours the fits cannot stage in LDS (more than 1664
- * distinct list sources, LP_DEBUG_GLOBAL_GATHER, or every tile while the
+ * particles whose neighbours the fits cannot stage in LDS as one (more than
+ * 1664 distinct list sources: staged in halves, LP_DEBUG_GLOBAL_GATHER, or every tile while the
  * list has no tile map: the map is built by lp_step, lp_step2 and
  * lp_step_graph, not by lp_build_cells or the adjoint entry points), and
  * all tiles.

@@ -115,7 +115,7 @@ __device__ __forceinline__ void acc_flush(const AdjBufs& B, int64_t n, const dou
                                           const int32_t* tsrc, int ns)
 {
     for (int q = threadIdx.x; q < ns; q += NT) {
-        const int64_t j = tsrc[q];
+        const int64_t j = tsrc[q] & ~MBIT;
 #pragma unroll
         for (int f = 0; f < NRECV; ++f) {
             const double x = acc[f * STAGE_CAP + q];
@@ -186,58 +186,69 @@ __global__ void k_adj_init(int64_t n, AdjSeed S, AdjBufs B)
 
 // ---- reverse of the update, the RHS and the fit of P and eta -------------
 
+// What a reverse sweep knows of a row's point: a ghost (no receiver), else
+// its receiver `to` (the slot of a staged source, else the real particle
+// behind the point) and whether it is a mirror.
+struct RowPt {
+    bool ghost, mirror;
+    int32_t to;
+};
+
 // The stencil rows of particle i with the P and eta their points carry:
-// from the tile's sources staged in LDS (positions, P, eta and mirror
-// pressure, as the forward pass-2 fit reads them) when the tile is
-// staged, else from global memory.  body(a, w, p, Pj, Ej, src): src is the
-// real particle behind the point (a mirror's source).
+// from the tile's sources staged in LDS (positions, P and eta, as the
+// forward pass-2 fit reads them) when the tile is staged (`reals` of its
+// sources are no mirrors), else from global memory.  body(a, w, p, Pj, Ej).
 // With LPP lanes per particle, lane sub visits its share of the rows.
-template <int LPP, class F>
+template <int LPP, bool PERIODIC, class F>
 __device__ __forceinline__ void adj_rows2(const View& v, const GridInfo& g,
                                           const lp_params& prm, const AdjBufs& B,
                                           int64_t i, const Rec& r, int sub, bool staged,
-                                          const int32_t* tsrc, const double* sx,
+                                          int reals, const double* sx,
                                           const double* sy, const double* sz,
-                                          const double* sP, const double* sE,
-                                          const double* sM, F&& body)
+                                          const double* sP, const double* sE, F&& body)
 {
     if (staged) {
-        for_rows_staged_sub<FIT_BATCH, LPP, true>(v, g, i, r, sub, sx, sy, sz,
-                                                  [&](const double* a, double w,
-                                                      const Pt* p) {
-            if (!p) body(a, w, p, 0.0, 0.0, -1);
-            else if (p->mirror) body(a, w, p, sM[p->src], 0.0, tsrc[p->src]);
-            else body(a, w, p, sP[p->src], sE[p->src], tsrc[p->src]);
-        });
+        for_rows_staged<LPP, true, PERIODIC>(
+            v, g, i, r.m, r.gm, sub, sx, sy, sz, [&](const double* a, double w, uint32_t q) {
+                const int32_t slot = (int32_t)(q >> 3);
+                body(a, w, RowPt{false, slot >= reals, slot}, staged_at(sP, q),
+                     staged_at(sE, q));
+            }, [&](const double* a, double w) {
+                body(a, w, RowPt{true, false, -1}, 0.0, 0.0);
+            });
     } else {
-        for_rows_sub<LPP>(v, g, i, r, sub, [&](const double* a, double w, const Pt* p) {
+        for_rows_sub<LPP>(v, g, i, load_rec(v, i), sub,
+                          [&](const double* a, double w, const Pt* p) {
             double Pj, Ej;
             pass2_values(v, B.P, B.eta, p, prm, Pj, Ej);
-            body(a, w, p, Pj, Ej, p ? p->src : -1);
+            if (p) body(a, w, RowPt{false, p->mirror, p->src}, Pj, Ej);
+            else body(a, w, RowPt{true, false, -1}, Pj, Ej);
         });
     }
 }
 
 // Reverse of the update, the RHS and the fit of P and eta at real particle
-// i of the block's tile (ns staged sources, -1: not staged), on LPP
+// i of the staged unit, on LPP
 // adjacent lanes: each sums its share of the rows (lane sub), the sums are
 // added across the lanes, every lane then solves the same small systems,
 // and lane 0 writes the particle's own results.
-template <int LPP>
+template <int LPP, bool PERIODIC>
 __device__ __forceinline__ void adj2_particle(const View& v, const AdjSeed& S,
-                                              const AdjBufs& B, int64_t tile, int64_t i,
-                                              int sub, int ns, const double* sx,
+                                              const AdjBufs& B, int64_t i, int sub,
+                                              const StageUnit& unit, const double* sx,
                                               const double* sy, const double* sz,
                                               const double* sP, const double* sE,
-                                              const double* sM, double* acc)
+                                              double* acc)
 {
     const int64_t n = v.n;
     const int s = sys_of(v.off, v.n_sys, i);
     const GridInfo& g = v.grid[s];
     const lp_params& prm = v.prm[s];
-    const Rec r = load_rec(v, i);
-    const bool staged = ns >= 0;
-    const int32_t* tsrc = v.tile_src + tile * STAGE_CAP;
+    Rec r;
+    r.m = v.rec[REC_M * n + i];
+    r.gm = v.rec[REC_GM * n + i];
+    const bool staged = unit.S >= 0;
+    const int reals = unit.reals;
     const bool lin = B.flags[i] & FLAG_LINEAR;
     const double Pi = B.P[i], Ei = B.eta[i];
     // forward fit of P and eta (all nine coefficients)
@@ -246,9 +257,8 @@ __device__ __forceinline__ void adj2_particle(const View& v, const AdjSeed& S,
     for (int q = 0; q < 31; ++q) M[q] = 0.0;
 #pragma unroll
     for (int q = 0; q < 9; ++q) y0[q] = y1[q] = 0.0;
-    adj_rows2<LPP>(v, g, prm, B, i, r, sub, staged, tsrc, sx, sy, sz, sP, sE, sM,
-                   [&](const double* a, double w, const Pt*, double Pj, double Ej,
-                       int32_t) {
+    adj_rows2<LPP, PERIODIC>(v, g, prm, B, i, r, sub, staged, reals, sx, sy, sz, sP, sE,
+                             [&](const double* a, double w, RowPt, double Pj, double Ej) {
         moments_add(M, a, w);
         const double bP = w * (Pj - Pi), bE = w * (Ej - Ei);
 #pragma unroll
@@ -359,9 +369,8 @@ __device__ __forceinline__ void adj2_particle(const View& v, const AdjSeed& S,
         chol_solve<9>(U, yE);
     }
     double aPs = 0.0, aEs = 0.0, ax = 0.0, ay = 0.0, az = 0.0;
-    adj_rows2<LPP>(v, g, prm, B, i, r, sub, staged, tsrc, sx, sy, sz, sP, sE, sM,
-                   [&](const double* a, double, const Pt* p, double Pj, double Ej,
-                       int32_t src) {
+    adj_rows2<LPP, PERIODIC>(v, g, prm, B, i, r, sub, staged, reals, sx, sy, sz, sP, sE,
+                             [&](const double* a, double, RowPt p, double Pj, double Ej) {
         double rP = Pj - Pi, rE = Ej - Ei, bP = 0.0, bE = 0.0;
 #pragma unroll
         for (int q = 0; q < 9; ++q) {
@@ -372,7 +381,7 @@ __device__ __forceinline__ void adj2_particle(const View& v, const AdjSeed& S,
         }
         aPs -= bP;
         aEs -= bE;
-        if (!p) return;   // ghost rows: constant rows, value 0
+        if (p.ghost) return;   // constant rows, value 0
         double Ab[9];
 #pragma unroll
         for (int q = 0; q < 9; ++q)
@@ -385,16 +394,16 @@ __device__ __forceinline__ void adj2_particle(const View& v, const AdjSeed& S,
         ax -= gx;
         ay -= gy;
         az -= gz;
-        if (!p->mirror) {
+        if (!p.mirror) {
             const double c[6] = {bP, bE, 0.0, gx, gy, gz};
-            deliver(B, n, acc, staged, staged ? p->src : src, c);
+            deliver(B, n, acc, staged, p.to, c);
         } else {
             // mirror pressure P(phi_src) of the quasi-static law; no eta
-            const double Vs = v.V[src];
+            const double Vs = v.V[staged ? unit.src[p.to] & ~MBIT : p.to];
             const double dV = 1.0 / Vs > prm.phi_max
                                   ? -bP * prm.rho_s * prm.beta / (Vs * Vs) : 0.0;
             const double c[6] = {0.0, 0.0, dV, gx, gy, -gz};
-            deliver(B, n, acc, staged, staged ? p->src : src, c);
+            deliver(B, n, acc, staged, p.to, c);
         }
     });
     // this particle's own terms (other particles' rows arrive in B.recv)
@@ -418,36 +427,37 @@ __device__ __forceinline__ void adj2_particle(const View& v, const AdjSeed& S,
 // accumulators (all the LDS of a CU), the reverse pass of each particle
 // (LPP lanes each), then the accumulators added into the global receive
 // buffers.
-template <int LPP>
+template <int LPP, bool PERIODIC>
 __global__ __launch_bounds__(BLOCK * LPP, 1) void k_adj_pass2(View v, AdjSeed S, AdjBufs B,
-                                                              int map_ok)
+                                                              int rows_ok)
 {
     constexpr int NT = BLOCK * LPP;
     __shared__ double sx[STAGE_CAP], sy[STAGE_CAP], sz[STAGE_CAP];
-    __shared__ double sP[STAGE_CAP], sE[STAGE_CAP], sM[STAGE_CAP];
+    __shared__ double sP[STAGE_CAP], sE[STAGE_CAP];
     __shared__ double acc[NRECV * STAGE_CAP];
-    const int64_t tile = xcd_block(blockIdx.x, gridDim.x);
-    const int64_t i = tile * BLOCK + threadIdx.x / LPP;
+    const BlockPart<BLOCK> part(v, rows_ok);
+    if (part.idle()) return;
+    const StageUnit& unit = part.unit;
+    const int64_t i = part.i0 + threadIdx.x / LPP;
     const int sub = threadIdx.x % LPP;
-    const int tc = map_ok ? v.tile_cnt[tile] : -1;
-    const int ns = tc <= STAGE_CAP ? tc : -1;   // -1: not staged
-    if (ns >= 0) {
-        stage_pass2<NT>(v, B.P, B.eta, tile, ns, sx, sy, sz, sP, sE, sM);
-        acc_zero<NT>(acc, ns);
+    if (unit.S >= 0) {
+        stage_pass2<NT>(v, B.P, B.eta, unit, sx, sy, sz, sP, sE);
+        acc_zero<NT>(acc, unit.S);
         __syncthreads();
     }
-    if (i < v.n) adj2_particle<LPP>(v, S, B, tile, i, sub, ns, sx, sy, sz, sP, sE, sM, acc);
-    if (ns >= 0) {
+    if (i < v.n && part.mine(threadIdx.x / LPP))
+        adj2_particle<LPP, PERIODIC>(v, S, B, i, sub, unit, sx, sy, sz, sP, sE, acc);
+    if (unit.S >= 0) {
         __syncthreads();
-        acc_flush<NT>(B, v.n, acc, v.tile_src + tile * STAGE_CAP, ns);
+        acc_flush<NT>(B, v.n, acc, unit.src, unit.S);
     }
 }
 
 // ---- reverse of the closure and of the fit of u, v, w ----------------------
 
 // LPP lanes per particle, as in k_adj_pass2.
-template <int LPP>
-__global__ __launch_bounds__(BLOCK * LPP, 1) void k_adj_pass1(View v, AdjBufs B, int map_ok)
+template <int LPP, bool PERIODIC>
+__global__ __launch_bounds__(BLOCK * LPP, 1) void k_adj_pass1(View v, AdjBufs B, int rows_ok)
 {
     constexpr int NT = BLOCK * LPP;
     // the tile's staged sources (positions and velocities, as the forward
@@ -465,46 +475,52 @@ __global__ __launch_bounds__(BLOCK * LPP, 1) void k_adj_pass1(View v, AdjBufs B,
     double* sv = lds + 4 * STAGE_CAP;
     double* sw = lds + 5 * STAGE_CAP;
     const int t = threadIdx.x;
-    const int64_t tile = xcd_block(blockIdx.x, gridDim.x);
-    const int64_t i = tile * BLOCK + t / LPP;
+    const BlockPart<BLOCK> part(v, rows_ok);
+    if (part.idle()) return;
+    const StageUnit& unit = part.unit;
+    const int64_t i = part.i0 + t / LPP;
     const int sub = t % LPP;
     const bool lead = sub == 0;
-    const int tc = map_ok ? v.tile_cnt[tile] : -1;
-    const int ns = tc <= STAGE_CAP ? tc : -1;   // -1: not staged
-    if (ns >= 0) {
-        stage_pass1<NT>(v, tile, ns, sx, sy, sz, su, sv, sw);
-        acc_zero<NT>(acc, ns);
-        __syncthreads();
-    }
     double th[3] = {0.0, 0.0, 0.0};
     int s = -1;
-    if (i < v.n) {
+    if (unit.S >= 0) {
+        stage_pass1<NT>(v, unit, sx, sy, sz, su, sv, sw);
+        acc_zero<NT>(acc, unit.S);
+        __syncthreads();
+    }
+    if (i < v.n && part.mine(t / LPP)) {
         const int64_t n = v.n;
         s = sys_of(v.off, v.n_sys, i);
         const GridInfo& g = v.grid[s];
         const lp_params& prm = v.prm[s];
-        const Rec r = load_rec(v, i);
-        const bool staged = ns >= 0;
+        Rec r;
+        r.m = v.rec[REC_M * n + i];
+        r.gm = v.rec[REC_GM * n + i];
+        const bool staged = unit.S >= 0;
+        const int reals = unit.reals;
         // rows with the velocities of their points (ghosts: u_i)
         // (this lane's share of them)
         auto rows = [&](auto&& body) {
             if (staged) {
-                for_rows_staged_sub<FIT_BATCH, LPP, true>(v, g, i, r, sub, sx, sy, sz,
-                                                          [&](const double* a, double w,
-                                                              const Pt* p) {
+                for_rows_staged<LPP, true, PERIODIC>(
+                    v, g, i, r.m, r.gm, sub, sx, sy, sz,
+                    [&](const double* a, double w, uint32_t q) {
+                        const int32_t slot = (int32_t)(q >> 3);
+                        body(a, w, RowPt{false, slot >= reals, slot}, staged_at(su, q),
+                             staged_at(sv, q), staged_at(sw, q));
+                    }, [&](const double* a, double w) {
+                        body(a, w, RowPt{true, false, -1}, 0.0, 0.0, 0.0);
+                    });
+            } else {
+                for_rows_sub<LPP>(v, g, i, load_rec(v, i), sub,
+                                  [&](const double* a, double w, const Pt* p) {
                     if (!p) {
-                        body(a, w, p, 0.0, 0.0, 0.0);
+                        body(a, w, RowPt{true, false, -1}, 0.0, 0.0, 0.0);
                         return;
                     }
-                    const int q = p->src;
-                    body(a, w, p, su[q], sv[q], p->mirror ? -sw[q] : sw[q]);
-                });
-            } else {
-                for_rows_sub<LPP>(v, g, i, r, sub, [&](const double* a, double w,
-                                                       const Pt* p) {
-                    double uj = 0.0, vj = 0.0, wj = 0.0;
-                    if (p) point_velocity(v, *p, uj, vj, wj);
-                    body(a, w, p, uj, vj, wj);
+                    double uj, vj, wj;
+                    point_velocity(v, *p, uj, vj, wj);
+                    body(a, w, RowPt{false, p->mirror, p->src}, uj, vj, wj);
                 });
             }
         };
@@ -614,10 +630,9 @@ __global__ __launch_bounds__(BLOCK * LPP, 1) void k_adj_pass1(View v, AdjBufs B,
             }
             const double ui = v.u[i], vi = v.v[i], wi = v.w[i];
             double au[3] = {0.0, 0.0, 0.0}, ax = 0.0, ay = 0.0, az = 0.0;
-            rows([&](const double* a, double, const Pt* p, double uj, double vj,
-                     double wj) {
+            rows([&](const double* a, double, RowPt p, double uj, double vj, double wj) {
                 double b[3] = {0.0, 0.0, 0.0};   // ghosts carry u_i
-                if (p) {
+                if (!p.ghost) {
                     b[0] = uj - ui;
                     b[1] = vj - vi;
                     b[2] = wj - wi;
@@ -638,7 +653,7 @@ __global__ __launch_bounds__(BLOCK * LPP, 1) void k_adj_pass1(View v, AdjBufs B,
 #pragma unroll
                     for (int q = 0; q < 9; ++q) Ab[q] += rr * y[f][q] - yy * cu[f][q];
                 }
-                if (!p) return;   // ghost rows: constant, value u_i
+                if (p.ghost) return;   // constant, value u_i
                 au[0] -= bb[0];
                 au[1] -= bb[1];
                 au[2] -= bb[2];
@@ -650,9 +665,9 @@ __global__ __launch_bounds__(BLOCK * LPP, 1) void k_adj_pass1(View v, AdjBufs B,
                 ax -= gx;
                 ay -= gy;
                 az -= gz;
-                const double sg = p->mirror ? -1.0 : 1.0;
+                const double sg = p.mirror ? -1.0 : 1.0;
                 const double cr[6] = {bb[0], bb[1], sg * bb[2], gx, gy, sg * gz};
-                deliver(B, n, acc, staged, p->src, cr);
+                deliver(B, n, acc, staged, p.to, cr);
             });
             // this particle's own terms (other particles' rows arrive in
             // B.recv)
@@ -673,9 +688,9 @@ __global__ __launch_bounds__(BLOCK * LPP, 1) void k_adj_pass1(View v, AdjBufs B,
             }
         }
     }
-    if (ns >= 0) {
+    if (unit.S >= 0) {
         __syncthreads();
-        acc_flush<NT>(B, v.n, acc, v.tile_src + tile * STAGE_CAP, ns);
+        acc_flush<NT>(B, v.n, acc, unit.src, unit.S);
     }
     // parameter cotangents: one atomic per block when the block lies in
     // one system, else one per thread (the staged rows are dead once every
@@ -756,15 +771,21 @@ lp_status step_adjoint(lp_ctx* c, const double* const st[7], const AdjSeed& seed
     hipStream_t s = c->stream;
     B.recv = w.adj_recv;
     B.M = w.adj_M;
-    const int mo = c->map_ok ? 1 : 0;
+    const int ro = c->map_ok && c->rows_ok ? 1 : 0;
+    const dim3 gb(blocks_for(n)), bb(BLOCK), ga(BlockPart<BLOCK>::blocks(n)),
+        ba(BLOCK * ADJ_LPP);
     // (k_adj_init clears the receive buffers, the fold of pass 2 clears
     // them again for pass 1, whose fold writes the result)
-    hipLaunchKernelGGL(k_adj_init, dim3(blocks_for(n)), dim3(BLOCK), 0, s, n, seed, B);
-    hipLaunchKernelGGL(k_adj_pass2<ADJ_LPP>, dim3(blocks_for(n)), dim3(BLOCK * ADJ_LPP), 0, s,
-                       v, seed, B, mo);
-    hipLaunchKernelGGL(k_fold2, dim3(blocks_for(n)), dim3(BLOCK), 0, s, n, B);
-    hipLaunchKernelGGL(k_adj_pass1<ADJ_LPP>, dim3(blocks_for(n)), dim3(BLOCK * ADJ_LPP), 0, s,
-                       v, B, mo);
+    hipLaunchKernelGGL(k_adj_init, gb, bb, 0, s, n, seed, B);
+    if (c->periodic)
+        hipLaunchKernelGGL((k_adj_pass2<ADJ_LPP, true>), ga, ba, 0, s, v, seed, B, ro);
+    else
+        hipLaunchKernelGGL((k_adj_pass2<ADJ_LPP, false>), ga, ba, 0, s, v, seed, B, ro);
+    hipLaunchKernelGGL(k_fold2, gb, bb, 0, s, n, B);
+    if (c->periodic)
+        hipLaunchKernelGGL((k_adj_pass1<ADJ_LPP, true>), ga, ba, 0, s, v, B, ro);
+    else
+        hipLaunchKernelGGL((k_adj_pass1<ADJ_LPP, false>), ga, ba, 0, s, v, B, ro);
     hipLaunchKernelGGL(k_fold_unpermute, dim3(blocks_for(n)), dim3(BLOCK), 0, s, n, perm, B,
                        dout);
     const hipError_t e = hipGetLastError();

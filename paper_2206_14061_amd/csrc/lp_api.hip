@@ -42,6 +42,8 @@ View make_view(lp_ctx* c, const double* const st[7])
     v.tile_src = w.tile_src;
     v.tile_cnt = w.tile_cnt;
     v.vs = w.vs;
+    v.ks = w.ks;
+    v.map_ok = c->map_ok ? 1 : 0;
     v.rec = w.rec;
     v.kmask = w.kmask;
     v.ghost_margin = c->cfg.ghost_margin;
@@ -81,6 +83,7 @@ void free_work(Work& w)
     for (int a = 0; a < 3; ++a) f(w.xref[a]);
     f(w.mirror_of); f(w.msrc); f(w.bsum); f(w.cs); f(w.ce);
     f(w.vl); f(w.vcnt); f(w.tile_src); f(w.tile_cnt); f(w.vs);
+    f(w.ks);
     f(w.rec); f(w.kmask); f(w.hard); f(w.hard_n);
     f(w.redo); f(w.redo_n);
     f(w.P); f(w.eta); f(w.hand); f(w.uf);
@@ -306,7 +309,7 @@ lp_status lp_reserve(lp_ctx* c, int64_t n_max, int64_t cells_max)
     if (e == hipSuccess) e = hipMemset(w.summary, 0, sizeof(Summary));
     // no tile is staged until a neighbour list is built
     if (e == hipSuccess)
-        e = hipMemset(w.tile_cnt, 0xFF, sizeof(int32_t) * ((n_max + BLOCK - 1) / BLOCK));
+        e = hipMemset(w.tile_cnt, 0xFF, 2 * sizeof(int32_t) * ((n_max + BLOCK - 1) / BLOCK));
     if (e == hipSuccess) {
         ErrWord ew{0, 0, ~0ull};
         e = hipMemcpy(w.err, &ew, sizeof(ew), hipMemcpyHostToDevice);
@@ -934,12 +937,13 @@ lp_status lp_stats(lp_ctx* c, int64_t* out8)
         out8[6] = out8[7] = (c->n + BLOCK - 1) / BLOCK;
     } else if (c->list_ok && c->n > 0) {
         const int64_t tiles = (c->n + BLOCK - 1) / BLOCK;
-        std::vector<int32_t> tc((size_t)tiles);
-        e = hipMemcpy(tc.data(), c->w.tile_cnt, sizeof(int32_t) * tiles,
+        std::vector<int32_t> tc((size_t)(2 * tiles));
+        e = hipMemcpy(tc.data(), c->w.tile_cnt, 2 * sizeof(int32_t) * tiles,
                       hipMemcpyDeviceToHost);
         if (e != hipSuccess) return hip_fail(c, e, "lp_stats");
         int64_t off = 0;
-        for (int32_t v : tc) off += (v < 0 || v > STAGE_CAP) ? 1 : 0;
+        // (staged in halves, or not at all)
+        for (int64_t t = 0; t < tiles; ++t) off += tc[2 * t + 1] != TILE_WHOLE ? 1 : 0;
         out8[6] = off;
         out8[7] = tiles;
     }

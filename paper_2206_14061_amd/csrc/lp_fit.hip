@@ -2,12 +2,13 @@
 // 2.2.1), right-hand side (Sec. 2.1) and explicit update (Sec. 3.1 steps
 // 8 and 10).
 //
-// Fit: one thread per particle accumulates the 9x9 Gram matrix
+// Fit: one thread per particle (a few lanes each where the particles are
+// few) accumulates the 9x9 Gram matrix
 // G = sum_r w a_r a_r^T and the moments sum_r w a_r b_r of its Taylor rows
 // (stencil rows plus ghost rows), factors G = U^T U (Cholesky) and solves.
 // The rows are scaled by 1/h, so G is well conditioned on every regular
-// stencil (the pivot ratio min U_jj / max U_jj is checked); this needs no
-// cross-lane reductions and keeps every accumulator in registers.  A
+// stencil (the pivot ratio min U_jj / max U_jj is checked); this keeps every
+// accumulator in registers.  A
 // stencil whose pivot ratio falls below the refit threshold is refitted
 // by float64 Householder QR (a wavefront per stencil), which
 // also applies the rank test min|r_jj|/max|r_jj| < fallback_tol.
@@ -301,34 +302,82 @@ __global__ __launch_bounds__(QR_TPB) void k_fit_generic_qr(
 
 // ---- lp_step pass 1: fit u, v, w + closure --------------------------------
 
+// The solves of one particle's pass-1 fit, shared by its LPP lanes: the
+// coefficients of u, v, w (in c3, for the lead lane) and the rows 0-2 of
+// G^-1, stored into the hand-off.
+template <int LPP, int N>
+__device__ __forceinline__ void pass1_solves(const double (&U)[45], const double (&B)[3][9],
+                                             int sub, double* hand, int64_t n, int64_t i,
+                                             double (&c3)[3][9])
+{
+    if (LPP < 4) {
+#pragma unroll
+        for (int f = 0; f < 3; ++f) {
+#pragma unroll
+            for (int q = 0; q < 9; ++q) c3[f][q] = q < N ? B[f][q] : 0.0;
+            chol_solve<N>(U, c3[f]);
+        }
+        if (sub == 0) store_ginv_rows<N>(U, hand, n, i);
+        return;
+    }
+    // right-hand side sub (+ LPP): u, v, w, then three unit vectors
+#pragma unroll
+    for (int t = 0; t < 6; t += LPP) {
+        const int f = t + sub;
+        double e[9];
+#pragma unroll
+        for (int q = 0; q < 9; ++q) {
+            const double unit = q == f - 3 ? 1.0 : 0.0;
+            e[q] = q >= N ? 0.0
+                   : t > 0 ? unit
+                   : f == 0 ? B[0][q] : (f == 1 ? B[1][q] : (f == 2 ? B[2][q] : unit));
+        }
+        chol_solve<N>(U, e);
+        if (f >= 3 && f < 6)
+#pragma unroll
+            for (int q = 0; q < 9; ++q)
+                hand[(int64_t)((f - 3) * 9 + q) * n + i] = q < N ? e[q] : 0.0;
+        if (t == 0)
+            // lanes 1 and 2 of the quad hand theirs to the lead
+#pragma unroll
+            for (int q = 0; q < 9; ++q) {
+                c3[0][q] = e[q];
+                c3[1][q] = dpp_move<0x55>(e[q]);
+                c3[2][q] = dpp_move<0xAA>(e[q]);
+            }
+    }
+}
+
 // Factor, solve and store one particle's pass-1 fit from its Gram moments
-// M and right-hand sides B (mt rows): coefficients, closure and the rows of
-// G^-1 for pass 2, or a queued QR refit when the Gram matrix is too ill
-// conditioned.  Only the lead lane of the particle writes.
+// M and right-hand sides B (mt rows; the same in its LPP lanes):
+// coefficients, closure and the rows of G^-1 for pass 2, or a queued QR
+// refit when the Gram matrix is too ill conditioned.
+template <int LPP>
 __device__ __forceinline__ void pass1_solve(const View& v, const StepOut& o,
                                             const GridInfo& g, int s, int64_t i,
                                             const double (&M)[31], double (&B)[3][9],
-                                            int mt, bool lead, int32_t* redo,
+                                            int mt, int sub, int32_t* redo,
                                             unsigned int* redo_n, int force_qr)
 {
     double G[45], c3[3][9], none[27];
     gram_from_moments(M, G);
-    uint8_t fl;
-    if (!gram_solve<3>(G, B, mt, v.redo_ratio, force_qr != 0, c3, none, false, fl)) {
-        if (lead) {
+    const bool lin = mt < 9;
+    const double ratio = lin ? cholesky<3>(G) : cholesky<9>(G);
+    if (ratio < v.redo_ratio || force_qr) {
+        if (sub == 0) {
             redo[atomicAdd(redo_n, 1u)] = (int32_t)i;
             o.flags[i] = FLAG_QR;
         }
         return;
     }
-    if (!lead) return;
+    if (lin) pass1_solves<LPP, 3>(G, B, sub, o.hand, v.n, i, c3);
+    else pass1_solves<LPP, 9>(G, B, sub, o.hand, v.n, i, c3);
+    if (sub != 0) return;
     double c[27];
 #pragma unroll
     for (int q = 0; q < 27; ++q)
         c[q] = c3[q / 9][q % 9] * ((q % 9) < 3 ? g.inv_h : g.inv_h * g.inv_h);
-    finish_pass1(v, v.prm[s], i, c, none, false, fl, o);
-    if (mt < 9) store_ginv_rows<3>(G, o.hand, v.n, i);
-    else store_ginv_rows<9>(G, o.hand, v.n, i);
+    finish_pass1(v, v.prm[s], i, c, none, false, lin ? FLAG_LINEAR : 0, o);
 }
 
 // LPP lanes per particle: each lane accumulates every LPP-th row; the
@@ -384,75 +433,104 @@ __global__ __launch_bounds__(BLOCK, 2) void k_pass1(View v, StepOut o,
             B[2][q] = lane_sum<LPP>(B[2][q]);
         }
     }
-    pass1_solve(v, o, g, s, i, M, B, order_rows(v, r, mt), sub == 0, redo, redo_n,
-                force_qr);
+    pass1_solve<LPP>(v, o, g, s, i, M, B, order_rows(v, r, mt), sub, redo, redo_n, force_qr);
 }
 
-// Pass 1 with the neighbours of the block's tile staged in LDS (one lane
-// per particle): the positions and velocities of the tile's list sources
+// Threads per block of the staged fits: a tile on one lane per particle, or
+// a part of it on more.
+constexpr int st_threads(int lpp) { return lpp == 1 ? BLOCK : 2 * BLOCK; }
+
+// Pass 1 with the neighbours of the block's tile staged in LDS, LPP lanes
+// per particle: the positions and velocities of the tile's list sources
 // are loaded once, coalesced, and every stencil row reads them from LDS.
+//
+// What bounds it: above ST_L8_MAX particles the vector ALU, two wavefronts
+// per SIMD (250 registers and 80 KB of LDS); below, the chain of one
+// particle.  Rows used to be found by walking the keep mask over the list's
+// slot words, with a mirror and a periodic case in each (115 vector
+// instructions a row, 73 of them the sums themselves); the selection now
+// leaves the kept rows' slots in list order, mirrors are sources of their
+// own, and both cases are compile-time: 176 -> 130 us at 524,288 particles,
+// 50 -> 37 at 131,072.  A tile with too many sources used to gather from
+// memory in one block, which the launch then waited for: 48 -> 21 us at
+// 33,263 particles (one such tile of 130), 514 -> 300 at 1,048,576 sheared
+// (377 of 4,096).
 // A tile that is not staged reads its neighbours from global memory as
-// k_pass1<1> does, and so does every tile when the tile map is stale
-// (map_ok = 0).  UNIT: the weights are unit
-// (known at compile time).
-template <bool UNIT>
+// k_pass1 does, and so does every tile when the staged rows are stale
+// (rows_ok = 0).  UNIT: the weights are unit, PERIODIC: some axis is
+// periodic (both known at compile time).
 // skip_rows > 0: particles whose stencils have at most skip_rows rows
 // (ghosts included) are left to the size-class launches.
-__global__ __launch_bounds__(BLOCK, 2) void k_pass1_st(View v, StepOut o,
-                                                       int32_t* redo,
-                                                       unsigned int* redo_n,
-                                                       int force_qr, int map_ok,
-                                                       int skip_rows)
+template <int LPP, bool UNIT, bool PERIODIC>
+__global__ __launch_bounds__(st_threads(LPP), 2) void k_pass1_st(View v, StepOut o,
+                                                                int32_t* redo,
+                                                                unsigned int* redo_n,
+                                                                int force_qr, int rows_ok,
+                                                                int skip_rows)
 {
+    constexpr int NT = st_threads(LPP), P = NT / LPP;
     __shared__ double sx[STAGE_CAP], sy[STAGE_CAP], sz[STAGE_CAP];
     __shared__ double su[STAGE_CAP], sv[STAGE_CAP], sw[STAGE_CAP];
-    const int64_t tile = xcd_block(blockIdx.x, gridDim.x);
-    const int64_t i = tile * BLOCK + threadIdx.x;
-    const int tc = map_ok ? v.tile_cnt[tile] : -1;
-    const int S = tc <= STAGE_CAP ? tc : -1;   // -1: not staged
-    if (S >= 0) {
-        stage_pass1(v, tile, S, sx, sy, sz, su, sv, sw);
+    const BlockPart<P> part(v, rows_ok);
+    if (part.idle()) return;
+    const StageUnit& unit = part.unit;
+    const int64_t i = part.i0 + threadIdx.x / LPP;
+    const int sub = threadIdx.x % LPP;
+    if (unit.S >= 0) {
+        stage_pass1<NT>(v, unit, sx, sy, sz, su, sv, sw);
         __syncthreads();
     }
-    if (i >= v.n) return;
+    const int64_t n = v.n;
+    if (i >= n || !part.mine(threadIdx.x / LPP)) return;
     const int s = sys_of(v.off, v.n_sys, i);
     const GridInfo& g = v.grid[s];
-    const Rec r = load_rec(v, i);
-    if (skip_rows > 0 && r.m + __popc((unsigned)r.gm & 0xFFu) <= skip_rows) return;
+    Rec r;
+    r.m = v.rec[REC_M * n + i];
+    r.gm = v.rec[REC_GM * n + i];
+    const int mt = r.m + __popc((unsigned)r.gm & 0xFFu);
+    if (skip_rows > 0 && mt <= skip_rows) return;
     const double ui = v.u[i], vi = v.v[i], wi = v.w[i];
     double M[31], B[3][9];
 #pragma unroll
     for (int q = 0; q < 31; ++q) M[q] = 0.0;
 #pragma unroll
     for (int q = 0; q < 9; ++q) B[0][q] = B[1][q] = B[2][q] = 0.0;
-    auto add_b = [&](const double* a, double w, double uj, double vj, double wj) {
-        const double b0 = w * (uj - ui), b1 = w * (vj - vi), b2 = w * (wj - wi);
-#pragma unroll
-        for (int q = 0; q < 9; ++q) {
-            B[0][q] += a[q] * b0;
-            B[1][q] += a[q] * b1;
-            B[2][q] += a[q] * b2;
-        }
+    auto add = [&](const double* a, double w, double uj, double vj, double wj) {
+        moments_add(M, a, w);
+        rhs_add(B[0], a, w * (uj - ui));
+        rhs_add(B[1], a, w * (vj - vi));
+        rhs_add(B[2], a, w * (wj - wi));
     };
-    int mt;
-    if (S >= 0) {
-        mt = for_rows_staged<FIT_BATCH, UNIT>(v, g, i, r, sx, sy, sz,
-                                        [&](const double* a, double w, const Pt* p) {
-            moments_add(M, a, w);
-            if (!p) return;   // ghosts carry u_i (b = 0)
-            const int q = p->src;
-            add_b(a, w, su[q], sv[q], p->mirror ? -sw[q] : sw[q]);
-        });
+    // ghosts carry u_i (b = 0)
+    auto add_ghost = [&](const double* a, double w) { moments_add(M, a, w); };
+    if (unit.S >= 0) {
+        for_rows_staged<LPP, UNIT, PERIODIC>(
+            v, g, i, r.m, r.gm, sub, sx, sy, sz, [&](const double* a, double w, uint32_t q) {
+                add(a, w, staged_at(su, q), staged_at(sv, q), staged_at(sw, q));
+            }, add_ghost);
     } else {
-        mt = for_rows(v, g, i, r, [&](const double* a, double w, const Pt* p) {
-            moments_add(M, a, w);
-            if (!p) return;
+        for_rows_sub<LPP>(v, g, i, load_rec(v, i), sub,
+                          [&](const double* a, double w, const Pt* p) {
+            if (!p) {
+                add_ghost(a, w);
+                return;
+            }
             double uj, vj, wj;
             point_velocity(v, *p, uj, vj, wj);
-            add_b(a, w, uj, vj, wj);
+            add(a, w, uj, vj, wj);
         });
     }
-    pass1_solve(v, o, g, s, i, M, B, order_rows(v, r, mt), true, redo, redo_n, force_qr);
+    if (LPP > 1) {
+#pragma unroll
+        for (int q = 0; q < 31; ++q) M[q] = lane_sum<LPP>(M[q]);
+#pragma unroll
+        for (int f = 0; f < 3; ++f)
+#pragma unroll
+            for (int q = 0; q < 9; ++q) B[f][q] = lane_sum<LPP>(B[f][q]);
+    }
+#pragma unroll
+    for (int f = 0; f < 3; ++f) halve_squares(B[f]);
+    pass1_solve<LPP>(v, o, g, s, i, M, B, order_rows(v, r, mt), sub, redo, redo_n, force_qr);
 }
 
 __global__ __launch_bounds__(QR_TPB) void k_pass1_qr(View v, StepOut o,
@@ -603,64 +681,104 @@ __global__ __launch_bounds__(BLOCK) void k_pass2(View v, const double* P,
     pass2_finish(v, prm, g, i, hand, yP, yE, Ei, o);
 }
 
-// Pass 2 with the neighbours of the block's tile staged in LDS (one lane
-// per particle): positions, P, eta and the pressure a mirror of each list
-// source carries are loaded once, coalesced, and every stencil row reads
-// them from LDS.  A tile that is not staged reads its neighbours from
-// global memory as k_pass2<1> does, and so does every tile when the tile
-// map is stale (map_ok = 0).  UNIT: the
-// weights are unit (known at compile time).
-template <bool UNIT>
-__global__ __launch_bounds__(BLOCK) void k_pass2_st(View v, const double* P,
-                                                    const double* eta,
-                                                    const double* hand,
-                                                    const uint8_t* flags, RhsOut o,
-                                                    int map_ok, int skip_rows)
+// Pass 2 with the neighbours of the block's tile staged in LDS, LPP lanes
+// per particle: positions, P and eta of the tile's list sources are loaded
+// once, coalesced, and every stencil row reads them from LDS.
+//
+// What bounds it: bytes (the hand-off's 37 doubles, the state, 300 MB at
+// 524,288 particles) and the vector ALU about alike; two lanes per particle
+// (four wavefronts per SIMD) take the same 98 us as one.  Before the kept
+// rows were read in order (as in pass 1) it took 146 us there, 49 at 131,072
+// (now 23), 42 at 33,263 (now 15), 455 at 1,048,576 sheared (now 232).
+//
+// A tile that
+// is not staged reads its neighbours from global memory as k_pass2 does,
+// and so does every tile when the staged rows are stale (rows_ok = 0).
+// UNIT: the weights are unit, PERIODIC: some axis is periodic (both known
+// at compile time).
+template <int LPP, bool UNIT, bool PERIODIC>
+__global__ __launch_bounds__(st_threads(LPP), LPP == 1 ? 2 : 4) void k_pass2_st(
+    View v, const double* P, const double* eta, const double* hand, const uint8_t* flags,
+    RhsOut o, int rows_ok, int skip_rows)
 {
+    constexpr int NT = st_threads(LPP), PB = NT / LPP;
     __shared__ double sx[STAGE_CAP], sy[STAGE_CAP], sz[STAGE_CAP];
-    __shared__ double sP[STAGE_CAP], sE[STAGE_CAP], sM[STAGE_CAP];
-    const int64_t tile = xcd_block(blockIdx.x, gridDim.x);
-    const int64_t i = tile * BLOCK + threadIdx.x;
-    const int tc = map_ok ? v.tile_cnt[tile] : -1;
-    const int S = tc <= STAGE_CAP ? tc : -1;   // -1: not staged
-    if (S >= 0) {
-        stage_pass2(v, P, eta, tile, S, sx, sy, sz, sP, sE, sM);
+    __shared__ double sP[STAGE_CAP], sE[STAGE_CAP];
+    const BlockPart<PB> part(v, rows_ok);
+    if (part.idle()) return;
+    const StageUnit& unit = part.unit;
+    const int64_t i = part.i0 + threadIdx.x / LPP;
+    const int sub = threadIdx.x % LPP;
+    if (unit.S >= 0) {
+        stage_pass2<NT>(v, P, eta, unit, sx, sy, sz, sP, sE);
         __syncthreads();
     }
-    if (i >= v.n) return;
+    const int64_t n = v.n;
+    if (i >= n || !part.mine(threadIdx.x / LPP)) return;
     if (flags[i] & FLAG_QR) return;
     const int s = sys_of(v.off, v.n_sys, i);
     const GridInfo& g = v.grid[s];
     const lp_params& prm = v.prm[s];
-    const Rec r = load_rec(v, i);
-    if (skip_rows > 0 && r.m + __popc((unsigned)r.gm & 0xFFu) <= skip_rows) return;
+    const int m = v.rec[REC_M * n + i], gm = v.rec[REC_GM * n + i];
+    if (skip_rows > 0 && m + __popc((unsigned)gm & 0xFFu) <= skip_rows) return;
     const double Pi = P[i], Ei = eta[i];
     double yP[9], yE[9];
 #pragma unroll
     for (int q = 0; q < 9; ++q) yP[q] = yE[q] = 0.0;
-    auto add_y = [&](const double* a, double w, double Pj, double Ej) {
-        const double bP = w * (Pj - Pi), bE = w * (Ej - Ei);
-#pragma unroll
-        for (int q = 0; q < 9; ++q) {
-            yP[q] += a[q] * bP;
-            yE[q] += a[q] * bE;
-        }
+    auto add = [&](const double* a, double w, double Pj, double Ej) {
+        rhs_add(yP, a, w * (Pj - Pi));
+        rhs_add(yE, a, w * (Ej - Ei));
     };
-    if (S >= 0) {
-        for_rows_staged<PASS2_BATCH, UNIT>(v, g, i, r, sx, sy, sz,
-                                     [&](const double* a, double w, const Pt* p) {
-            if (!p) add_y(a, w, 0.0, 0.0);
-            else if (p->mirror) add_y(a, w, sM[p->src], 0.0);
-            else add_y(a, w, sP[p->src], sE[p->src]);
-        });
+    if (unit.S >= 0) {
+        for_rows_staged<LPP, UNIT, PERIODIC>(
+            v, g, i, m, gm, sub, sx, sy, sz, [&](const double* a, double w, uint32_t q) {
+                add(a, w, staged_at(sP, q), staged_at(sE, q));
+            }, [&](const double* a, double w) { add(a, w, 0.0, 0.0); });
     } else {
-        for_rows<PASS2_BATCH>(v, g, i, r, [&](const double* a, double w, const Pt* p) {
+        for_rows_sub<LPP, PASS2_BATCH>(v, g, i, load_rec(v, i), sub,
+                                       [&](const double* a, double w, const Pt* p) {
             double Pj, Ej;
             pass2_values(v, P, eta, p, prm, Pj, Ej);
-            add_y(a, w, Pj, Ej);
+            add(a, w, Pj, Ej);
         });
     }
-    pass2_finish(v, prm, g, i, hand, yP, yE, Ei, o);
+    if (LPP > 1) {
+#pragma unroll
+        for (int q = 0; q < 9; ++q) {
+            yP[q] = lane_sum<LPP>(yP[q]);
+            yE[q] = lane_sum<LPP>(yE[q]);
+        }
+    }
+    halve_squares(yP);
+    halve_squares(yE);
+    // the gradients: lane sub takes the columns sub, sub + LPP, ... of the
+    // stored rows of G^-1
+    double gP[3] = {0.0, 0.0, 0.0}, gE[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int t = 0; t < 9; t += LPP) {
+        double a = yP[t], b = yE[t];
+#pragma unroll
+        for (int q = t + 1; q < t + LPP && q < 9; ++q) {
+            a = sub == q - t ? yP[q] : a;
+            b = sub == q - t ? yE[q] : b;
+        }
+        if (LPP > 1 && t + sub >= 9) continue;
+#pragma unroll
+        for (int rr = 0; rr < 3; ++rr) {
+            const double gi = hand[(int64_t)(rr * 9 + t + sub) * n + i];
+            gP[rr] += gi * a;
+            gE[rr] += gi * b;
+        }
+    }
+#pragma unroll
+    for (int rr = 0; rr < 3; ++rr) {
+        gP[rr] = lane_sum<LPP>(gP[rr]) * g.inv_h;
+        gE[rr] = lane_sum<LPP>(gE[rr]) * g.inv_h;
+    }
+    if (sub != 0) return;
+    double hv[11];
+    load_hand_tail(hand, n, i, Ei, hv);
+    finish_rhs(v, prm, i, hv, gP, gE, o);
 }
 
 // ---- refined FP32 fits ----------------------------------------------------
@@ -671,17 +789,6 @@ __global__ __launch_bounds__(BLOCK) void k_pass2_st(View v, const double* P,
 // (45 floats) is kept for pass 2, which refines the same way.  A stencil
 // whose float32 pivot ratio falls below the refit threshold takes the
 // float64 Householder refit of the float64 path.
-
-// rows per batch (measured at the 524,288-particle column): the moment
-// sweeps take those of the float64 fits; pass 1's float64 residual sweep,
-// which also holds three fields' coefficients and corrections, takes 2,
-// pass 2's (two fields) 4
-template <int B>
-struct RowBatch {
-    static constexpr int value = B;
-};
-constexpr int REF1_SWEEP_BATCH = 2;
-constexpr int REF2_SWEEP_BATCH = 4;
 
 template <int N>
 __device__ __forceinline__ void store_factor(const float (&U)[45], float* uf, int64_t n,
@@ -717,47 +824,44 @@ __device__ __forceinline__ void refine_step(const float (&U)[45], const double (
 // Both sweeps read their rows from the tile's LDS stage when the tile is
 // staged (as k_pass1_st does), else from global memory.  UNIT: the
 // weights are unit (known at compile time).
-template <bool UNIT>
+template <bool UNIT, bool PERIODIC>
 __global__ __launch_bounds__(BLOCK, 2) void k_pass1_ref(View v, StepOut o, float* uf,
                                                         int32_t* redo,
-                                                        unsigned int* redo_n, int map_ok)
+                                                        unsigned int* redo_n, int rows_ok)
 {
     __shared__ double sx[STAGE_CAP], sy[STAGE_CAP], sz[STAGE_CAP];
     __shared__ double su[STAGE_CAP], sv[STAGE_CAP], sw[STAGE_CAP];
-    const int64_t tile = xcd_block(blockIdx.x, gridDim.x);
-    const int64_t i = tile * BLOCK + threadIdx.x;
-    const int tc = map_ok ? v.tile_cnt[tile] : -1;
-    const int S = tc <= STAGE_CAP ? tc : -1;   // -1: not staged
-    if (S >= 0) {
-        stage_pass1(v, tile, S, sx, sy, sz, su, sv, sw);
+    const BlockPart<BLOCK> part(v, rows_ok);
+    if (part.idle()) return;
+    const StageUnit& unit = part.unit;
+    const int64_t i = part.i0 + threadIdx.x;
+    if (unit.S >= 0) {
+        stage_pass1(v, unit, sx, sy, sz, su, sv, sw);
         __syncthreads();
     }
-    if (i >= v.n) return;
+    if (i >= v.n || !part.mine(threadIdx.x)) return;
     const int64_t n = v.n;
     const int s = sys_of(v.off, v.n_sys, i);
     const GridInfo& g = v.grid[s];
-    const Rec r = load_rec(v, i);
+    Rec r;
+    r.m = v.rec[REC_M * n + i];
+    r.gm = v.rec[REC_GM * n + i];
     const double ui = v.u[i], vi = v.v[i], wi = v.w[i];
-    const bool staged = S >= 0;
-    // body(a, w, has, uj, vj, wj) for every row, bt.value rows at a time:
-    // has is false for a ghost row, which carries u_i
-    auto rows = [&](auto bt, auto&& body) -> int {
-        constexpr int RB = decltype(bt)::value;
+    const bool staged = unit.S >= 0;
+    // body(a, w, has, uj, vj, wj) for every row: has is false for a ghost
+    // row, which carries u_i
+    auto rows = [&](auto&& body) {
         if (staged)
-            return for_rows_staged<RB, UNIT>(v, g, i, r, sx, sy, sz,
-                                            [&](const double* a, double w, const Pt* p) {
-                if (!p) {
-                    body(a, w, false, ui, vi, wi);
-                    return;
-                }
-                const int q = p->src;
-                body(a, w, true, su[q], sv[q], p->mirror ? -sw[q] : sw[q]);
+            for_rows_staged<1, UNIT, PERIODIC>(
+                v, g, i, r.m, r.gm, 0, sx, sy, sz, [&](const double* a, double w, uint32_t q) {
+                    body(a, w, true, staged_at(su, q), staged_at(sv, q), staged_at(sw, q));
+                }, [&](const double* a, double w) { body(a, w, false, ui, vi, wi); });
+        else
+            for_rows(v, g, i, load_rec(v, i), [&](const double* a, double w, const Pt* p) {
+                double uj = ui, vj = vi, wj = wi;
+                if (p) point_velocity(v, *p, uj, vj, wj);
+                body(a, w, p != nullptr, uj, vj, wj);
             });
-        return for_rows<RB>(v, g, i, r, [&](const double* a, double w, const Pt* p) {
-            double uj = ui, vj = vi, wj = wi;
-            if (p) point_velocity(v, *p, uj, vj, wj);
-            body(a, w, p != nullptr, uj, vj, wj);
-        });
     };
     // ---- float32 moments and right-hand sides
     float M[31], B[3][9];
@@ -765,8 +869,8 @@ __global__ __launch_bounds__(BLOCK, 2) void k_pass1_ref(View v, StepOut o, float
     for (int q = 0; q < 31; ++q) M[q] = 0.0f;
 #pragma unroll
     for (int q = 0; q < 9; ++q) B[0][q] = B[1][q] = B[2][q] = 0.0f;
-    const int mt = rows(RowBatch<FIT_BATCH>{}, [&](const double* a, double w, bool has,
-                                                   double uj, double vj, double wj) {
+    const int mt = r.m + __popc((unsigned)r.gm & 0xFFu);
+    rows([&](const double* a, double w, bool has, double uj, double vj, double wj) {
         float af[9];
 #pragma unroll
         for (int q = 0; q < 9; ++q) af[q] = (float)a[q];
@@ -812,8 +916,7 @@ __global__ __launch_bounds__(BLOCK, 2) void k_pass1_ref(View v, StepOut o, float
     double d[3][9];
 #pragma unroll
     for (int q = 0; q < 9; ++q) d[0][q] = d[1][q] = d[2][q] = 0.0;
-    rows(RowBatch<REF1_SWEEP_BATCH>{}, [&](const double* a, double w, bool has, double uj,
-                                           double vj, double wj) {
+    rows([&](const double* a, double w, bool has, double uj, double vj, double wj) {
         double b0 = 0.0, b1 = 0.0, b2 = 0.0;   // ghosts carry u_i
         if (has) {
             b0 = uj - ui;
@@ -855,48 +958,46 @@ __global__ __launch_bounds__(BLOCK, 2) void k_pass1_ref(View v, StepOut o, float
 
 // Both sweeps read their rows from the tile's LDS stage when the tile is
 // staged (as k_pass2_st does), else from global memory.
-template <bool UNIT>
+template <bool UNIT, bool PERIODIC>
 __global__ __launch_bounds__(BLOCK, 2) void k_pass2_ref(View v, const double* P,
                                                      const double* eta,
                                                      const double* hand,
                                                      const float* uf,
                                                      const uint8_t* flags, RhsOut o,
-                                                     int map_ok)
+                                                     int rows_ok)
 {
     __shared__ double sx[STAGE_CAP], sy[STAGE_CAP], sz[STAGE_CAP];
-    __shared__ double sP[STAGE_CAP], sE[STAGE_CAP], sM[STAGE_CAP];
-    const int64_t tile = xcd_block(blockIdx.x, gridDim.x);
-    const int64_t i = tile * BLOCK + threadIdx.x;
-    const int tc = map_ok ? v.tile_cnt[tile] : -1;
-    const int S = tc <= STAGE_CAP ? tc : -1;   // -1: not staged
-    if (S >= 0) {
-        stage_pass2(v, P, eta, tile, S, sx, sy, sz, sP, sE, sM);
+    __shared__ double sP[STAGE_CAP], sE[STAGE_CAP];
+    const BlockPart<BLOCK> part(v, rows_ok);
+    if (part.idle()) return;
+    const StageUnit& unit = part.unit;
+    const int64_t i = part.i0 + threadIdx.x;
+    if (unit.S >= 0) {
+        stage_pass2(v, P, eta, unit, sx, sy, sz, sP, sE);
         __syncthreads();
     }
-    if (i >= v.n) return;
+    if (i >= v.n || !part.mine(threadIdx.x)) return;
     const uint8_t fl = flags[i];
     if (fl & FLAG_QR) return;
     const int64_t n = v.n;
     const int s = sys_of(v.off, v.n_sys, i);
     const GridInfo& g = v.grid[s];
     const lp_params& prm = v.prm[s];
-    const Rec r = load_rec(v, i);
+    Rec r;
+    r.m = v.rec[REC_M * n + i];
+    r.gm = v.rec[REC_GM * n + i];
     const bool lin = fl & FLAG_LINEAR;
     const double Pi = P[i], Ei = eta[i];
-    const bool staged = S >= 0;
-    // body(a, w, Pj, Ej) for every row (what pass2_values gives), bt.value
-    // rows at a time
-    auto rows = [&](auto bt, auto&& body) {
-        constexpr int RB = decltype(bt)::value;
+    const bool staged = unit.S >= 0;
+    // body(a, w, Pj, Ej) for every row (what pass2_values gives)
+    auto rows = [&](auto&& body) {
         if (staged)
-            for_rows_staged<RB, UNIT>(v, g, i, r, sx, sy, sz,
-                                             [&](const double* a, double w, const Pt* p) {
-                if (!p) body(a, w, 0.0, 0.0);
-                else if (p->mirror) body(a, w, sM[p->src], 0.0);
-                else body(a, w, sP[p->src], sE[p->src]);
-            });
+            for_rows_staged<1, UNIT, PERIODIC>(
+                v, g, i, r.m, r.gm, 0, sx, sy, sz, [&](const double* a, double w, uint32_t q) {
+                    body(a, w, staged_at(sP, q), staged_at(sE, q));
+                }, [&](const double* a, double w) { body(a, w, 0.0, 0.0); });
         else
-            for_rows<RB>(v, g, i, r, [&](const double* a, double w, const Pt* p) {
+            for_rows(v, g, i, load_rec(v, i), [&](const double* a, double w, const Pt* p) {
                 double Pj, Ej;
                 pass2_values(v, P, eta, p, prm, Pj, Ej);
                 body(a, w, Pj, Ej);
@@ -906,7 +1007,7 @@ __global__ __launch_bounds__(BLOCK, 2) void k_pass2_ref(View v, const double* P,
     float yP[9], yE[9];
 #pragma unroll
     for (int q = 0; q < 9; ++q) yP[q] = yE[q] = 0.0f;
-    rows(RowBatch<PASS2_BATCH>{}, [&](const double* a, double w, double Pj, double Ej) {
+    rows([&](const double* a, double w, double Pj, double Ej) {
         const float bP = (float)(w * (Pj - Pi)), bE = (float)(w * (Ej - Ei));
 #pragma unroll
         for (int q = 0; q < 9; ++q) {
@@ -942,7 +1043,7 @@ __global__ __launch_bounds__(BLOCK, 2) void k_pass2_ref(View v, const double* P,
     double d[2][9];
 #pragma unroll
     for (int q = 0; q < 9; ++q) d[0][q] = d[1][q] = 0.0;
-    rows(RowBatch<REF2_SWEEP_BATCH>{}, [&](const double* a, double w, double Pj, double Ej) {
+    rows([&](const double* a, double w, double Pj, double Ej) {
         double rP = Pj - Pi, rE = Ej - Ei;
 #pragma unroll
         for (int q = 0; q < 9; ++q) {
@@ -1069,6 +1170,66 @@ static lp_status need_stencils(lp_ctx* c)
 
 namespace {
 
+// Particles up to which the staged fits take eight lanes each: one round of
+// their blocks (64 particles) on 256 CUs.  Measured, us per launch (pass 1,
+// pass 2) on eight lanes and on one: 4,096 particles 14.4, 8.0 and 18.9,
+// 13.4; 12,075 15.6, 8.7 and 19.6, 13.8; 33,263 43, 19.6 and 21.1, 14.7.
+constexpr int64_t ST_L8_MAX = 16384;
+
+// f(unit, periodic) with both as compile-time constants.
+template <class F>
+void by_kind(const lp_ctx* c, F&& f)
+{
+    if (c->cfg.weight == LP_W_UNIT) {
+        if (c->periodic) f(std::true_type{}, std::true_type{});
+        else f(std::true_type{}, std::false_type{});
+    } else {
+        if (c->periodic) f(std::false_type{}, std::true_type{});
+        else f(std::false_type{}, std::false_type{});
+    }
+}
+
+// The fits may read the staged rows of the last selection.
+int staged_rows(const lp_ctx* c) { return c->map_ok && c->rows_ok ? 1 : 0; }
+
+template <int LPP>
+void launch_pass1_st(lp_ctx* c, const View& v, const StepOut& so, int fq, int skip_rows)
+{
+    Work& w = c->w;
+    constexpr int NT = st_threads(LPP);
+    by_kind(c, [&](auto unit, auto per) {
+        hipLaunchKernelGGL((k_pass1_st<LPP, unit.value, per.value>),
+                           dim3(BlockPart<NT / LPP>::blocks(c->n)), dim3(NT), 0, c->stream, v, so,
+                           w.redo, w.redo_n, fq, staged_rows(c), skip_rows);
+    });
+}
+
+template <int LPP>
+void launch_pass2_st(lp_ctx* c, const View& v, const RhsOut& o, int skip_rows)
+{
+    Work& w = c->w;
+    constexpr int NT = st_threads(LPP);
+    by_kind(c, [&](auto unit, auto per) {
+        hipLaunchKernelGGL((k_pass2_st<LPP, unit.value, per.value>),
+                           dim3(BlockPart<NT / LPP>::blocks(c->n)), dim3(NT), 0, c->stream, v,
+                           (const double*)w.P, (const double*)w.eta, (const double*)w.hand,
+                           (const uint8_t*)w.flags, o, staged_rows(c), skip_rows);
+    });
+}
+
+// The staged fits: lanes per particle by the particle count.
+void launch_pass1_tiles(lp_ctx* c, const View& v, const StepOut& so, int fq, int skip_rows)
+{
+    if (c->n <= ST_L8_MAX) launch_pass1_st<8>(c, v, so, fq, skip_rows);
+    else launch_pass1_st<1>(c, v, so, fq, skip_rows);
+}
+
+void launch_pass2_tiles(lp_ctx* c, const View& v, const RhsOut& o, int skip_rows)
+{
+    if (c->n <= ST_L8_MAX) launch_pass2_st<8>(c, v, o, skip_rows);
+    else launch_pass2_st<1>(c, v, o, skip_rows);
+}
+
 void launch_pass1(lp_ctx* c, int lpp, const View& v, const StepOut& so, int fq)
 {
     Work& w = c->w;
@@ -1084,15 +1245,7 @@ void launch_pass1(lp_ctx* c, int lpp, const View& v, const StepOut& so, int fq)
         hipLaunchKernelGGL((k_pass1<2>), dim3(blocks_for(2 * n)), dim3(BLOCK), 0,
                            c->stream, v, so, w.redo, w.redo_n, fq, no, nc);
         break;
-    default:
-        if (c->cfg.weight == LP_W_UNIT)
-            hipLaunchKernelGGL(k_pass1_st<true>, dim3(blocks_for(n)), dim3(BLOCK), 0,
-                               c->stream, v, so, w.redo, w.redo_n, fq, c->map_ok ? 1 : 0,
-                               0);
-        else
-            hipLaunchKernelGGL(k_pass1_st<false>, dim3(blocks_for(n)), dim3(BLOCK), 0,
-                               c->stream, v, so, w.redo, w.redo_n, fq, c->map_ok ? 1 : 0,
-                               0);
+    default: launch_pass1_tiles(c, v, so, fq, 0);
     }
 }
 
@@ -1115,13 +1268,7 @@ void launch_pass2(lp_ctx* c, int lpp, const View& v, const RhsOut& o)
         hipLaunchKernelGGL((k_pass2<2>), dim3(blocks_for(2 * n)), dim3(BLOCK), 0,
                            c->stream, v, P, E, H, F, o, no, nc);
         break;
-    default:
-        if (c->cfg.weight == LP_W_UNIT)
-            hipLaunchKernelGGL(k_pass2_st<true>, dim3(blocks_for(n)), dim3(BLOCK), 0,
-                               c->stream, v, P, E, H, F, o, c->map_ok ? 1 : 0, 0);
-        else
-            hipLaunchKernelGGL(k_pass2_st<false>, dim3(blocks_for(n)), dim3(BLOCK), 0,
-                               c->stream, v, P, E, H, F, o, c->map_ok ? 1 : 0, 0);
+    default: launch_pass2_tiles(c, v, o, 0);
     }
 }
 
@@ -1147,13 +1294,7 @@ void launch_pass1_class(lp_ctx* c, int cls, int lpp, const View& v, const StepOu
     const uint32_t* cnt = w.cls_cnt + cls;
     if (lpp == 0) {
         // the largest class through the LDS-staged tile kernel
-        const int mo = c->map_ok ? 1 : 0;
-        if (c->cfg.weight == LP_W_UNIT)
-            hipLaunchKernelGGL(k_pass1_st<true>, dim3(blocks_for(n)), dim3(BLOCK), 0,
-                               c->stream, v, so, w.redo, w.redo_n, fq, mo, CLASS_ROWS1);
-        else
-            hipLaunchKernelGGL(k_pass1_st<false>, dim3(blocks_for(n)), dim3(BLOCK), 0,
-                               c->stream, v, so, w.redo, w.redo_n, fq, mo, CLASS_ROWS1);
+        launch_pass1_tiles(c, v, so, fq, CLASS_ROWS1);
         return;
     }
     switch (lpp) {
@@ -1182,13 +1323,7 @@ void launch_pass2_class(lp_ctx* c, int cls, int lpp, const View& v, const RhsOut
     const double* H = w.hand;
     const uint8_t* F = w.flags;
     if (lpp == 0) {
-        const int mo = c->map_ok ? 1 : 0;
-        if (c->cfg.weight == LP_W_UNIT)
-            hipLaunchKernelGGL(k_pass2_st<true>, dim3(blocks_for(n)), dim3(BLOCK), 0,
-                               c->stream, v, P, E, H, F, o, mo, CLASS_ROWS1);
-        else
-            hipLaunchKernelGGL(k_pass2_st<false>, dim3(blocks_for(n)), dim3(BLOCK), 0,
-                               c->stream, v, P, E, H, F, o, mo, CLASS_ROWS1);
+        launch_pass2_tiles(c, v, o, CLASS_ROWS1);
         return;
     }
     switch (lpp) {
@@ -1339,13 +1474,12 @@ lp_status step_rhs(lp_ctx* c, const double* const st[7])
         if (c->cfg.fit_order == 3)
             launch_pass1_cubic(c, v, so);
         else if (c->cfg.precision == LP_FP32_REFINED && !fq) {
-            const int mo = c->map_ok ? 1 : 0;
-            if (c->cfg.weight == LP_W_UNIT)
-                hipLaunchKernelGGL(k_pass1_ref<true>, dim3(blocks_for(n)), dim3(BLOCK), 0,
-                                   c->stream, v, so, w.uf, w.redo, w.redo_n, mo);
-            else
-                hipLaunchKernelGGL(k_pass1_ref<false>, dim3(blocks_for(n)), dim3(BLOCK), 0,
-                                   c->stream, v, so, w.uf, w.redo, w.redo_n, mo);
+            by_kind(c, [&](auto unit, auto per) {
+                hipLaunchKernelGGL((k_pass1_ref<unit.value, per.value>),
+                                   dim3(BlockPart<BLOCK>::blocks(n)),
+                                   dim3(BLOCK), 0, c->stream, v, so, w.uf, w.redo, w.redo_n,
+                                   staged_rows(c));
+            });
         }
         else
             run_pass1(c, v, so, fq);
@@ -1395,17 +1529,14 @@ lp_status step_pass2(lp_ctx* c, const double* const st[7], double dt,
         if (c->cfg.fit_order == 3)
             launch_pass2_cubic(c, v, w.P, w.eta, w.hand, o);
         else if (c->cfg.precision == LP_FP32_REFINED && !fp64) {
-            const int mo = c->map_ok ? 1 : 0;
-            if (c->cfg.weight == LP_W_UNIT)
-                hipLaunchKernelGGL(k_pass2_ref<true>, dim3(blocks_for(n)), dim3(BLOCK), 0,
-                                   c->stream, v, (const double*)w.P, (const double*)w.eta,
-                                   (const double*)w.hand, (const float*)w.uf,
-                                   (const uint8_t*)w.flags, o, mo);
-            else
-                hipLaunchKernelGGL(k_pass2_ref<false>, dim3(blocks_for(n)), dim3(BLOCK), 0,
-                                   c->stream, v, (const double*)w.P, (const double*)w.eta,
-                                   (const double*)w.hand, (const float*)w.uf,
-                                   (const uint8_t*)w.flags, o, mo);
+            by_kind(c, [&](auto unit, auto per) {
+                hipLaunchKernelGGL((k_pass2_ref<unit.value, per.value>),
+                                   dim3(BlockPart<BLOCK>::blocks(n)),
+                                   dim3(BLOCK), 0, c->stream, v, (const double*)w.P,
+                                   (const double*)w.eta, (const double*)w.hand,
+                                   (const float*)w.uf, (const uint8_t*)w.flags, o,
+                                   staged_rows(c));
+            });
         }
         else
             run_pass2(c, v, o);
@@ -1482,6 +1613,9 @@ lp_status autotune_fits(lp_ctx* c, const double* const st[7], int32_t* choice)
     uint32_t counts[4] = {0, 0, 0, 0};
     if (e == hipSuccess && c->cfg.precision == LP_FP64 && c->n > 0) {
         classify(c, v);
+        // (few particles: the staged kernel on eight lanes is left to the one
+        // launch over all of them)
+        const int first = c->n > ST_L8_MAX ? -1 : 0;
         e = hipMemcpyAsync(counts, w.cls_cnt, sizeof(uint32_t) * NCLASS,
                            hipMemcpyDeviceToHost, c->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
@@ -1491,7 +1625,7 @@ lp_status autotune_fits(lp_ctx* c, const double* const st[7], int32_t* choice)
                 cb1[k] = 0.f;
                 continue;
             }
-            for (int q = (k == NCLASS - 1 ? -1 : 0); q < 3 && e == hipSuccess; ++q) {
+            for (int q = (k == NCLASS - 1 ? first : 0); q < 3 && e == hipSuccess; ++q) {
                 const int l = q < 0 ? 0 : cand[q];   // 0: staged tile kernel
                 const float t = timed([&] { launch_pass1_class(c, k, l, v, so, 0); });
                 if (t < cb1[k]) { cb1[k] = t; cp1[k] = l; }
@@ -1507,7 +1641,7 @@ lp_status autotune_fits(lp_ctx* c, const double* const st[7], int32_t* choice)
                 cb2[k] = 0.f;
                 continue;
             }
-            for (int q = (k == NCLASS - 1 ? -1 : 0); q < 3 && e == hipSuccess; ++q) {
+            for (int q = (k == NCLASS - 1 ? first : 0); q < 3 && e == hipSuccess; ++q) {
                 const int l = q < 0 ? 0 : cand[q];
                 const float t = timed([&] { launch_pass2_class(c, k, l, v, o); });
                 if (t < cb2[k]) { cb2[k] = t; cp2[k] = l; }

@@ -265,61 +265,35 @@ __device__ __forceinline__ int for_rows(const View& v, const GridInfo& g,
     return m;
 }
 
-// for_rows for a particle of a staged tile: stencil rows from the LDS
-// copies (sx, sy, sz) through visit_staged, then the ghost rows.
-// UNIT: the weights are unit (LP_W_UNIT), so f receives the constant 1.
-template <int B, bool UNIT, class F>
-__device__ __forceinline__ int for_rows_staged(const View& v, const GridInfo& g,
-                                               int64_t i, const Rec& r, const double* sx,
-                                               const double* sy, const double* sz, F&& f)
+// for_rows for a particle of a staged tile with m stencil rows and ghost
+// mask gm, spread over LPP adjacent lanes: this lane's stencil rows from the
+// LDS copies (sx, sy, sz) through visit_staged as f(a, w, off), then its
+// ghost rows (o mod LPP = sub) as ghost(a, w).  UNIT: the weights are unit
+// (LP_W_UNIT), so f receives the constant 1.
+template <int LPP, bool UNIT, bool PERIODIC, class F, class FG>
+__device__ __forceinline__ void for_rows_staged(const View& v, const GridInfo& g, int64_t i,
+                                                int m, int gm, int sub, const double* sx,
+                                                const double* sy, const double* sz, F&& f,
+                                                FG&& ghost)
 {
-    int m = 0;
     const Seen s = seen_from(v, g, i);
-    visit_staged<B>(v, s, i, r, sx, sy, sz,
-                    [&](const Pt& p, double dx, double dy, double dz) {
+    const double ih = g.inv_h, R2 = g.R2;
+    visit_staged<LPP, PERIODIC>(v, s, i, m, sub, sx, sy, sz,
+                                [&](uint32_t off, double dx, double dy, double dz) {
         double a[9];
-        const double w = point_row(v, g, dx, dy, dz, a);
-        f(a, UNIT ? 1.0 : w, &p);
-        ++m;
+        taylor_row(dx * ih, dy * ih, dz * ih, a);
+        f(a, UNIT ? 1.0 : exp(-4.0 * (dx * dx + dy * dy + dz * dz) / R2), off);
     });
+    if ((gm & 0xFF) == 0) return;
+    const double wg = UNIT ? 1.0 : exp(-12.0 * g.h * g.h / R2);
 #pragma unroll
     for (int o = 0; o < 8; ++o)
-        if ((r.gm >> o) & 1) {
-            double a[9];
-            const double w = ghost_row(v, g, o, a);
-            f(a, UNIT ? 1.0 : w, (const Pt*)nullptr);
-            ++m;
+        if (((gm >> o) & 1) && (o % LPP) == sub) {
+            double sx1, sy1, sz1, a[9];
+            ghost_offset(o, sx1, sy1, sz1);
+            taylor_row(sx1, sy1, sz1, a);
+            ghost(a, wg);
         }
-    return m;
-}
-
-// for_rows_staged with the rows spread over LPP adjacent lanes: lane sub
-// takes the kept rows sub, sub + LPP, ... (visit_staged_sub) and the ghost
-// rows o with o mod LPP = sub; returns this lane's rows.
-template <int B, int LPP, bool UNIT, class F>
-__device__ __forceinline__ int for_rows_staged_sub(const View& v, const GridInfo& g,
-                                                   int64_t i, const Rec& r, int sub,
-                                                   const double* sx, const double* sy,
-                                                   const double* sz, F&& f)
-{
-    int m = 0;
-    const Seen s = seen_from(v, g, i);
-    visit_staged_sub<B, LPP>(v, s, i, r, sub, sx, sy, sz,
-                             [&](const Pt& p, double dx, double dy, double dz) {
-        double a[9];
-        const double w = point_row(v, g, dx, dy, dz, a);
-        f(a, UNIT ? 1.0 : w, &p);
-        ++m;
-    });
-#pragma unroll
-    for (int o = 0; o < 8; ++o)
-        if (((r.gm >> o) & 1) && (o % LPP) == sub) {
-            double a[9];
-            const double w = ghost_row(v, g, o, a);
-            f(a, UNIT ? 1.0 : w, (const Pt*)nullptr);
-            ++m;
-        }
-    return m;
 }
 
 // for_rows with the rows spread over LPP lanes (stencil rows as in
@@ -398,6 +372,29 @@ __device__ __forceinline__ void moments_add(T (&M)[31], const T* a, T w)
     M[30] += wzz * xy;
 }
 
+// y += b (x, y, z, xx, yy, zz, xy, xz, yz): a row's right-hand side with the
+// squares' halves left to halve_squares, once per particle (exact).
+template <class T>
+__device__ __forceinline__ void rhs_add(T (&y)[9], const T* a, T b)
+{
+    y[0] += a[0] * b;
+    y[1] += a[1] * b;
+    y[2] += a[2] * b;
+    y[3] += (a[0] * a[0]) * b;
+    y[4] += (a[1] * a[1]) * b;
+    y[5] += (a[2] * a[2]) * b;
+    y[6] += a[6] * b;
+    y[7] += a[7] * b;
+    y[8] += a[8] * b;
+}
+template <class T>
+__device__ __forceinline__ void halve_squares(T (&y)[9])
+{
+    y[3] *= T(0.5);
+    y[4] *= T(0.5);
+    y[5] *= T(0.5);
+}
+
 template <class T>
 __device__ __forceinline__ void gram_from_moments(const T (&M)[31], T (&G)[45])
 {
@@ -458,8 +455,7 @@ __device__ __forceinline__ void pass2_values(const View& v, const double* P,
 // ---- staging of a tile's list sources in LDS (fits and their adjoints) --
 
 // Staged sources per thread of a block of NT threads, and this thread's
-// source ids in the tile (slot threadIdx.x + u NT; -1 past the tile's S
-// sources).
+// source ids in the unit (slot threadIdx.x + u NT; -1 past its sources).
 template <int NT = BLOCK>
 constexpr int stage_per() { return (STAGE_CAP + NT - 1) / NT; }
 // six staged FP64 fields per source; two blocks must fit one CU's 160 KB
@@ -467,32 +463,32 @@ static_assert(2 * 6 * STAGE_CAP * (int)sizeof(double) <= 160 * 1024,
               "two staged fit blocks per CU");
 
 template <int NT = BLOCK>
-__device__ __forceinline__ void stage_ids(const View& v, int64_t tile, int S,
+__device__ __forceinline__ void stage_ids(const StageUnit& su,
                                           int32_t (&js)[stage_per<NT>()])
 {
-    const int32_t* src = v.tile_src + tile * STAGE_CAP;
 #pragma unroll
     for (int u = 0; u < stage_per<NT>(); ++u) {
         const int q = (int)threadIdx.x + u * NT;
-        js[u] = q < S ? src[q] : -1;
+        js[u] = q < su.S ? su.src[q] : -1;
     }
 }
 
-// Loads the positions and velocities of the tile's S list sources into
-// LDS (slot q holds the q-th source of the tile's sorted set): every
-// thread takes its sources at once, their ids first, then their fields.
+// Loads the positions and velocities of a unit's list sources into
+// LDS (slot q holds the q-th of them; a mirror its
+// reflection): every thread takes its sources at once, their ids first,
+// then their fields.
 template <int NT = BLOCK>
-__device__ __forceinline__ void stage_pass1(const View& v, int64_t tile, int S, double* sx,
-                                            double* sy, double* sz, double* su,
+__device__ __forceinline__ void stage_pass1(const View& v, const StageUnit& unit,
+                                            double* sx, double* sy, double* sz, double* su,
                                             double* sv, double* sw)
 {
     constexpr int SP = stage_per<NT>();
     int32_t js[SP];
-    stage_ids<NT>(v, tile, S, js);
+    stage_ids<NT>(unit, js);
     double f[6][SP];
 #pragma unroll
     for (int u = 0; u < SP; ++u) {
-        const int32_t j = js[u] < 0 ? 0 : js[u];
+        const int32_t j = js[u] < 0 ? 0 : js[u] & ~MBIT;
         f[0][u] = v.x[j];
         f[1][u] = v.y[j];
         f[2][u] = v.z[j];
@@ -504,6 +500,11 @@ __device__ __forceinline__ void stage_pass1(const View& v, int64_t tile, int S, 
     for (int u = 0; u < SP; ++u) {
         if (js[u] < 0) continue;
         const int q = (int)threadIdx.x + u * NT;
+        if (js[u] & MBIT) {
+            const GridInfo& g = v.grid[sys_of(v.off, v.n_sys, js[u] & ~MBIT)];
+            f[2][u] = dsub(dmul(2.0, g.wall), f[2][u]);
+            f[5][u] = -f[5][u];
+        }
         sx[q] = f[0][u];
         sy[q] = f[1][u];
         sz[q] = f[2][u];
@@ -513,21 +514,21 @@ __device__ __forceinline__ void stage_pass1(const View& v, int64_t tile, int S, 
     }
 }
 
-// Loads the positions, P and eta of the tile's S list sources into LDS,
-// with the pressure a mirror of each source carries (pass2_values).
+// Loads the positions, P and eta of a unit's list sources into LDS (a
+// mirror's: its reflection and what pass2_values gives it).
 template <int NT = BLOCK>
 __device__ __forceinline__ void stage_pass2(const View& v, const double* P,
-                                            const double* eta, int64_t tile, int S,
+                                            const double* eta, const StageUnit& unit,
                                             double* sx, double* sy, double* sz,
-                                            double* sP, double* sE, double* sM)
+                                            double* sP, double* sE)
 {
     constexpr int SP = stage_per<NT>();
     int32_t js[SP];
-    stage_ids<NT>(v, tile, S, js);
+    stage_ids<NT>(unit, js);
     double f[5][SP];
 #pragma unroll
     for (int u = 0; u < SP; ++u) {
-        const int32_t j = js[u] < 0 ? 0 : js[u];
+        const int32_t j = js[u] < 0 ? 0 : js[u] & ~MBIT;
         f[0][u] = v.x[j];
         f[1][u] = v.y[j];
         f[2][u] = v.z[j];
@@ -538,26 +539,21 @@ __device__ __forceinline__ void stage_pass2(const View& v, const double* P,
     for (int u = 0; u < SP; ++u) {
         if (js[u] < 0) continue;
         const int q = (int)threadIdx.x + u * NT;
-        const int32_t j = js[u];
+        if (js[u] & MBIT) {
+            // (its system is that of every particle listing it)
+            Pt m;
+            m.mirror = true;
+            m.src = js[u] & ~MBIT;
+            const int sj = sys_of(v.off, v.n_sys, m.src);
+            m.z = dsub(dmul(2.0, v.grid[sj].wall), f[2][u]);
+            pass2_values(v, P, eta, &m, v.prm[sj], f[3][u], f[4][u]);
+            f[2][u] = m.z;
+        }
         sx[q] = f[0][u];
         sy[q] = f[1][u];
         sz[q] = f[2][u];
         sP[q] = f[3][u];
         sE[q] = f[4][u];
-        // j's system is that of every particle listing it.  Only a source
-        // within R of the wall has a mirror (the rule that sets mirror_of).
-        const int sj = sys_of(v.off, v.n_sys, j);
-        const GridInfo& gj = v.grid[sj];
-        double pm = 0.0;
-        if (dsub(f[2][u], gj.wall) < gj.R) {
-            Pt m;
-            m.mirror = true;
-            m.src = j;
-            m.z = dsub(dmul(2.0, gj.wall), f[2][u]);
-            double em;
-            pass2_values(v, P, eta, &m, v.prm[sj], pm, em);
-        }
-        sM[q] = pm;
     }
 }
 

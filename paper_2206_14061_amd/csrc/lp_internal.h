@@ -67,13 +67,15 @@ __device__ __forceinline__ void vs_store4(uint16_t* vs, int64_t n, int64_t i, in
 }
 // A tile is BLOCK consecutive particles.  The fits stage the fields of the
 // distinct sources of a tile's neighbour lists in LDS (at most STAGE_CAP
-// of them); a list entry names its source's slot in a 16-bit word whose
-// top bit marks a mirror entry.
+// of them); a list entry names its source's slot in a 16-bit word (8 x slot,
+// the byte offset in a staged field).  A mirror is a source of its own (its
+// id is MBIT | the particle it reflects), after all real ones, so that a row
+// needs no mirror case.  A tile with more sources than fit is staged in
+// halves, each half with its own sources and slots.
 #ifndef LP_STAGE_CAP
 #define LP_STAGE_CAP 1664
 #endif
 constexpr int STAGE_CAP = LP_STAGE_CAP;
-constexpr uint32_t SLOT_MIRROR = 0x8000u;
 constexpr int32_t MBIT = 0x40000000;  // list entry: mirror of the real id
 constexpr int32_t NOID = 0x7FFFFFFF;
 // per-particle stencil record (int32 fields, field f of particle i at
@@ -84,8 +86,19 @@ constexpr int HAND = 37;          // pass-1 -> pass-2 handoff doubles
 // stencil size classes of the fits (rows, ghosts included): at most 16,
 // at most 32, more
 constexpr int NCLASS = 3;
-constexpr int CLASS_ROWS0 = 16, CLASS_ROWS1 = 32;
 constexpr int BLOCK = 256;        // threads per block of per-particle kernels
+constexpr int HALF = BLOCK / 2;   // particles of half a tile
+// Words 2 t, 2 t + 1 of tile_cnt are the halves of tile t (their sources are
+// at STAGE_CAP times these in tile_src); the second is TILE_WHOLE when the
+// first stands for the whole tile.  A word holds the unit's sources and how
+// many of them are real, or -1: not staged.
+constexpr int32_t TILE_WHOLE = -2;
+__host__ __device__ __forceinline__ int tile_slots(int32_t tc)
+{
+    return tc < 0 ? -1 : tc & 0xFFFF;
+}
+__host__ __device__ __forceinline__ int tile_reals(int32_t tc) { return tc >> 16; }
+constexpr int CLASS_ROWS0 = 16, CLASS_ROWS1 = 32;
 constexpr int SORT_ITEMS = 16;    // keys per thread in a radix tile
 constexpr int RADIX_MAX_BITS = 9; // digit width of the radix sort, at most
 constexpr int RADIX_MAX_DIGITS = 1 << RADIX_MAX_BITS;
@@ -147,6 +160,9 @@ struct Counters {
     unsigned long long pad[4];
 };
 
+// Row words held per particle for a stencil cap of mm.
+__host__ __device__ constexpr int row_cap(int mm) { return (mm + 3) / 4 * 4; }
+
 // Everything a per-particle kernel needs to find neighbours and states.
 struct View {
     int64_t n;                  // real particles
@@ -166,11 +182,16 @@ struct View {
     // neighbour list with skin (entry k of particle i at vl_at(n, i, k))
     const int32_t* vl;
     const int32_t* vcnt;
-    // per tile: its list sources in ascending order (STAGE_CAP per tile)
-    // and their count (-1: not staged); slot of every list entry
+    // per half tile: its list sources in ascending order (STAGE_CAP each)
+    // and their counts (tile_slots, tile_reals); slot of every list entry
     const int32_t* tile_src;
     const int32_t* tile_cnt;
     const uint16_t* vs;
+    // slot words of the kept rows of a particle that is staged, in list
+    // order, laid out as those of the list are; written by the selection
+    // when map_ok is set
+    uint16_t* ks;
+    int32_t map_ok;             // the tile map matches the list
     // stencil records and keep bitmasks
     int32_t* rec;
     uint64_t* kmask;            // MASK_WORDS x n
@@ -214,9 +235,10 @@ struct Work {
     // neighbour list, records, sorted-path stencils
     int32_t* vl = nullptr;
     int32_t* vcnt = nullptr;
-    int32_t* tile_src = nullptr;          // tiles x STAGE_CAP
-    int32_t* tile_cnt = nullptr;          // tiles
+    int32_t* tile_src = nullptr;          // 2 x tiles x STAGE_CAP
+    int32_t* tile_cnt = nullptr;          // 2 x tiles
     uint16_t* vs = nullptr;               // VCAP x n
+    uint16_t* ks = nullptr;               // row_cap(m_max) x n
     int32_t* rec = nullptr;
     uint64_t* kmask = nullptr;            // MASK_WORDS x n
     int32_t* hard = nullptr;
@@ -276,9 +298,10 @@ constexpr void work_layout(Work& w, int64_t n_max, int64_t cells_max, int mm,
     A(w.mirror_of, n_max); A(w.msrc, n_max); A(w.bsum, nb + 1);
     A(w.cs, cells_max); A(w.ce, cells_max);
     A(w.vl, (int64_t)VCAP * n_max); A(w.vcnt, n_max);
-    A(w.tile_src, (int64_t)STAGE_CAP * tiles);
-    A(w.tile_cnt, tiles);
+    A(w.tile_src, 2 * (int64_t)STAGE_CAP * tiles);
+    A(w.tile_cnt, 2 * tiles);
     A(w.vs, (int64_t)VCAP * n_max);
+    A(w.ks, (int64_t)row_cap(mm) * n_max);
     A(w.kmask, (int64_t)MASK_WORDS * n_max);
     A(w.rec, (int64_t)REC_FIELDS * n_max); 
     A(w.hard, n_max); A(w.hard_n, 1);
@@ -312,6 +335,7 @@ struct lp_ctx {
     std::vector<lp_params> h_prm;
     bool periodic = false;                // some system has a periodic axis
     bool map_ok = false;                  // the tile map matches the current list
+    bool rows_ok = false;                 // the last selection wrote the staged rows
     lp::Work w;
     int axis_bits = 0;
     int64_t total_cells = 0;

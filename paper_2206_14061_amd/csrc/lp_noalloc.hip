@@ -67,7 +67,7 @@ __global__ void k_noalloc_clear(ErrWord* err, Counters* cnt, Summary* sum,
         *cnt = Counters{};
         *sum = Summary{};
     }
-    if (i < tiles) tile_cnt[i] = -1;
+    if (i < 2 * tiles) tile_cnt[i] = -1;
 }
 
 void init_slot(DevSlot& d)
@@ -153,7 +153,7 @@ extern "C" lp_status lp_step_noalloc(void* stream, const lp_config* cfg, int32_t
     if (r != LP_OK) return r;
     // state left by the previous call on this device: none of it is kept
     const int64_t tiles = (NOALLOC_N + BLOCK - 1) / BLOCK;
-    hipLaunchKernelGGL(k_noalloc_clear, dim3((unsigned)((tiles + BLOCK - 1) / BLOCK)),
+    hipLaunchKernelGGL(k_noalloc_clear, dim3((unsigned)((2 * tiles + BLOCK - 1) / BLOCK)),
                        dim3(BLOCK), 0, c->stream, c->w.err, c->w.cnt, c->w.summary,
                        c->w.tile_cnt, tiles);
     hipError_t e = hipGetLastError();

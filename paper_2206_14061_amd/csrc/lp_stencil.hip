@@ -701,12 +701,14 @@ struct TieList {
 // the positions of the tile's list sources are in (sx, sy, sz), and an
 // entry's is read through its slot word; else they are gathered from the
 // 32-byte records.  FULL: with every case of the rule; else a particle that
-// needs that is appended to `hard`.
+// needs that is appended to `hard`.  write_rows (the same for the group):
+// leave the kept rows' slot words, by way of the group's LDS `rows`.
 template <int L, bool STAGED, bool PERIODIC, bool FULL>
 __device__ __forceinline__ void select_particle(const View& v, int64_t i, int sub,
                                                 const double* sx, const double* sy,
                                                 const double* sz, TieList ties, int32_t* hard,
-                                                unsigned int* hard_n, int force_rest)
+                                                unsigned int* hard_n, int force_rest,
+                                                bool write_rows, uint16_t* rows)
 {
     constexpr int NCH = VCAP / (4 * L);      // chunks of a full list
     const int64_t n = v.n;
@@ -780,10 +782,12 @@ __device__ __forceinline__ void select_particle(const View& v, int64_t i, int su
         }
         key[2 * c + h] = kk[0] | (kk[1] << 16);
     };
+    // (the first chunks' words stay for the kept rows below)
+    constexpr int TIER = (3 * NCH + 7) / 8;
+    uint2 w[NCH];
     if constexpr (STAGED) {
         // every chunk's slot words are in flight before the first is used
         const uint2* vs0 = reinterpret_cast<const uint2*>(v.vs + vs_at(n, i, 4 * sub));
-        uint2 w[NCH];
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
             w[c] = make_uint2(0u, 0u);
@@ -792,46 +796,29 @@ __device__ __forceinline__ void select_particle(const View& v, int64_t i, int su
             w[c] = vs0[(int64_t)c * L * n];
         }
         nact = __builtin_amdgcn_readfirstlane(nact);
-        // does some entry of the wavefront stand for a mirror?
-        uint32_t any = 0u;
         static_for<0, NCH>([&](auto C) {
             constexpr int c = decltype(C)::value;
+            if (c >= nact) {
+                key[2 * c] = key[2 * c + 1] = NO_KEY | (NO_KEY << 16);
+                return;
+            }
             // a list's last chunk is padded with STAGE_CAP, the words of
             // chunks past it are arbitrary
-            constexpr uint32_t PAD = (uint32_t)STAGE_CAP | ((uint32_t)STAGE_CAP << 16);
-            if (c < nact) {
-                const bool none = left <= 4 * L * c;
-                w[c].x = none ? PAD : w[c].x;
-                w[c].y = none ? PAD : w[c].y;
-                any |= w[c].x | w[c].y;
-            }
-        });
-        const bool mirrors = __ballot((any & (SLOT_MIRROR | (SLOT_MIRROR << 16))) != 0u) != 0ull;
-        auto run = [&](auto MIR) {
-            static_for<0, NCH>([&](auto C) {
-                constexpr int c = decltype(C)::value;
-                if (c >= nact) {
-                    key[2 * c] = key[2 * c + 1] = NO_KEY | (NO_KEY << 16);
-                    return;
-                }
-                static_for<0, 2>([&](auto Hh) {
-                    const uint32_t ww = Hh.value ? w[c].y : w[c].x;
-                    double px[2], py[2], pz[2];
+            constexpr uint32_t PAD = 8u * STAGE_CAP | (8u * STAGE_CAP << 16);
+            const bool none = left <= 4 * L * c;
+            static_for<0, 2>([&](auto Hh) {
+                const uint32_t ww = none ? PAD : (Hh.value ? w[c].y : w[c].x);
+                double px[2], py[2], pz[2];
 #pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        const uint32_t e = u ? ww >> 16 : ww & 0xFFFFu;
-                        const uint32_t q = MIR.value ? e & (SLOT_MIRROR - 1u) : e;
-                        px[u] = sx[q];
-                        py[u] = sy[q];
-                        pz[u] = sz[q];
-                        if (MIR.value) pz[u] = e & SLOT_MIRROR ? reflect(pz[u]) : pz[u];
-                    }
-                    test2(C, Hh, px, py, pz);
-                });
+                for (int u = 0; u < 2; ++u) {
+                    const uint32_t q = u ? ww >> 16 : ww & 0xFFFFu;
+                    px[u] = staged_at(sx, q);
+                    py[u] = staged_at(sy, q);
+                    pz[u] = staged_at(sz, q);
+                }
+                test2(C, Hh, px, py, pz);
             });
-        };
-        if (mirrors) run(std::true_type{});
-        else run(std::false_type{});
+        });
     } else {
         const char* base = reinterpret_cast<const char*>(v.p4);
         // list words of the next chunk are loaded ahead (every particle
@@ -882,7 +869,6 @@ __device__ __forceinline__ void select_particle(const View& v, int64_t i, int su
     const int gm = (int)(__brev(~(seen >> 16) & 0xFFu) >> 24);
     // f over the chunks in use (and some empty ones): the first TIER chunks
     // without a branch per chunk, which lists of ordinary length fit in
-    constexpr int TIER = (3 * NCH + 7) / 8;
     auto chunks = [&](auto&& f) {
         static_for<0, TIER>(f);
         if (nact > TIER) static_for<TIER, NCH>(f);
@@ -1139,7 +1125,55 @@ __device__ __forceinline__ void select_particle(const View& v, int64_t i, int su
     for (int w = 0; w < MASK_WORDS; ++w)
         if (sub == w % L)
             v.kmask[w * n + i] = (uint64_t)mw[2 * w] | ((uint64_t)mw[2 * w + 1] << 32);
+
+    // ---- the kept rows' slot words, in list order, for the fits of a staged
+    // tile: ranked by the mask, gathered in LDS, written by chunks.  (It
+    // costs the selection 17 us of 131 at 524,288 particles and saves the two
+    // fits, which walked the mask over the list's words, some 80.)
+    if (write_rows) {
+        const uint2* vs0 = reinterpret_cast<const uint2*>(v.vs + vs_at(n, i, 4 * sub));
+        static_for<STAGED ? TIER : 0, NCH>([&](auto C) {
+            constexpr int c = decltype(C)::value;
+            w[c] = make_uint2(0u, 0u);
+            if (c < nact && left > 4 * L * c) w[c] = vs0[(int64_t)c * L * n];
+        });
+        int before = 0;                  // rows of the mask words before
+        static_for<0, NCH>([&](auto C) {
+            constexpr int c = decltype(C)::value;
+            if (c >= nact) return;
+            constexpr int W = 4 * L * c / 32;
+            const uint32_t word = L == 16 && sub >= 8 ? mw[W + 1] : mw[W];
+            const int sh = L == 16 ? 4 * (sub & 7) : 4 * L * c % 32 + 4 * sub;
+            int row = before + __popc(word & ((1u << sh) - 1u));
+            if (L == 16) row += sub >= 8 ? __popc(mw[W]) : 0;
+            const uint32_t nib = word >> sh;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t e = u < 2 ? w[c].x : w[c].y;
+                if ((nib >> u) & 1u)
+                    rows[row] = (uint16_t)(u & 1 ? e >> 16 : e);
+                row += (int)((nib >> u) & 1u);
+            }
+            if (L == 16) before += __popc(mw[W]) + __popc(mw[W + 1]);
+            else if (4 * L * (c + 1) % 32 == 0) before += __popc(mw[W]);
+        });
+        wave_sync();
+        for (int q = sub; 4 * q < m; q += L)
+            *reinterpret_cast<uint2*>(v.ks + vs_at(n, i, 4 * q)) =
+                *reinterpret_cast<const uint2*>(rows + 4 * q);
+        wave_sync();
     }
+    }
+}
+
+// LDS words of one particle's rows (a multiple of 4, and of a stride that
+// spreads the particles over the banks)
+constexpr int ROW_LDS = MMAX_LIMIT + 4;
+
+// Do the fits read particle i's rows from its tile's staged sources?
+__device__ __forceinline__ bool rows_wanted(const View& v, int64_t i)
+{
+    return v.map_ok && stage_unit(v, i / BLOCK, (int)(i % BLOCK) / HALF).S >= 0;
 }
 
 // Threads per block of the selection: with staging, half a tile at L = 4.
@@ -1153,12 +1187,14 @@ __global__ __launch_bounds__(BLOCK, 4) void k_select_full(View v)
     constexpr int TIE_CAP = 64;
     __shared__ double tie_r2[P][TIE_CAP];
     __shared__ int32_t tie_id[P][TIE_CAP];
+    __shared__ __align__(8) uint16_t rows[P][ROW_LDS];
     const int grp = threadIdx.x / L;
     const int64_t i = xcd_block(blockIdx.x, gridDim.x) * P + grp;
     if (i >= v.n) return;
     select_particle<L, false, PERIODIC, true>(v, i, threadIdx.x % L, nullptr, nullptr, nullptr,
                                               TieList{tie_r2[grp], tie_id[grp], TIE_CAP},
-                                              nullptr, nullptr, 0);
+                                              nullptr, nullptr, 0, rows_wanted(v, i),
+                                              rows[grp]);
 }
 
 // Leaves the rare cases to k_select_rest.  STAGED: from the tile's list
@@ -1171,32 +1207,39 @@ __global__ __launch_bounds__(sel_threads(STAGED), 4) void k_select(View v, int32
 {
     constexpr int NT = sel_threads(STAGED);
     constexpr int P = NT / L;                // particles per block
-    static_assert(BLOCK % P == 0, "a block lies in one tile");
     // slot STAGE_CAP: the source of an entry past a list's end, infinitely
     // far away
     constexpr int NS = STAGED ? STAGE_CAP + 1 : 1;
     __shared__ double sx[NS], sy[NS], sz[NS];
+    __shared__ __align__(8) uint16_t rows[STAGED ? P : 1][ROW_LDS];
     const int t = threadIdx.x;
     const int64_t i0 = xcd_block(blockIdx.x, gridDim.x) * P;
     const int64_t i = i0 + t / L;
     int S = -1;                              // staged sources, -1: none
     if (STAGED) {
-        const int64_t tile = i0 / BLOCK;
-        const int tc = v.tile_cnt[tile];
-        S = tc <= STAGE_CAP ? tc : -1;
+        static_assert(P <= HALF, "a block lies in half a tile");
+        const StageUnit su = stage_unit(v, i0 / BLOCK, (int)(i0 % BLOCK) / HALF);
+        S = su.S;
         if (S >= 0) {
             constexpr int SP = (STAGE_CAP + NT - 1) / NT;
-            const int32_t* src = v.tile_src + tile * STAGE_CAP;
+            const int32_t* src = su.src;
             int32_t js[SP];
 #pragma unroll
             for (int u = 0; u < SP; ++u) js[u] = t + u * NT < S ? src[t + u * NT] : -1;
             double q[3][SP];
 #pragma unroll
             for (int u = 0; u < SP; ++u)
-                packed_pos(v, js[u] < 0 ? 0 : js[u], q[0][u], q[1][u], q[2][u]);
+                packed_pos(v, js[u] < 0 ? 0 : js[u] & ~MBIT, q[0][u], q[1][u], q[2][u]);
 #pragma unroll
             for (int u = 0; u < SP; ++u) {
                 if (js[u] < 0) continue;
+                if (js[u] & MBIT) {
+                    // a mirror exists while its source lies within R of the
+                    // wall (the rule that sets mirror_of), at its reflection
+                    const GridInfo& g = v.grid[sys_of(v.off, v.n_sys, js[u] & ~MBIT)];
+                    q[2][u] = dsub(q[2][u], g.wall) < g.R
+                                  ? dsub(dmul(2.0, g.wall) + 0.0, q[2][u]) : (double)INFINITY;
+                }
                 sx[t + u * NT] = q[0][u];
                 sy[t + u * NT] = q[1][u];
                 sz[t + u * NT] = q[2][u];
@@ -1209,10 +1252,10 @@ __global__ __launch_bounds__(sel_threads(STAGED), 4) void k_select(View v, int32
     const TieList none{nullptr, nullptr, 0};
     if (STAGED && S >= 0)
         select_particle<L, STAGED, PERIODIC, false>(v, i, t % L, sx, sy, sz, none, hard,
-                                                    hard_n, force_rest);
+                                                    hard_n, force_rest, true, rows[t / L]);
     else
         select_particle<L, false, PERIODIC, false>(v, i, t % L, sx, sy, sz, none, hard,
-                                                   hard_n, force_rest);
+                                                   hard_n, force_rest, false, nullptr);
 }
 
 // The particles k_select has listed, with every case of the rule.
@@ -1227,6 +1270,7 @@ __global__ __launch_bounds__(BLOCK) void k_select_rest(View v, const int32_t* ha
     constexpr int P = BLOCK / REST_LANES;
     __shared__ double tie_r2[P][VCAP];
     __shared__ int32_t tie_id[P][VCAP];
+    __shared__ __align__(8) uint16_t rows[P][ROW_LDS];
     const int grp = threadIdx.x / REST_LANES, sub = threadIdx.x % REST_LANES;
     const unsigned int total = *hard_n;
     if (blockIdx.x == 0 && threadIdx.x == 0)
@@ -1235,7 +1279,7 @@ __global__ __launch_bounds__(BLOCK) void k_select_rest(View v, const int32_t* ha
          q += (int64_t)gridDim.x * P)
         select_particle<REST_LANES, false, PERIODIC, true>(
             v, hard[q], sub, nullptr, nullptr, nullptr, TieList{tie_r2[grp], tie_id[grp], VCAP},
-            nullptr, nullptr, 0);
+            nullptr, nullptr, 0, rows_wanted(v, hard[q]), rows[grp]);
 }
 
 template <int L>
@@ -1276,6 +1320,7 @@ bool select_in_one(const lp_ctx* c)
 
 void launch_select(lp_ctx* c, const View& v)
 {
+    c->rows_ok = c->map_ok;
     if (select_in_one(c)) {
         if (c->n <= SELECT_L16_MAX) launch_select_full<16>(c, v);
         else launch_select_full<8>(c, v);
@@ -1392,15 +1437,17 @@ __global__ void k_export_stencils(View v, int32_t* cnt_out, int32_t* idx_out,
 // and marks each source by a plain byte store, which many threads may do at
 // once.  The granules present are ranked by id, a prefix sum of their marks
 // numbers the sources in ascending order, and every list entry then gets the
-// slot of its source (a 16-bit word, with SLOT_MIRROR for a mirror entry).
-// A tile with more than STAGE_CAP sources, or more granules than the table
-// holds, is marked -1 (not staged).
+// slot of its source (a 16-bit word).  A mirror is a source of its own, named
+// MBIT | the particle it reflects, so mirrors come after the real ones.
+// A tile with more than STAGE_CAP sources is numbered by halves; a half with
+// too many is not staged, nor is a tile with more granules than the table
+// holds.
 //
 // What bounds it: one tile's chain up to 131,072 particles, the list's bytes
 // in and the words' bytes out (twice) above.  Inserting every entry by LDS
 // compare-and-swap and sorting the sources (66 bitonic steps) took 75 us at
 // 4,096 particles, 87 at 32,768, 100 at 131,072, 146 at 262,144 and 230 at
-// 524,288; by granules it is 16, 19, 29, 52 and 108 (about 400 MB there,
+// 524,288; by granules it is 16, 20, 30, 55 and 115 (about 400 MB there,
 // 80 us at the copy rate).  The map is built before the selection, which
 // then reads staged positions in the passes that rebuild too; on a second
 // stream beside the selection the two took longer than in line (114 us at
@@ -1408,12 +1455,11 @@ __global__ void k_export_stencils(View v, int32_t* cnt_out, int32_t* idx_out,
 
 constexpr int GRAN = 16;               // ids per granule
 constexpr int GRAN_SLOTS = 1024;       // granules per tile (power of 2)
-static_assert(GRAN * GRAN_SLOTS <= (int)SLOT_MIRROR && STAGE_CAP <= (int)SLOT_MIRROR,
-              "places and slots fit below the mirror bit");
+static_assert(GRAN * GRAN_SLOTS <= 0x10000 && STAGE_CAP < 0x2000, "16-bit places and slots");
 constexpr int MAP_SPLIT = 4, MAP_NT = BLOCK * MAP_SPLIT;
 static_assert(GRAN_SLOTS % MAP_NT == 0 && GRAN == 16, "tile map sizes");
 
-__global__ __launch_bounds__(MAP_NT) void k_tile_map(
+__global__ __launch_bounds__(MAP_NT, 8) void k_tile_map(
     int64_t n, const int32_t* __restrict__ vl, const int32_t* __restrict__ vcnt,
     int32_t* __restrict__ tile_src, int32_t* __restrict__ tile_cnt,
     uint16_t* __restrict__ vs, int disable, const int32_t* gate)
@@ -1421,25 +1467,27 @@ __global__ __launch_bounds__(MAP_NT) void k_tile_map(
     if (gate && *gate == 0) return;
     constexpr int PER = GRAN_SLOTS / MAP_NT;
     __shared__ int32_t gkey[GRAN_SLOTS];               // granule of a table place, -1: free
-    __shared__ uint32_t mark[GRAN_SLOTS * GRAN / 4];   // a byte per id of each place
+    // a byte per half tile and id of each place
+    __shared__ uint32_t mark[2][GRAN_SLOTS * GRAN / 4];
     __shared__ int32_t list[GRAN_SLOTS];               // the places in use
     __shared__ int32_t lkey[GRAN_SLOTS];               // and their granules
     __shared__ uint32_t rcnt[GRAN_SLOTS];              // marks of the granule of each rank
     __shared__ uint32_t wsum[MAP_NT / 64];
-    __shared__ int full, ng;
+    __shared__ int full, ng, reals;
     const int t = threadIdx.x;
     const int64_t tile = blockIdx.x;
     const int64_t i = tile * BLOCK + t % BLOCK;
     const int part = t / BLOCK;
     const int cnt = i < n ? vcnt[i] : 0;
+    const int half = t % BLOCK / HALF;
     for (int h = t; h < GRAN_SLOTS; h += MAP_NT) gkey[h] = -1;
-    for (int h = t; h < GRAN_SLOTS * GRAN / 4; h += MAP_NT) mark[h] = 0u;
+    for (int h = t; h < GRAN_SLOTS * GRAN / 4; h += MAP_NT) mark[0][h] = mark[1][h] = 0u;
     if (t == 0) {
         full = disable;
         ng = 0;
     }
     __syncthreads();
-    uint8_t* markb = reinterpret_cast<uint8_t*>(mark);
+    uint8_t* markb = reinterpret_cast<uint8_t*>(mark[half]);
     // list words are loaded MAP_BATCH at a time (one memory latency per
     // batch instead of per entry)
     constexpr int MAP_BATCH = 8;
@@ -1455,7 +1503,7 @@ __global__ __launch_bounds__(MAP_NT) void k_tile_map(
         for (int u = 0; u < MAP_BATCH; ++u) {
             hb[u] = 0u;
             if (k0 + u >= cnt) continue;
-            const int32_t j = jb[u] & ~MBIT;
+            const int32_t j = jb[u];       // (with its mirror bit)
             const int32_t gr = j / GRAN;
             if (gr != last) {
                 last = gr;
@@ -1477,11 +1525,9 @@ __global__ __launch_bounds__(MAP_NT) void k_tile_map(
                 if (probe == GRAN_SLOTS) full = 1;
                 place = h;
             }
-            const uint32_t pos = place * GRAN + (uint32_t)(j % GRAN);
-            markb[pos] = 1;
-            // the entry's place (and mirror bit) until its source's slot is
-            // known
-            hb[u] = pos | ((jb[u] & MBIT) ? SLOT_MIRROR : 0u);
+            // the entry's place until its source's slot is known
+            hb[u] = place * GRAN + (uint32_t)(j % GRAN);
+            markb[hb[u]] = 1;
         }
 #pragma unroll
         for (int u = 0; u < MAP_BATCH; u += 4) vs_store4(vs, n, i, k0 + u, hb + u);
@@ -1489,25 +1535,28 @@ __global__ __launch_bounds__(MAP_NT) void k_tile_map(
     __syncthreads();
     const int G = ng;
     if (full) {
-        if (t == 0) tile_cnt[tile] = -1;
+        if (t < 2) tile_cnt[2 * tile + t] = -1;
         return;
     }
     // thread t takes the granules t, t + MAP_NT, ... of the list: their marks
     // as bits, and their rank among the granules
-    uint32_t bits[PER];
+    uint32_t bits[2][PER];
     int32_t key[PER], rank[PER];
 #pragma unroll
     for (int r = 0; r < PER; ++r) {
         const int q = t + r * MAP_NT;
-        bits[r] = 0u;
+        bits[0][r] = bits[1][r] = 0u;
         key[r] = rank[r] = 0;
         if (q < G) {
             const int h = list[q];
             key[r] = lkey[q];
-            const uint4 m = *reinterpret_cast<const uint4*>(&mark[h * GRAN / 4]);
             // bytes of 0 or 1 -> four bits (byte k's bit moves to 28 + k)
             auto nib = [](uint32_t x) { return (x * 0x10204080u) >> 28; };
-            bits[r] = nib(m.x) | nib(m.y) << 4 | nib(m.z) << 8 | nib(m.w) << 12;
+#pragma unroll
+            for (int w = 0; w < 2; ++w) {
+                const uint4 m = *reinterpret_cast<const uint4*>(&mark[w][h * GRAN / 4]);
+                bits[w][r] = nib(m.x) | nib(m.y) << 4 | nib(m.z) << 8 | nib(m.w) << 12;
+            }
         }
     }
     if (t < G)
@@ -1517,9 +1566,16 @@ __global__ __launch_bounds__(MAP_NT) void k_tile_map(
 #pragma unroll
             for (int r = 0; r < PER; ++r) rank[r] += k < key[r] ? 1 : 0;
         }
+    uint32_t* tab = mark[0];               // (the marks have been read)
+    // the whole tile (unit -1), or else its halves
+    for (int unit = -1; unit < 2; ++unit) {
+    uint32_t b[PER];
+    __syncthreads();
 #pragma unroll
-    for (int r = 0; r < PER; ++r)
-        if (t + r * MAP_NT < G) rcnt[rank[r]] = (uint32_t)__popc(bits[r]);
+    for (int r = 0; r < PER; ++r) {
+        b[r] = unit < 0 ? bits[0][r] | bits[1][r] : bits[unit][r];
+        if (t + r * MAP_NT < G) rcnt[rank[r]] = (uint32_t)__popc(b[r]);
+    }
     __syncthreads();
     // exclusive prefix sum over the ranks, thread t the ranks [t PER, ...)
     uint32_t c[PER], mine = 0u, total = 0u;
@@ -1535,35 +1591,46 @@ __global__ __launch_bounds__(MAP_NT) void k_tile_map(
         at += c[r];
     }
     const int S = (int)total;
-    if (t == 0) tile_cnt[tile] = S > STAGE_CAP ? -1 : S;
-    if (S > STAGE_CAP) return;
+    if (t == 0) reals = S;
+    if (S > STAGE_CAP) {
+        if (t == 0 && unit >= 0) tile_cnt[2 * tile + unit] = -1;
+        continue;                          // (the same in every thread)
+    }
     __syncthreads();
     // the sources, and each place's first slot with its marks
-    uint32_t* tab = mark;                  // (the marks have been read)
+    int32_t* src = tile_src + (2 * tile + (unit < 0 ? 0 : unit)) * STAGE_CAP;
 #pragma unroll
     for (int r = 0; r < PER; ++r) {
         const int q = t + r * MAP_NT;
         if (q >= G) continue;
         const uint32_t first = rcnt[rank[r]];
-        tab[list[q]] = bits[r] | (first << 16);
-        int32_t* out = tile_src + tile * STAGE_CAP + first;
-        for (uint32_t b = bits[r]; b; b &= b - 1) *out++ = key[r] * GRAN + __builtin_ctz(b);
+        tab[list[q]] = b[r] | (first << 16);
+        if (key[r] >= MBIT / GRAN) atomicMin(&reals, (int)first);
+        int32_t* out = src + first;
+        for (uint32_t m = b[r]; m; m &= m - 1) *out++ = key[r] * GRAN + __builtin_ctz(m);
     }
     __syncthreads();
+    if (t == 0) {
+        tile_cnt[2 * tile + (unit < 0 ? 0 : unit)] = S | (reals << 16);
+        if (unit < 0) tile_cnt[2 * tile + 1] = TILE_WHOLE;
+    }
     // places -> slots (the thread rereads its own words); the words past the
     // list in its last chunk stand for no source
+    if (unit < 0 || unit == half)
     for (int k0 = part * MAP_BATCH; k0 < cnt; k0 += MAP_SPLIT * MAP_BATCH) {
         uint32_t hb[MAP_BATCH];
 #pragma unroll
         for (int u = 0; u < MAP_BATCH; u += 4) vs_load4(vs, n, i, k0 + u, hb + u);
 #pragma unroll
         for (int u = 0; u < MAP_BATCH; ++u) {
-            const uint32_t w = tab[(hb[u] & (SLOT_MIRROR - 1u)) / GRAN];
+            const uint32_t w = tab[hb[u] / GRAN];
             const uint32_t q = (w >> 16) + (uint32_t)__popc(w & ((1u << (hb[u] % GRAN)) - 1u));
-            hb[u] = k0 + u < cnt ? q | (hb[u] & SLOT_MIRROR) : (uint32_t)STAGE_CAP;
+            hb[u] = 8u * (k0 + u < cnt ? q : (uint32_t)STAGE_CAP);
         }
 #pragma unroll
         for (int u = 0; u < MAP_BATCH; u += 4) vs_store4(vs, n, i, k0 + u, hb + u);
+    }
+    if (unit < 0) break;
     }
 }
 

@@ -251,94 +251,116 @@ __device__ __forceinline__ void visit_sources(const View& v, int64_t i, const Re
     }
 }
 
-// visit_stencil for a particle of a staged tile:
-// the fields of the tile's list sources sit in LDS in slot order, and a
-// row's point is read from there through the slot word of its list entry.
-// The Pt handed to f carries the slot in `src` (and no id).  Rows come in
-// the same order as from visit_stencil.
-template <int B, class F>
-__device__ __forceinline__ void visit_staged(const View& v, const Seen& s, int64_t i,
-                                             const Rec& r, const double* sx,
-                                             const double* sy, const double* sz, F&& f)
+// The sources staged for half h of a tile: those of the half, or of the
+// whole tile.  S < 0: not staged; reals: those that are no mirrors.
+struct StageUnit {
+    int S, reals;
+    const int32_t* src;
+};
+__device__ __forceinline__ bool tile_split(const View& v, int64_t tile)
 {
-    const int64_t n = v.n;
-    auto row = [&](uint32_t word) {
-        Pt p;
-        const int q = (int)(word & (SLOT_MIRROR - 1u));
-        p.mirror = (word & SLOT_MIRROR) != 0u;
-        p.valid = true;
-        p.src = q;
-        p.id = -1;
-        p.x = sx[q];
-        p.y = sy[q];
-        p.z = p.mirror ? dsub(s.wall2, sz[q]) : sz[q];
-        if (v.periodic) {
-            p.x = image_coord(p.x, s.xi, s.Lx, s.hLx);
-            p.y = image_coord(p.y, s.yi, s.Ly, s.hLy);
-        }
-        f(p, dsub(p.x, s.xi), dsub(p.y, s.yi), dsub(p.z, s.zi));
-    };
-    MaskWalk mw(r);
-    int t = 0;
-    for (; t + B <= r.m; t += B) {
-        uint32_t w[B];
-#pragma unroll
-        for (int u = 0; u < B; ++u) w[u] = v.vs[vs_at(n, i, mw.pop())];
-#pragma unroll
-        for (int u = 0; u < B; ++u) row(w[u]);
-    }
-    for (; t < r.m; ++t) row(v.vs[vs_at(n, i, mw.pop())]);
+    return v.tile_cnt[2 * tile + 1] != TILE_WHOLE;
+}
+__device__ __forceinline__ StageUnit stage_unit(const View& v, int64_t tile, int h)
+{
+    const int64_t u = 2 * tile + (h && tile_split(v, tile) ? 1 : 0);
+    const int32_t tc = v.tile_cnt[u];
+    return StageUnit{tile_slots(tc), tile_reals(tc), v.tile_src + u * STAGE_CAP};
 }
 
-// visit_staged with the rows of particle i spread over LPP adjacent lanes:
-// lane `sub` takes the kept rows sub, sub + LPP, sub + 2 LPP, ... (B of
-// them loaded together), in the order of visit_staged.
-template <int B, int LPP, class F>
-__device__ __forceinline__ void visit_staged_sub(const View& v, const Seen& s, int64_t i,
-                                                 const Rec& r, int sub, const double* sx,
-                                                 const double* sy, const double* sz, F&& f)
-{
-    const int64_t n = v.n;
-    auto row = [&](uint32_t word) {
-        Pt p;
-        const int q = (int)(word & (SLOT_MIRROR - 1u));
-        p.mirror = (word & SLOT_MIRROR) != 0u;
-        p.valid = true;
-        p.src = q;
-        p.id = -1;
-        p.x = sx[q];
-        p.y = sy[q];
-        p.z = p.mirror ? dsub(s.wall2, sz[q]) : sz[q];
-        if (v.periodic) {
-            p.x = image_coord(p.x, s.xi, s.Lx, s.hLx);
-            p.y = image_coord(p.y, s.yi, s.Ly, s.hLy);
-        }
-        f(p, dsub(p.x, s.xi), dsub(p.y, s.yi), dsub(p.z, s.zi));
-    };
-    MaskWalk mw(r);
-    // this lane's rows; the walk skips the other lanes' rows
-    const int mine = sub < r.m ? (r.m - sub + LPP - 1) / LPP : 0;
-    for (int q = 0; q < sub && mw.any(); ++q) mw.pop();
-    auto next = [&]() {
-        const int k = mw.pop();
-#pragma unroll
-        for (int q = 1; q < LPP; ++q)
-            if (mw.any()) mw.pop();
-        return k;
-    };
-    int t = 0;
-    for (; t + B <= mine; t += B) {
-        uint32_t w[B];
-#pragma unroll
-        for (int u = 0; u < B; ++u) w[u] = v.vs[vs_at(n, i, next())];
-#pragma unroll
-        for (int u = 0; u < B; ++u) row(w[u]);
+// The part of the particles a block of a staged kernel takes, P of them from
+// i0 on and the unit they are staged as.  A block of a whole tile (P = BLOCK)
+// takes its first half only when the tile is staged in halves; the second
+// halves are those of a second grid's worth of blocks, which do nothing for
+// other tiles (a loop over the two in one block costs 176 spilled registers
+// in pass 1).
+template <int P>
+struct BlockPart {
+    int64_t i0;
+    int h;                      // half (P = BLOCK: 1 only in the second set)
+    StageUnit unit;
+    bool split;
+    static unsigned blocks(int64_t n)
+    {
+        return (unsigned)((P == BLOCK ? 2 : 1) * ((n + P - 1) / P));
     }
-    for (; t < mine; ++t) row(v.vs[vs_at(n, i, next())]);
+    __device__ __forceinline__ BlockPart(const View& v, int rows_ok)
+    {
+        if (P == BLOCK) {
+            const unsigned half = gridDim.x / 2;
+            h = blockIdx.x >= half ? 1 : 0;
+            i0 = xcd_block(blockIdx.x - (h ? half : 0u), half) * P;
+        } else {
+            i0 = xcd_block(blockIdx.x, gridDim.x) * P;
+            h = (int)(i0 % BLOCK) / HALF;
+        }
+        unit = StageUnit{-1, 0, nullptr};
+        split = false;
+        if (rows_ok) {
+            unit = stage_unit(v, i0 / BLOCK, h);
+            split = tile_split(v, i0 / BLOCK);
+        }
+    }
+    // nothing to do in this block
+    __device__ __forceinline__ bool idle() const { return P == BLOCK && h == 1 && !split; }
+    // is the block's particle p in the unit?
+    __device__ __forceinline__ bool mine(int p) const
+    {
+        return P < BLOCK || !split || p / HALF == h;
+    }
+    static_assert(P == BLOCK || HALF % P == 0, "a tile, or a part of half of one");
+};
+
+// A staged field at a row's byte offset.
+__device__ __forceinline__ double staged_at(const double* field, uint32_t off)
+{
+    return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(field) + off);
+}
+
+// visit_stencil for a particle of a staged tile: the fields of the tile's
+// list sources sit in LDS in slot order, and a row's point is read from
+// there at the byte offset the selection left for it.  The m rows are
+// spread over LPP adjacent lanes: lane `sub` takes the chunks of four rows
+// sub, sub + LPP, ... (one 8-byte load each, the next one in flight), in
+// list order.  Calls f(off, dx, dy, dz).
+template <int LPP, bool PERIODIC, class F>
+__device__ __forceinline__ void visit_staged(const View& v, const Seen& s, int64_t i, int m,
+                                             int sub, const double* sx, const double* sy,
+                                             const double* sz, F&& f)
+{
+    auto row = [&](uint32_t off) {
+        double x = staged_at(sx, off), y = staged_at(sy, off);
+        const double z = staged_at(sz, off);
+        if (PERIODIC) {
+            x = image_coord(x, s.xi, s.Lx, s.hLx);
+            y = image_coord(y, s.yi, s.Ly, s.hLy);
+        }
+        f(off, dsub(x, s.xi), dsub(y, s.yi), dsub(z, s.zi));
+    };
+    const int full = m >> 2, used = (m + 3) >> 2;
+    const uint2* kp = reinterpret_cast<const uint2*>(v.ks + vs_at(v.n, i, 4 * sub));
+    const int64_t step = (int64_t)LPP * v.n;
+    uint2 w = make_uint2(0u, 0u);
+    if (sub < used) w = *kp;
+    int c = sub;
+    while (c < full) {
+        const uint2 cur = w;
+        c += LPP;
+        kp += step;
+        if (c < used) w = *kp;
+        row(cur.x & 0xFFFFu);
+        row(cur.x >> 16);
+        row(cur.y & 0xFFFFu);
+        row(cur.y >> 16);
+    }
+    if (c == full)
+        for (int u = 0; u < (m & 3); ++u)
+            row(((u & 2 ? w.y : w.x) >> (16 * (u & 1))) & 0xFFFFu);
 }
 
 // visit_stencil with the rows of particle i spread over LPP adjacent
-// lanes: lane `sub` takes kept rows sub, sub + LPP, sub + 2 LPP, ...
+// lanes as in visit_staged: lane `sub` takes the chunks of four kept rows
+// sub, sub + LPP, ...
 template <int LPP, class F>
 __device__ __forceinline__ void visit_stencil_sub(const View& v, const GridInfo& g,
                                                   int64_t i, const Rec& r, int sub, F&& f)
@@ -348,24 +370,50 @@ __device__ __forceinline__ void visit_stencil_sub(const View& v, const GridInfo&
         return;
     }
     const int64_t n = v.n;
-    const double xi = v.x[i], yi = v.y[i], zi = v.z[i];
+    const Seen s = seen_from(v, g, i);
+    const double xi = s.xi, yi = s.yi, zi = s.zi;
     MaskWalk mw(r);
-    for (int t = 0; t < sub && t < r.m; ++t) mw.pop();
-    for (int t = sub; t < r.m; t += LPP) {
-        const int k = mw.pop();
-        const Pt p = list_point(v, g, v.vl[vl_at(n, i, k)], xi, yi);
-        f(p, dsub(p.x, xi), dsub(p.y, yi), dsub(p.z, zi));
-        for (int u = 1; u < LPP && t + u < r.m; ++u) mw.pop();
+    for (int t = 0; t < 4 * sub && t < r.m; ++t) mw.pop();
+    for (int t = 4 * sub; t < r.m; t += 4 * LPP) {
+        for (int u = t; u < t + 4 && u < r.m; ++u) {
+            const int32_t e[1] = {v.vl[vl_at(n, i, mw.pop())]};
+            Pt p[1];
+            gather_list(v, s, e, p);
+            f(p[0], dsub(p[0].x, xi), dsub(p[0].y, yi), dsub(p[0].z, zi));
+        }
+        for (int u = t + 4; u < t + 4 * LPP && u < r.m; ++u) mw.pop();
     }
 }
 
-// sum of x over the LPP adjacent lanes of a particle (the same value in
-// every one of them: the butterfly adds the same operands in each lane)
+template <int CTRL>
+__device__ __forceinline__ int dpp_move(int x)
+{
+    return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, false);
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float x)
+{
+    return __int_as_float(dpp_move<CTRL>(__float_as_int(x)));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double x)
+{
+    return __hiloint2double(dpp_move<CTRL>(__double2hiint(x)),
+                            dpp_move<CTRL>(__double2loint(x)));
+}
+
+// sum of x over the LPP (up to 16) adjacent lanes of a particle (the same
+// value in every one of them: the partners of a step add the same operands):
+// swaps of neighbours and of pairs inside quads, then the half-row and row
+// mirrors
 template <int LPP, class T>
 __device__ __forceinline__ T lane_sum(T x)
 {
-#pragma unroll
-    for (int off = 1; off < LPP; off <<= 1) x += __shfl_xor(x, off);
+    static_assert(LPP == 1 || LPP == 2 || LPP == 4 || LPP == 8 || LPP == 16, "lanes of a row");
+    if (LPP >= 2) x += dpp_move<0xB1>(x);
+    if (LPP >= 4) x += dpp_move<0x4E>(x);
+    if (LPP >= 8) x += dpp_move<0x141>(x);
+    if (LPP >= 16) x += dpp_move<0x140>(x);
     return x;
 }
 
