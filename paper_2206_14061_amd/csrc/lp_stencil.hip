@@ -181,9 +181,20 @@ __global__ __launch_bounds__(BLOCK) void k_list_build(
 // For each particle the accepted lanes append their ids in lane order (a
 // ballot prefix count), so the lists are identical to the per-particle
 // scan's (same entries, same order, same test on the same values).  A
-// particle's potential mirror sources (the cells of its reflection, which
-// differ between the particles of a cell) follow its real entries, one
-// particle at a time, through the same sequence around the reflection.
+// particle's potential mirror sources follow its real entries, through the
+// same sequence around its reflection; the particles whose reflections fall
+// in one cell take it together.  Where the cells are few, several wavefronts
+// share a cell's particles.
+//
+// What bounds it: the chain of a cell at the wall up to 65,536 particles,
+// above the instructions per particle and 64 candidates (24 vector ones; 14 %
+// of the candidates are accepted, the cells' share of the sphere).  With the
+// reflections scanned one particle at a time and one wavefront per cell that
+// chain took 100 us at 4,096 to 131,072 particles, and the build 154 at
+// 262,144 and 250 at 524,288; now 17 at 4,096, 39 at 32,768, 87 at 131,072,
+// 149 and 244.  Entries gathered in LDS and written by chunks (280 us at
+// 524,288: the LDS costs wavefronts) and four particles tested together
+// (282) were slower.
 // The cell's particles are taken 64 at a time; their positions sit in LDS
 // (read with one address by the whole wavefront) and their running counts
 // in lane q of `cntv`.
@@ -264,7 +275,7 @@ __global__ __launch_bounds__(BLOCK) void k_list_cells(
     int64_t n, int n_sys, const GridInfo* __restrict__ grid,
     const double* __restrict__ p4, const int32_t* __restrict__ cs,
     const int32_t* __restrict__ ce, int64_t n_cells, const int64_t* __restrict__ n_cells_dev,
-    int32_t* __restrict__ vl, int32_t* __restrict__ vcnt, ErrWord* err,
+    int split, int32_t* __restrict__ vl, int32_t* __restrict__ vcnt, ErrWord* err,
     const int32_t* gate)
 {
     if (gate && *gate == 0) return;
@@ -275,7 +286,8 @@ __global__ __launch_bounds__(BLOCK) void k_list_cells(
     int32_t* sb = seqb[wv];
     int32_t* so = seqo[wv];
     const int64_t tc = n_cells_dev ? *n_cells_dev : n_cells;
-    const int64_t groups = (tc + LC_WAVES - 1) / LC_WAVES;
+    const int64_t units = tc * split;
+    const int64_t groups = (units + LC_WAVES - 1) / LC_WAVES;
     const char* p4b = reinterpret_cast<const char*>(p4);
     const uint32_t cst = (uint32_t)(n * VCHUNK);
     auto load_pos = [&](int32_t j, double& qx, double& qy, double& qz) {
@@ -286,15 +298,21 @@ __global__ __launch_bounds__(BLOCK) void k_list_cells(
         qz = r[2];
     };
     for (int64_t grp = xcd_block(blockIdx.x, gridDim.x); grp < groups; grp += gridDim.x) {
-        const int64_t cell = grp * LC_WAVES + wv;
-        if (cell >= tc) break;
-        const int32_t cb = cs[cell], cend = ce[cell];
+        const int64_t unit = grp * LC_WAVES + wv;
+        if (unit >= units) break;
+        // this wavefront's share of a cell's particles
+        const int64_t cell = unit / split;
+        const int part = (int)(unit - cell * split);
+        const int32_t first = cs[cell], all = ce[cell] - first;
+        const int share = (all + split - 1) / split;
+        const int32_t cb = first + part * share;
+        const int32_t cend = first + ((part + 1) * share < all ? (part + 1) * share : all);
         if (cend <= cb) continue;
         const GridInfo& g = grid[sys_of_cell(grid, n_sys, cell)];
         const int loc = (int)(cell - g.cell_base);
         const int cx = loc % g.nx, cy = (loc / g.nx) % g.ny, cz = loc / (g.nx * g.ny);
         const double Rv2 = g.Rv2 * (1.0 + 1e-12);
-        const int tot = cell_seq(g, cs, ce, cx, cy, cz, sb, so);
+        int tot = cell_seq(g, cs, ce, cx, cy, cz, sb, so);
         for (int32_t q0 = cb; q0 < cend; q0 += 64) {
             const int nq = cend - q0 < 64 ? cend - q0 : 64;
             const int32_t mi = q0 + lane;          // this lane's particle
@@ -332,40 +350,55 @@ __global__ __launch_bounds__(BLOCK) void k_list_cells(
                     }
                 }
             }
-            // potential mirrors of each particle near the wall: reals near
-            // the wall that lie near its reflection
-            bool reseq = false;
-            for (int q = 0; q < nq; ++q) {
-                const double4 pq = ppos[wv][q];
-                if (!(pq.z - g.wall < g.Rv)) continue;
-                const int32_t iq = q0 + q;
-                const double zm = dsub(dmul(2.0, g.wall), pq.z);
+            // potential mirrors of the particles near the wall: reals near the
+            // wall that lie near their reflections.  The cell's particles
+            // whose reflections fall in one cell (all of them, where the
+            // reflections are clamped to the grid's lowest layer) scan its
+            // surroundings together, as above.
+            const double zq = lane < nq ? ppos[wv][lane].z : 0.0;
+            int mcell = -1;
+            if (lane < nq && zq - g.wall < g.Rv) {
                 int mx, my, mz;
-                cell_clamp(g, pq.x, pq.y, zm, mx, my, mz);
+                cell_clamp(g, ppos[wv][lane].x, ppos[wv][lane].y,
+                           dsub(dmul(2.0, g.wall), zq), mx, my, mz);
+                mcell = mx + g.nx * (my + g.ny * mz);
+            }
+            uint64_t todo = __ballot(mcell >= 0);
+            const bool reseq = todo != 0ull;
+            while (todo) {
+                const int mc = __builtin_amdgcn_readlane(mcell, __builtin_ctzll(todo));
+                const uint64_t same = __ballot(mcell == mc);
+                todo &= ~same;
                 wave_sync();
-                const int mtot = cell_seq(g, cs, ce, mx, my, mz, sb, so);
-                reseq = true;
-                int c = __builtin_amdgcn_readlane(cntv, q);
+                const int mtot = cell_seq(g, cs, ce, mc % g.nx, (mc / g.nx) % g.ny,
+                                          mc / (g.nx * g.ny), sb, so);
                 for (int t0 = 0; t0 < mtot; t0 += 64) {
                     const int32_t j = seq_at(sb, so, t0 + lane, mtot, cb);
                     double qx, qy, qz;
                     load_pos(j, qx, qy, qz);
-                    const double dx =
-                        (PERIODIC ? image_coord(qx, pq.x, g.Lx, g.hLx) : qx) - pq.x;
-                    const double dy =
-                        (PERIODIC ? image_coord(qy, pq.y, g.Ly, g.hLy) : qy) - pq.y;
-                    const double dz = qz - zm;
-                    const bool acc = t0 + lane < mtot &&
-                                     !(fma(dz, dz, fma(dy, dy, dx * dx)) >= Rv2) &&
-                                     qz - g.wall < g.Rv;
-                    const uint64_t m = __ballot(acc);
-                    const uint32_t pos = (uint32_t)c + __builtin_amdgcn_mbcnt_hi(
-                                             (uint32_t)(m >> 32),
-                                             __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                    if (acc && pos < (uint32_t)VCAP) vl_put(vl, iq, cst, pos, j | MBIT);
-                    c += __popcll(m);
+                    const bool in = t0 + lane < mtot && qz - g.wall < g.Rv;
+                    for (uint64_t rest = same; rest; rest &= rest - 1) {
+                        const int q = __builtin_ctzll(rest);
+                        const double4 pq = ppos[wv][q];
+                        const int32_t iq = q0 + q;
+                        const double dx =
+                            (PERIODIC ? image_coord(qx, pq.x, g.Lx, g.hLx) : qx) - pq.x;
+                        const double dy =
+                            (PERIODIC ? image_coord(qy, pq.y, g.Ly, g.hLy) : qy) - pq.y;
+                        const double dz = qz - dsub(dmul(2.0, g.wall), pq.z);
+                        const bool acc = in && !(fma(dz, dz, fma(dy, dy, dx * dx)) >= Rv2);
+                        const uint64_t m = __ballot(acc);
+                        if (m) {
+                            const int c0 = __builtin_amdgcn_readlane(cntv, q);
+                            const uint32_t pos = (uint32_t)c0 + __builtin_amdgcn_mbcnt_hi(
+                                                     (uint32_t)(m >> 32),
+                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                            if (acc && pos < (uint32_t)VCAP)
+                                vl_put(vl, iq, cst, pos, j | MBIT);
+                            cntv = lane == q ? c0 + __popcll(m) : cntv;
+                        }
+                    }
                 }
-                cntv = lane == q ? c : cntv;
             }
             if (lane < nq) {
                 if (cntv > VCAP) {
@@ -377,7 +410,7 @@ __global__ __launch_bounds__(BLOCK) void k_list_cells(
             // the next chunk's positions (and the cell's own sequence, if
             // a mirror scan replaced it) overwrite the LDS words
             wave_sync();
-            if (reseq && q0 + 64 < cend) cell_seq(g, cs, ce, cx, cy, cz, sb, so);
+            if (reseq && q0 + 64 < cend) tot = cell_seq(g, cs, ce, cx, cy, cz, sb, so);
         }
         wave_sync();
     }
@@ -1672,17 +1705,22 @@ lp_status list_build(lp_ctx* c, const int32_t* gate)
         // with a grid sized by the particle count
         const int64_t tc = gate ? w.cells_max : c->total_cells;
         const int64_t* tdev = gate ? &w.summary->total_cells : nullptr;
-        const int64_t groups = (tc + LC_WAVES - 1) / LC_WAVES;
-        const int64_t cap = gate ? 2 * (int64_t)blocks_for(n) : (int64_t)LC_MAX_BLOCKS;
+        // Wavefronts per cell, until the cells alone fill the chip.  Measured
+        // with 1, 2, 4 and 8, us: 4,096 particles 52, 32, 22, 17; 12,075 53,
+        // 33, 23, 22; 32,768 54, 41, 39, 43; 65,536 63, 58, 59, 66; 131,072
+        // 95, 87, 97, 112; 262,144 150, 149, 167, 279.
+        const int split = n <= 16384 ? 8 : n <= 65536 ? 4 : n <= 262144 ? 2 : 1;
+        const int64_t groups = (tc * split + LC_WAVES - 1) / LC_WAVES;
+        const int64_t cap = gate ? 2 * split * (int64_t)blocks_for(n) : (int64_t)LC_MAX_BLOCKS;
         const unsigned nb = (unsigned)std::max<int64_t>(1, std::min(groups, cap));
         if (c->periodic)
             hipLaunchKernelGGL(k_list_cells<true>, dim3(nb), dim3(BLOCK), 0, c->stream, n,
-                               c->n_sys, w.grid, w.p4, w.cs, w.ce, tc, tdev, w.vl, w.vcnt,
-                               w.err, gate);
+                               c->n_sys, w.grid, w.p4, w.cs, w.ce, tc, tdev, split, w.vl,
+                               w.vcnt, w.err, gate);
         else
             hipLaunchKernelGGL(k_list_cells<false>, dim3(nb), dim3(BLOCK), 0, c->stream, n,
-                               c->n_sys, w.grid, w.p4, w.cs, w.ce, tc, tdev, w.vl, w.vcnt,
-                               w.err, gate);
+                               c->n_sys, w.grid, w.p4, w.cs, w.ce, tc, tdev, split, w.vl,
+                               w.vcnt, w.err, gate);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(c, e, "list build launch");
