@@ -489,11 +489,21 @@ __global__ void k_copy_i32(int64_t n, const int32_t* a, int32_t* b, const int32_
     if (i < n) b[i] = a[i];
 }
 
-__global__ void k_copy_f64(int64_t n, const double* a, double* b, const int32_t* gate)
+// the seven arrays of a state
+struct Copy7 {
+    const double* from[7];
+    double* to[7];
+};
+__global__ void k_copy7(int64_t n, Copy7 c, const int32_t* gate)
 {
     LP_GATE(gate);
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) b[i] = a[i];
+    if (i >= n) return;
+    double v[7];
+#pragma unroll
+    for (int a = 0; a < 7; ++a) v[a] = c.from[a][i];
+#pragma unroll
+    for (int a = 0; a < 7; ++a) c.to[a][i] = v[a];
 }
 
 // a[0..count) = b[0..count) = v, with count = *count_dev when given
@@ -829,9 +839,15 @@ lp_status state_copy(lp_ctx* c, double* const st[7], int32_t* perm_out,
     Work& w = c->w;
     const int64_t n = c->n;
     if (n > 0) {
-        for (int a = 0; a < 7 && arrays; ++a)
-            hipLaunchKernelGGL(k_copy_f64, dim3(blocks_for(n)), dim3(BLOCK), 0,
-                               c->stream, n, st[a], w.sst[a], gate);
+        if (arrays) {
+            Copy7 cp;
+            for (int a = 0; a < 7; ++a) {
+                cp.from[a] = st[a];
+                cp.to[a] = w.sst[a];
+            }
+            hipLaunchKernelGGL(k_copy7, dim3(blocks_for(n)), dim3(BLOCK), 0, c->stream, n, cp,
+                               gate);
+        }
         if (perm_out)
             hipLaunchKernelGGL(k_iota, dim3(blocks_for(n)), dim3(BLOCK), 0,
                                c->stream, n, perm_out, gate);
@@ -919,10 +935,15 @@ lp_status state_write_back(lp_ctx* c, double* const out[7])
 {
     Work& w = c->w;
     const int64_t n = c->n;
-    if (n > 0)
-        for (int a = 0; a < 7; ++a)
-            hipLaunchKernelGGL(k_copy_f64, dim3(blocks_for(n)), dim3(BLOCK), 0,
-                               c->stream, n, w.sst[a], out[a], nullptr);
+    if (n > 0) {
+        Copy7 cp;
+        for (int a = 0; a < 7; ++a) {
+            cp.from[a] = w.sst[a];
+            cp.to[a] = out[a];
+        }
+        hipLaunchKernelGGL(k_copy7, dim3(blocks_for(n)), dim3(BLOCK), 0, c->stream, n, cp,
+                           (const int32_t*)nullptr);
+    }
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? LP_OK : hip_fail(c, e, "state write-back");
 }
