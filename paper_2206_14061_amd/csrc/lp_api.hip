@@ -96,7 +96,7 @@ void free_work(Work& w)
     f(w.acc2); f(w.dVdt2); f(w.acc); f(w.dVdt); f(w.flags); f(w.coff);
     f(w.cls_idx); f(w.cls_cnt);
     if (w.h_summary) hipHostFree(w.h_summary);
-    w.h_summary = nullptr;
+    w.h_summary = w.pinned = nullptr;
     w.n_max = w.cells_max = 0;
 }
 
@@ -304,6 +304,7 @@ lp_status lp_reserve(lp_ctx* c, int64_t n_max, int64_t cells_max)
         if (e == hipSuccess) e = alloc(p, cnt);
     });
     if (e == hipSuccess) e = hipHostMalloc((void**)&w.h_summary, sizeof(Summary));
+    w.pinned = w.h_summary;
     if (e == hipSuccess) e = hipMemset(w.err, 0, sizeof(ErrWord));
     if (e == hipSuccess) e = hipMemset(w.cnt, 0, sizeof(Counters));
     if (e == hipSuccess) e = hipMemset(w.summary, 0, sizeof(Summary));

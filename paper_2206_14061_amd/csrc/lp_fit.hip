@@ -436,6 +436,25 @@ __global__ __launch_bounds__(BLOCK, 2) void k_pass1(View v, StepOut o,
     pass1_solve<LPP>(v, o, g, s, i, M, B, order_rows(v, r, mt), sub, redo, redo_n, force_qr);
 }
 
+// The pass-1 refit of particle i by a wavefront.
+__device__ __forceinline__ void pass1_refit(const View& v, const StepOut& o, int64_t i)
+{
+    const int s = sys_of(v.off, v.n_sys, i);
+    const GridInfo& g = v.grid[s];
+    const Rec r = load_rec(v, i);
+    const double own[3] = {v.u[i], v.v[i], v.w[i]};
+    auto vals = [&](const Pt* p, double* out) {
+        if (!p) {
+            out[0] = own[0]; out[1] = own[1]; out[2] = own[2];
+        } else {
+            point_velocity(v, *p, out[0], out[1], out[2]);
+        }
+    };
+    double c[27], none[27];
+    const uint8_t fl = qr_fit_point(v, g, i, r, 3, own, vals, c);
+    if ((threadIdx.x & 63u) == 0) finish_pass1(v, v.prm[s], i, c, none, false, fl, o);
+}
+
 // Threads per block of the staged fits: a tile on one lane per particle, or
 // a part of it on more.
 constexpr int st_threads(int lpp) { return lpp == 1 ? BLOCK : 2 * BLOCK; }
@@ -460,15 +479,19 @@ constexpr int st_threads(int lpp) { return lpp == 1 ? BLOCK : 2 * BLOCK; }
 // (rows_ok = 0).  UNIT: the weights are unit, PERIODIC: some axis is
 // periodic (both known at compile time).
 // skip_rows > 0: particles whose stencils have at most skip_rows rows
-// (ghosts included) are left to the size-class launches.
+// (ghosts included) are left to the size-class launches.  redo null: the
+// block refits its ill-conditioned particles itself, a wavefront each (else
+// a launch after this one does; idle, it costs a step some 5 us).
 template <int LPP, bool UNIT, bool PERIODIC>
 __global__ __launch_bounds__(st_threads(LPP), 2) void k_pass1_st(View v, StepOut o,
                                                                 int32_t* redo,
                                                                 unsigned int* redo_n,
                                                                 int force_qr, int rows_ok,
-                                                                int skip_rows)
+                                                                int skip_rows, Counters* cnt)
 {
     constexpr int NT = st_threads(LPP), P = NT / LPP;
+    __shared__ unsigned int own_n;
+    __shared__ int32_t own_redo[P];
     __shared__ double sx[STAGE_CAP], sy[STAGE_CAP], sz[STAGE_CAP];
     __shared__ double su[STAGE_CAP], sv[STAGE_CAP], sw[STAGE_CAP];
     const BlockPart<P> part(v, rows_ok);
@@ -476,10 +499,10 @@ __global__ __launch_bounds__(st_threads(LPP), 2) void k_pass1_st(View v, StepOut
     const StageUnit& unit = part.unit;
     const int64_t i = part.i0 + threadIdx.x / LPP;
     const int sub = threadIdx.x % LPP;
-    if (unit.S >= 0) {
-        stage_pass1<NT>(v, unit, sx, sy, sz, su, sv, sw);
-        __syncthreads();
-    }
+    if (threadIdx.x == 0) own_n = 0u;
+    if (unit.S >= 0) stage_pass1<NT>(v, unit, sx, sy, sz, su, sv, sw);
+    __syncthreads();
+    [&]() {
     const int64_t n = v.n;
     if (i >= n || !part.mine(threadIdx.x / LPP)) return;
     const int s = sys_of(v.off, v.n_sys, i);
@@ -530,7 +553,15 @@ __global__ __launch_bounds__(st_threads(LPP), 2) void k_pass1_st(View v, StepOut
     }
 #pragma unroll
     for (int f = 0; f < 3; ++f) halve_squares(B[f]);
-    pass1_solve<LPP>(v, o, g, s, i, M, B, order_rows(v, r, mt), sub, redo, redo_n, force_qr);
+    pass1_solve<LPP>(v, o, g, s, i, M, B, order_rows(v, r, mt), sub, redo ? redo : own_redo,
+                     redo ? redo_n : &own_n, force_qr);
+    }();
+    if (redo) return;
+    __syncthreads();
+    const int refits = (int)own_n;
+    if (refits == 0) return;
+    if (threadIdx.x == 0) atomicAdd(&cnt->qr_refits, (unsigned long long)refits);
+    for (int t = threadIdx.x >> 6; t < refits; t += NT / 64) pass1_refit(v, o, own_redo[t]);
 }
 
 __global__ __launch_bounds__(QR_TPB) void k_pass1_qr(View v, StepOut o,
@@ -539,29 +570,12 @@ __global__ __launch_bounds__(QR_TPB) void k_pass1_qr(View v, StepOut o,
                                                     Counters* cnt)
 {
     // a wavefront per refit
-    const int lane = (int)(threadIdx.x & 63u);
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
     const unsigned int total = *redo_n;
     if (blockIdx.x == 0 && threadIdx.x == 0)
         atomicAdd(&cnt->qr_refits, (unsigned long long)total);
-    for (int64_t t = wave; t < (int64_t)total; t += nw) {
-        const int64_t i = redo[t];
-        const int s = sys_of(v.off, v.n_sys, i);
-        const GridInfo& g = v.grid[s];
-        const Rec r = load_rec(v, i);
-        const double own[3] = {v.u[i], v.v[i], v.w[i]};
-        auto vals = [&](const Pt* p, double* out) {
-            if (!p) {
-                out[0] = own[0]; out[1] = own[1]; out[2] = own[2];
-            } else {
-                point_velocity(v, *p, out[0], out[1], out[2]);
-            }
-        };
-        double c[27], none[27];
-        const uint8_t fl = qr_fit_point(v, g, i, r, 3, own, vals, c);
-        if (lane == 0) finish_pass1(v, v.prm[s], i, c, none, false, fl, o);
-    }
+    for (int64_t t = wave; t < (int64_t)total; t += nw) pass1_refit(v, o, redo[t]);
 }
 
 // lp_rheology_rhs: closure from given coefficients, Gram factor for pass 2
@@ -681,6 +695,31 @@ __global__ __launch_bounds__(BLOCK) void k_pass2(View v, const double* P,
     pass2_finish(v, prm, g, i, hand, yP, yE, Ei, o);
 }
 
+// The pass-2 refit of particle i by a wavefront.
+__device__ __forceinline__ void pass2_refit(const View& v, const double* P, const double* eta,
+                                            const double* hand, const RhsOut& o, int64_t i)
+{
+    const int64_t n = v.n;
+    const int s = sys_of(v.off, v.n_sys, i);
+    const GridInfo& g = v.grid[s];
+    const lp_params& prm = v.prm[s];
+    const Rec r = load_rec(v, i);
+    const double own[2] = {P[i], eta[i]};
+    auto vals = [&](const Pt* p, double* out) {
+        pass2_values(v, P, eta, p, prm, out[0], out[1]);
+    };
+    double c[18];
+    const uint8_t fl = qr_fit_point(v, g, i, r, 2, own, vals, c);
+    if ((threadIdx.x & 63u) != 0) return;
+    if (o.flags)
+        o.flags[i] = (uint8_t)((o.flags[i] & ~FLAG_LINEAR) | (fl & FLAG_LINEAR) | FLAG_QR);
+    const double gP[3] = {c[0], c[1], c[2]};
+    const double gE[3] = {c[9], c[10], c[11]};
+    double hv[11];
+    load_hand_tail(hand, n, i, eta[i], hv);
+    finish_rhs(v, prm, i, hv, gP, gE, o);
+}
+
 // Pass 2 with the neighbours of the block's tile staged in LDS, LPP lanes
 // per particle: positions, P and eta of the tile's list sources are loaded
 // once, coalesced, and every stencil row reads them from LDS.
@@ -697,10 +736,12 @@ __global__ __launch_bounds__(BLOCK) void k_pass2(View v, const double* P,
 // UNIT: the weights are unit, PERIODIC: some axis is periodic (both known
 // at compile time).
 template <int LPP, bool UNIT, bool PERIODIC>
-__global__ __launch_bounds__(st_threads(LPP), LPP == 1 ? 2 : 4) void k_pass2_st(
+__global__ __launch_bounds__(st_threads(LPP), 2) void k_pass2_st(
     View v, const double* P, const double* eta, const double* hand, const uint8_t* flags,
-    RhsOut o, int rows_ok, int skip_rows)
+    RhsOut o, int rows_ok, int skip_rows, int own_qr)
 {
+    __shared__ unsigned int own_n;
+    __shared__ int32_t own_redo[st_threads(LPP) / LPP];
     constexpr int NT = st_threads(LPP), PB = NT / LPP;
     __shared__ double sx[STAGE_CAP], sy[STAGE_CAP], sz[STAGE_CAP];
     __shared__ double sP[STAGE_CAP], sE[STAGE_CAP];
@@ -709,13 +750,16 @@ __global__ __launch_bounds__(st_threads(LPP), LPP == 1 ? 2 : 4) void k_pass2_st(
     const StageUnit& unit = part.unit;
     const int64_t i = part.i0 + threadIdx.x / LPP;
     const int sub = threadIdx.x % LPP;
-    if (unit.S >= 0) {
-        stage_pass2<NT>(v, P, eta, unit, sx, sy, sz, sP, sE);
-        __syncthreads();
-    }
+    if (threadIdx.x == 0) own_n = 0u;
+    if (unit.S >= 0) stage_pass2<NT>(v, P, eta, unit, sx, sy, sz, sP, sE);
+    __syncthreads();
+    [&]() {
     const int64_t n = v.n;
     if (i >= n || !part.mine(threadIdx.x / LPP)) return;
-    if (flags[i] & FLAG_QR) return;
+    if (flags[i] & FLAG_QR) {
+        if (own_qr && sub == 0) own_redo[atomicAdd(&own_n, 1u)] = (int32_t)i;
+        return;
+    }
     const int s = sys_of(v.off, v.n_sys, i);
     const GridInfo& g = v.grid[s];
     const lp_params& prm = v.prm[s];
@@ -779,6 +823,12 @@ __global__ __launch_bounds__(st_threads(LPP), LPP == 1 ? 2 : 4) void k_pass2_st(
     double hv[11];
     load_hand_tail(hand, n, i, Ei, hv);
     finish_rhs(v, prm, i, hv, gP, gE, o);
+    }();
+    if (!own_qr) return;
+    __syncthreads();
+    const int refits = (int)own_n;
+    for (int t = threadIdx.x >> 6; t < refits; t += NT / 64)
+        pass2_refit(v, P, eta, hand, o, own_redo[t]);
 }
 
 // ---- refined FP32 fits ----------------------------------------------------
@@ -1079,33 +1129,11 @@ __global__ __launch_bounds__(QR_TPB) void k_pass2_qr(View v, const double* P,
                                                     RhsOut o)
 {
     // a wavefront per refit
-    const int lane = (int)(threadIdx.x & 63u);
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
     const unsigned int total = *redo_n;
-    const int64_t n = v.n;
-    for (int64_t t = wave; t < (int64_t)total; t += nw) {
-        const int64_t i = redo[t];
-        const int s = sys_of(v.off, v.n_sys, i);
-        const GridInfo& g = v.grid[s];
-        const lp_params& prm = v.prm[s];
-        const Rec r = load_rec(v, i);
-        const double own[2] = {P[i], eta[i]};
-        auto vals = [&](const Pt* p, double* out) {
-            pass2_values(v, P, eta, p, prm, out[0], out[1]);
-        };
-        double c[18];
-        const uint8_t fl = qr_fit_point(v, g, i, r, 2, own, vals, c);
-        if (lane == 0) {
-            if (o.flags)
-                o.flags[i] = (uint8_t)((o.flags[i] & ~FLAG_LINEAR) | (fl & FLAG_LINEAR) | FLAG_QR);
-            const double gP[3] = {c[0], c[1], c[2]};
-            const double gE[3] = {c[9], c[10], c[11]};
-            double hv[11];
-            load_hand_tail(hand, n, i, eta[i], hv);
-            finish_rhs(v, prm, i, hv, gP, gE, o);
-        }
-    }
+    for (int64_t t = wave; t < (int64_t)total; t += nw)
+        pass2_refit(v, P, eta, hand, o, redo[t]);
 }
 
 __global__ void k_zero_u32(unsigned int* p) { *p = 0u; }
@@ -1192,20 +1220,36 @@ void by_kind(const lp_ctx* c, F&& f)
 // The fits may read the staged rows of the last selection.
 int staged_rows(const lp_ctx* c) { return c->map_ok && c->rows_ok ? 1 : 0; }
 
+// Size-class dispatch applies to the float64 quadratic fits.
+bool classes_on(const lp_ctx* c)
+{
+    return c->classes && c->cfg.fit_order == 2 && c->cfg.precision == LP_FP64;
+}
+
+// The staged fits refit their own ill-conditioned particles: both fits run
+// as one staged launch each (the refits of one fit are those of the other).
+bool own_refits(const lp_ctx* c, int fq)
+{
+    return c->lpp1 == 1 && c->lpp2 == 1 && !classes_on(c) && !fq &&
+           c->cfg.precision == LP_FP64 && c->cfg.fit_order == 2;
+}
+
 template <int LPP>
-void launch_pass1_st(lp_ctx* c, const View& v, const StepOut& so, int fq, int skip_rows)
+void launch_pass1_st(lp_ctx* c, const View& v, const StepOut& so, int fq, int skip_rows,
+                     bool own)
 {
     Work& w = c->w;
     constexpr int NT = st_threads(LPP);
     by_kind(c, [&](auto unit, auto per) {
         hipLaunchKernelGGL((k_pass1_st<LPP, unit.value, per.value>),
                            dim3(BlockPart<NT / LPP>::blocks(c->n)), dim3(NT), 0, c->stream, v, so,
-                           w.redo, w.redo_n, fq, staged_rows(c), skip_rows);
+                           own ? nullptr : w.redo, own ? nullptr : w.redo_n, fq,
+                           staged_rows(c), skip_rows, w.cnt);
     });
 }
 
 template <int LPP>
-void launch_pass2_st(lp_ctx* c, const View& v, const RhsOut& o, int skip_rows)
+void launch_pass2_st(lp_ctx* c, const View& v, const RhsOut& o, int skip_rows, bool own)
 {
     Work& w = c->w;
     constexpr int NT = st_threads(LPP);
@@ -1213,24 +1257,25 @@ void launch_pass2_st(lp_ctx* c, const View& v, const RhsOut& o, int skip_rows)
         hipLaunchKernelGGL((k_pass2_st<LPP, unit.value, per.value>),
                            dim3(BlockPart<NT / LPP>::blocks(c->n)), dim3(NT), 0, c->stream, v,
                            (const double*)w.P, (const double*)w.eta, (const double*)w.hand,
-                           (const uint8_t*)w.flags, o, staged_rows(c), skip_rows);
+                           (const uint8_t*)w.flags, o, staged_rows(c), skip_rows, own ? 1 : 0);
     });
 }
 
 // The staged fits: lanes per particle by the particle count.
-void launch_pass1_tiles(lp_ctx* c, const View& v, const StepOut& so, int fq, int skip_rows)
+void launch_pass1_tiles(lp_ctx* c, const View& v, const StepOut& so, int fq, int skip_rows,
+                        bool own)
 {
-    if (c->n <= ST_L8_MAX) launch_pass1_st<8>(c, v, so, fq, skip_rows);
-    else launch_pass1_st<1>(c, v, so, fq, skip_rows);
+    if (c->n <= ST_L8_MAX) launch_pass1_st<8>(c, v, so, fq, skip_rows, own);
+    else launch_pass1_st<1>(c, v, so, fq, skip_rows, own);
 }
 
-void launch_pass2_tiles(lp_ctx* c, const View& v, const RhsOut& o, int skip_rows)
+void launch_pass2_tiles(lp_ctx* c, const View& v, const RhsOut& o, int skip_rows, bool own)
 {
-    if (c->n <= ST_L8_MAX) launch_pass2_st<8>(c, v, o, skip_rows);
-    else launch_pass2_st<1>(c, v, o, skip_rows);
+    if (c->n <= ST_L8_MAX) launch_pass2_st<8>(c, v, o, skip_rows, own);
+    else launch_pass2_st<1>(c, v, o, skip_rows, own);
 }
 
-void launch_pass1(lp_ctx* c, int lpp, const View& v, const StepOut& so, int fq)
+void launch_pass1(lp_ctx* c, int lpp, const View& v, const StepOut& so, int fq, bool own)
 {
     Work& w = c->w;
     const int64_t n = c->n;
@@ -1245,11 +1290,11 @@ void launch_pass1(lp_ctx* c, int lpp, const View& v, const StepOut& so, int fq)
         hipLaunchKernelGGL((k_pass1<2>), dim3(blocks_for(2 * n)), dim3(BLOCK), 0,
                            c->stream, v, so, w.redo, w.redo_n, fq, no, nc);
         break;
-    default: launch_pass1_tiles(c, v, so, fq, 0);
+    default: launch_pass1_tiles(c, v, so, fq, 0, own);
     }
 }
 
-void launch_pass2(lp_ctx* c, int lpp, const View& v, const RhsOut& o)
+void launch_pass2(lp_ctx* c, int lpp, const View& v, const RhsOut& o, bool own)
 {
     Work& w = c->w;
     const int64_t n = c->n;
@@ -1268,7 +1313,7 @@ void launch_pass2(lp_ctx* c, int lpp, const View& v, const RhsOut& o)
         hipLaunchKernelGGL((k_pass2<2>), dim3(blocks_for(2 * n)), dim3(BLOCK), 0,
                            c->stream, v, P, E, H, F, o, no, nc);
         break;
-    default: launch_pass2_tiles(c, v, o, 0);
+    default: launch_pass2_tiles(c, v, o, 0, own);
     }
 }
 
@@ -1294,7 +1339,7 @@ void launch_pass1_class(lp_ctx* c, int cls, int lpp, const View& v, const StepOu
     const uint32_t* cnt = w.cls_cnt + cls;
     if (lpp == 0) {
         // the largest class through the LDS-staged tile kernel
-        launch_pass1_tiles(c, v, so, fq, CLASS_ROWS1);
+        launch_pass1_tiles(c, v, so, fq, CLASS_ROWS1, false);
         return;
     }
     switch (lpp) {
@@ -1323,7 +1368,7 @@ void launch_pass2_class(lp_ctx* c, int cls, int lpp, const View& v, const RhsOut
     const double* H = w.hand;
     const uint8_t* F = w.flags;
     if (lpp == 0) {
-        launch_pass2_tiles(c, v, o, CLASS_ROWS1);
+        launch_pass2_tiles(c, v, o, CLASS_ROWS1, false);
         return;
     }
     switch (lpp) {
@@ -1341,12 +1386,6 @@ void launch_pass2_class(lp_ctx* c, int cls, int lpp, const View& v, const RhsOut
     }
 }
 
-// Size-class dispatch applies to the float64 quadratic fits.
-bool classes_on(const lp_ctx* c)
-{
-    return c->classes && c->cfg.fit_order == 2 && c->cfg.precision == LP_FP64;
-}
-
 // Pass 1 of a step: the size classes with their lanes, or one launch.
 void run_pass1(lp_ctx* c, const View& v, const StepOut& so, int fq)
 {
@@ -1354,16 +1393,16 @@ void run_pass1(lp_ctx* c, const View& v, const StepOut& so, int fq)
         classify(c, v);
         for (int k = 0; k < NCLASS; ++k) launch_pass1_class(c, k, c->cls_lpp1[k], v, so, fq);
     } else {
-        launch_pass1(c, c->lpp1, v, so, fq);
+        launch_pass1(c, c->lpp1, v, so, fq, own_refits(c, fq));
     }
 }
 
-void run_pass2(lp_ctx* c, const View& v, const RhsOut& o)
+void run_pass2(lp_ctx* c, const View& v, const RhsOut& o, bool own)
 {
     if (classes_on(c)) {
         for (int k = 0; k < NCLASS; ++k) launch_pass2_class(c, k, c->cls_lpp2[k], v, o);
     } else {
-        launch_pass2(c, c->lpp2, v, o);
+        launch_pass2(c, c->lpp2, v, o, own);
     }
 }
 
@@ -1446,7 +1485,7 @@ lp_status rhs_from_coef(lp_ctx* c, const double* const st[7],
         if (c->cfg.fit_order == 3) {
             launch_pass2_cubic(c, v, w.P, w.eta, w.hand, o);
         } else {
-            launch_pass2(c, c->lpp2, v, o);
+            launch_pass2(c, c->lpp2, v, o, false);
             hipLaunchKernelGGL(k_pass2_qr, dim3(QR_BLOCKS), dim3(QR_TPB), 0,
                                c->stream, v, (const double*)w.P, (const double*)w.eta,
                                (const double*)w.hand, (const int32_t*)w.redo,
@@ -1485,9 +1524,10 @@ lp_status step_rhs(lp_ctx* c, const double* const st[7])
             run_pass1(c, v, so, fq);
         prof_mark(c, 3, true);
         prof_mark(c, 4, false);
-        hipLaunchKernelGGL(k_pass1_qr, dim3(QR_BLOCKS), dim3(QR_TPB), 0,
-                           c->stream, v, so, (const int32_t*)w.redo,
-                           (const unsigned int*)w.redo_n, w.cnt);
+        if (!own_refits(c, fq))
+            hipLaunchKernelGGL(k_pass1_qr, dim3(QR_BLOCKS), dim3(QR_TPB), 0,
+                               c->stream, v, so, (const int32_t*)w.redo,
+                               (const unsigned int*)w.redo_n, w.cnt);
         prof_mark(c, 4, true);
     }
     hipError_t e = hipGetLastError();
@@ -1501,14 +1541,18 @@ lp_status step_pass1_coef(lp_ctx* c, const double* const st[7])
     const int64_t n = c->n;
     View v = make_view(c, st);
     StepOut so{w.P, w.eta, w.hand, w.flags, nullptr, w.coefu};
+    // float64 whatever the steps' precision: refits of its own only where the
+    // step's would be
+    const bool own = own_refits(c, 0);
     redo_reset(c);
     if (n > 0) {
         // the pass-2 fit of these stencils may run by size class
         if (classes_on(c)) classify(c, v);
-        launch_pass1(c, c->lpp1, v, so, 0);
-        hipLaunchKernelGGL(k_pass1_qr, dim3(QR_BLOCKS), dim3(QR_TPB), 0,
-                           c->stream, v, so, (const int32_t*)w.redo,
-                           (const unsigned int*)w.redo_n, w.cnt);
+        launch_pass1(c, c->lpp1, v, so, 0, own);
+        if (!own)
+            hipLaunchKernelGGL(k_pass1_qr, dim3(QR_BLOCKS), dim3(QR_TPB), 0,
+                               c->stream, v, so, (const int32_t*)w.redo,
+                               (const unsigned int*)w.redo_n, w.cnt);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(c, e, "adjoint pass-1 launch");
@@ -1524,6 +1568,9 @@ lp_status step_pass2(lp_ctx* c, const double* const st[7], double dt,
     RhsOut o = rhs_out(c, acc, dVdt, nullptr);
     for (int a = 0; a < 7; ++a) o.out[a] = out ? out[a] : nullptr;
     o.dt = dt;
+    // as pass 1 of these stencils did (fp64: step_pass1_coef)
+    const bool own =
+        own_refits(c, !fp64 && (c->cfg.debug_flags & LP_DEBUG_QR_FIT) ? 1 : 0);
     if (n > 0) {
         prof_mark(c, 5, false);
         if (c->cfg.fit_order == 3)
@@ -1539,13 +1586,14 @@ lp_status step_pass2(lp_ctx* c, const double* const st[7], double dt,
             });
         }
         else
-            run_pass2(c, v, o);
+            run_pass2(c, v, o, own);
         prof_mark(c, 5, true);
         prof_mark(c, 6, false);
-        hipLaunchKernelGGL(k_pass2_qr, dim3(QR_BLOCKS), dim3(QR_TPB), 0,
-                           c->stream, v, (const double*)w.P, (const double*)w.eta,
-                           (const double*)w.hand, (const int32_t*)w.redo,
-                           (const unsigned int*)w.redo_n, o);
+        if (!own)
+            hipLaunchKernelGGL(k_pass2_qr, dim3(QR_BLOCKS), dim3(QR_TPB), 0,
+                               c->stream, v, (const double*)w.P, (const double*)w.eta,
+                               (const double*)w.hand, (const int32_t*)w.redo,
+                               (const unsigned int*)w.redo_n, o);
         prof_mark(c, 6, true);
     }
     hipError_t e = hipGetLastError();
@@ -1593,16 +1641,16 @@ lp_status autotune_fits(lp_ctx* c, const double* const st[7], int32_t* choice)
     float best1 = 1e30f, best2 = 1e30f;
     int pick1 = 1, pick2 = 1;
     for (int q = 0; q < 3 && e == hipSuccess; ++q) {
-        const float t = timed([&] { launch_pass1(c, cand[q], v, so, 0); });
+        const float t = timed([&] { launch_pass1(c, cand[q], v, so, 0, false); });
         if (t < best1) { best1 = t; pick1 = cand[q]; }
     }
     // pass 2 needs the pass-1 outputs
     if (e == hipSuccess) {
         redo_reset(c);
-        launch_pass1(c, pick1, v, so, 0);
+        launch_pass1(c, pick1, v, so, 0, false);
     }
     for (int q = 0; q < 3 && e == hipSuccess; ++q) {
-        const float t = timed([&] { launch_pass2(c, cand[q], v, o); });
+        const float t = timed([&] { launch_pass2(c, cand[q], v, o, false); });
         if (t < best2) { best2 = t; pick2 = cand[q]; }
     }
     // by stencil size class (float64 quadratic fits): each class with its
@@ -1633,7 +1681,7 @@ lp_status autotune_fits(lp_ctx* c, const double* const st[7], int32_t* choice)
         }
         if (e == hipSuccess) {
             redo_reset(c);
-            launch_pass1(c, pick1, v, so, 0);
+            launch_pass1(c, pick1, v, so, 0, false);
         }
         for (int k = 0; k < NCLASS && e == hipSuccess; ++k) {
             cb2[k] = 1e30f;

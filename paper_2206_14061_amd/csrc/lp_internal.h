@@ -142,6 +142,7 @@ struct Summary {
     int32_t axis_bits;
     int32_t bad;                // a cell coordinate needs more than 16 bits
     unsigned long long disp;    // ordered encoding of max (displacement/skin)^2
+    uint32_t done, pad;         // blocks of a displacement check that have ended
 };
 
 // Device error word.
@@ -214,7 +215,8 @@ struct Work {
     GridInfo* grid = nullptr;
     unsigned long long* bbox = nullptr;   // n_sys x 6 ordered encodings
     Summary* summary = nullptr;
-    Summary* h_summary = nullptr;         // pinned host copy
+    Summary* h_summary = nullptr;         // host copy
+    Summary* pinned = nullptr;            // the same where the device can write it
     ErrWord* err = nullptr;
     Counters* cnt = nullptr;
     // sort

@@ -522,6 +522,80 @@ __global__ void k_mirror_count(int64_t n, int n_sys, const int64_t* off,
     }
 }
 
+// k_mirror_count and k_mirror_write in one launch, for few particles: a tile
+// per block of MIRROR_NT threads, each block counting the mirrors of the
+// tiles before its own again (at most MIRROR_ONE_MAX heights in all, from L2)
+// instead of waiting for a launch that has.  Two launches took 2.2 and 3.6 us
+// and the gap between them at 4,096 particles; one takes 3.2.
+constexpr int MIRROR_NT = 1024;
+constexpr int64_t MIRROR_ONE_MAX = 32768;
+__global__ __launch_bounds__(MIRROR_NT) void k_mirror_one(
+    int64_t n, int n_sys, const int64_t* off, const GridInfo* grid, const double* z,
+    unsigned int* hard_n, unsigned int* redo_n, Summary* sum, int32_t* mirror_of, int32_t* msrc)
+{
+    constexpr int PER = SORT_TILE / MIRROR_NT;
+    __shared__ uint32_t wsum[MIRROR_NT / 64], before;
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    if (t == 0) {
+        before = 0u;
+        if (blockIdx.x == 0) {
+            *hard_n = 0u;
+            *redo_n = 0u;
+            sum->disp = DISP_ZERO;
+        }
+    }
+    const int64_t t0 = (int64_t)blockIdx.x * SORT_TILE;
+    const bool one = n_sys == 1;
+    const double wall0 = grid[0].wall, R0 = grid[0].R;
+    auto near = [&](int64_t i, double zi) {
+        double wall = wall0, R = R0;
+        if (!one) {
+            const GridInfo& g = grid[sys_of(off, n_sys, i)];
+            wall = g.wall;
+            R = g.R;
+        }
+        return dsub(zi, wall) < R;
+    };
+    // this tile's heights first: wavefront w takes particles 64 PER w + 64 q
+    double zz[PER];
+    const int64_t wb = t0 + 64 * PER * w + lane;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) zz[q] = wb + 64 * q < n ? z[wb + 64 * q] : INFINITY;
+    __syncthreads();
+    uint32_t c = 0u;
+#pragma unroll 4
+    for (int64_t i = t; i < t0; i += MIRROR_NT) c += near(i, z[i]) ? 1u : 0u;
+    for (int d = 32; d > 0; d >>= 1) c += __shfl_xor(c, d);
+    if (lane == 0 && c) atomicAdd(&before, c);
+    uint64_t m[PER];
+    uint32_t mine = 0u;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        m[q] = __ballot(wb + 64 * q < n && near(wb + 64 * q, zz[q]));
+        mine += (uint32_t)__popcll(m[q]);
+    }
+    if (lane == 0) wsum[w] = mine;
+    __syncthreads();
+    uint32_t k = before, tot = before;
+    for (int q = 0; q < MIRROR_NT / 64; ++q) {
+        k += q < w ? wsum[q] : 0u;
+        tot += wsum[q];
+    }
+    if (blockIdx.x == gridDim.x - 1 && t == 0) sum->n_mirror = (int64_t)tot;
+    const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int64_t i = wb + 64 * q;
+        if (i < n) {
+            const bool f = (m[q] >> lane) & 1ull;
+            const uint32_t kk = k + (uint32_t)__popcll(m[q] & below);
+            mirror_of[i] = f ? (int32_t)kk : -1;
+            if (f) msrc[kk] = (int32_t)i;
+        }
+        k += (uint32_t)__popcll(m[q]);
+    }
+}
+
 // Exclusive scan in place of a uint32 array (single block of 1024); the
 // total goes to *total.
 __global__ void k_scan_total(uint32_t* a, int64_t cnt, int64_t* total)
@@ -1358,13 +1432,12 @@ void launch_select_rest(lp_ctx* c, const View& v)
 }
 
 // ---- exports -----------------------------------------------------------
-
 //
 // EXP_LANES adjacent lanes per particle: each tests or reads every
 // EXP_LANES-th list entry, the group's ids are gathered in LDS in list order
-// and written from there, consecutive lanes to consecutive places.  List
-// order is id order except around periodic axes; where it is not, every id is
-// ranked by counting the smaller ones.  (A thread per particle, sorting by
+// and written from there, consecutive lanes to consecutive places.  Lists run
+// by rows of cells and ids by the cells' Morton order, so an id's place is the
+// count of the smaller ones (unless the list is in order).  (A thread per particle, sorting by
 // insertion in its global row, took 484 us for the candidates and 266 for the
 // stencils of 49,569 particles, and the offsets summed by one block 105 twice;
 // now 57, 37 and 13.)
@@ -1809,19 +1882,25 @@ lp_status stencils_build(lp_ctx* c, const double* const st[7], bool packed, int 
                                st[1], st[2], w.p4);
         // mirrors of the current state (ids n + k in ascending source order)
         const int64_t nb = (n + SORT_TILE - 1) / SORT_TILE;
-        hipLaunchKernelGGL(k_mirror_count, dim3((unsigned)nb), dim3(BLOCK), 0, s, n,
-                           c->n_sys, w.off, w.grid, st[2], w.bsum, w.hard_n, w.redo_n,
-                           w.summary);
-        // up to MIRROR_SUM_BLOCKS blocks each add the counts before them
-        // (at most that many words per block, from L2) instead of a scan
-        const int scanned =
-            (nb > MIRROR_SUM_BLOCKS || (c->cfg.debug_flags & LP_DEBUG_MIRROR_SCAN)) ? 1 : 0;
-        if (scanned)
-            hipLaunchKernelGGL(k_scan_total, dim3(1), dim3(1024), 0, s,
-                               (uint32_t*)w.bsum, nb, &w.summary->n_mirror);
-        hipLaunchKernelGGL(k_mirror_write, dim3((unsigned)nb), dim3(BLOCK), 0, s, n,
-                           c->n_sys, w.off, w.grid, w.bsum, scanned, &w.summary->n_mirror,
-                           st[2], w.mirror_of, w.msrc);
+        if (n <= MIRROR_ONE_MAX && !(c->cfg.debug_flags & LP_DEBUG_MIRROR_SCAN)) {
+            hipLaunchKernelGGL(k_mirror_one, dim3((unsigned)nb), dim3(MIRROR_NT), 0, s, n,
+                               c->n_sys, w.off, w.grid, st[2], w.hard_n, w.redo_n, w.summary,
+                               w.mirror_of, w.msrc);
+        } else {
+            hipLaunchKernelGGL(k_mirror_count, dim3((unsigned)nb), dim3(BLOCK), 0, s, n,
+                               c->n_sys, w.off, w.grid, st[2], w.bsum, w.hard_n, w.redo_n,
+                               w.summary);
+            // up to MIRROR_SUM_BLOCKS blocks each add the counts before them
+            // (at most that many words per block, from L2) instead of a scan
+            const int scanned =
+                (nb > MIRROR_SUM_BLOCKS || (c->cfg.debug_flags & LP_DEBUG_MIRROR_SCAN)) ? 1 : 0;
+            if (scanned)
+                hipLaunchKernelGGL(k_scan_total, dim3(1), dim3(1024), 0, s,
+                                   (uint32_t*)w.bsum, nb, &w.summary->n_mirror);
+            hipLaunchKernelGGL(k_mirror_write, dim3((unsigned)nb), dim3(BLOCK), 0, s, n,
+                               c->n_sys, w.off, w.grid, w.bsum, scanned, &w.summary->n_mirror,
+                               st[2], w.mirror_of, w.msrc);
+        }
         // the select phase times the selection kernel alone
         prof_mark(c, 1, false);
         launch_select(c, v);

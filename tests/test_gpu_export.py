@@ -1,7 +1,6 @@
 """Candidate and stencil exports at the edges of their kernels: particle
 counts around a block of the offset sums (4,096) and around 16 particles,
-and periodic boxes, where list order is not id order and every id is ranked;
-against the oracle, entry for entry."""
+and periodic boxes; against the oracle, entry for entry."""
 import numpy as np
 import pytest
 
