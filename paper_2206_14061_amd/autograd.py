@@ -88,7 +88,8 @@ def _make_function():
                         st = ckpts[k0].clone()
                         inputs, recs = [], []
                         for k in range(k0, end):
-                            inputs.append(st.clone())
+                            # (the checkpoint itself is the first step's input)
+                            inputs.append(st.clone() if k > k0 else ckpts[k0])
                             rec = StepRecord(st.n, force_sort=(k == k0))
                             step(st, dt, rec=rec)
                             recs.append(rec)
