@@ -191,8 +191,9 @@ lp_status step_device(lp_ctx* c, double* const in[7], int32_t* ids, double dt, i
     for (int a = 0; a < 7; ++a) cin[a] = in[a];
     // the decision copies the state into the working state, which a
     // rebuild overwrites in its new order
-    lp_status r = rebuild_decision(c, cin, c->cfg.skin > 0.0 ? 0 : 1, first);
-    if (r == LP_OK) r = cells_build_device(c, in, ids, c->w.gate, bits);
+    const int force = c->cfg.skin > 0.0 ? 0 : 1;
+    lp_status r = rebuild_decision(c, cin, force, first, bits);
+    if (r == LP_OK) r = cells_build_device(c, in, ids, c->w.gate, bits, force);
     if (r == LP_OK) r = tile_map_build(c, c->w.gate);
     const double* sorted[7];
     for (int a = 0; a < 7; ++a) sorted[a] = c->w.sst[a];

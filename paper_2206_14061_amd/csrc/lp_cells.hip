@@ -148,13 +148,10 @@ __global__ void k_bbox(int64_t n, int n_sys, const int64_t* off,
 // (captured steps, no host check) every edge is scaled up by a common
 // factor until each axis needs at most max_bits bits and all cells fit in
 // max_cells: any edge at least the list radius finds the same pairs.
-__global__ void k_grid(int n_sys, const int64_t* off, const lp_params* prm,
-                       double skin, const unsigned long long* bbox,
-                       GridInfo* grid, Summary* sum, int max_bits,
-                       int64_t max_cells, ErrWord* err, const int32_t* gate)
+__device__ void grid_of(int n_sys, const int64_t* off, const lp_params* prm, double skin,
+                        const unsigned long long* bbox, GridInfo* grid, Summary* sum,
+                        int max_bits, int64_t max_cells, ErrWord* err)
 {
-    LP_GATE(gate);
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
     double scale = 1.0;
     for (int attempt = 0; attempt < 64; ++attempt) {
         int64_t base = 0;
@@ -258,6 +255,16 @@ __global__ void k_grid(int n_sys, const int64_t* off, const lp_params* prm,
     }
 }
 
+__global__ void k_grid(int n_sys, const int64_t* off, const lp_params* prm,
+                       double skin, const unsigned long long* bbox,
+                       GridInfo* grid, Summary* sum, int max_bits,
+                       int64_t max_cells, ErrWord* err, const int32_t* gate)
+{
+    LP_GATE(gate);
+    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    grid_of(n_sys, off, prm, skin, bbox, grid, sum, max_bits, max_cells, err);
+}
+
 __device__ __forceinline__ void cell_of(const GridInfo& g, double x, double y,
                                         double z, int& cx, int& cy, int& cz)
 {
@@ -270,7 +277,26 @@ __device__ __forceinline__ void cell_of(const GridInfo& g, double x, double y,
     cz = iz < 0 ? 0 : (iz >= g.nz ? g.nz - 1 : iz);
 }
 
-// Sort keys (system, Morton code of the cell) and identity values.
+// Sort key of particle i (system, Morton code of the cell).
+__device__ __forceinline__ unsigned long long key_of(int n_sys, const int64_t* off,
+                                                     const GridInfo* grid, int64_t i, double x,
+                                                     double y, double z, int shift_sys,
+                                                     ErrWord* err)
+{
+    const int s = sys_of(off, n_sys, i);
+    const GridInfo& g = grid[s];
+    int cx, cy, cz;
+    cell_of(g, x, y, z, cx, cy, cz);
+    // positions along a periodic axis must lie within one period of the box
+    const bool outx = g.Lx > 0.0 && !(x >= dsub(g.xlo, g.Lx) &&
+                                      x < dadd(g.xlo, dmul(2.0, g.Lx)));
+    const bool outy = g.Ly > 0.0 && !(y >= dsub(g.ylo, g.Ly) &&
+                                      y < dadd(g.ylo, dmul(2.0, g.Ly)));
+    if (outx || outy) raise_error(err, ERR_BOX, i);
+    return ((unsigned long long)s << shift_sys) | morton3(cx, cy, cz);
+}
+
+// Sort keys and identity values.
 __global__ void k_keys(int64_t n, int n_sys, const int64_t* off,
                        const GridInfo* grid, const double* x, const double* y,
                        const double* z, int shift_sys,
@@ -280,18 +306,8 @@ __global__ void k_keys(int64_t n, int n_sys, const int64_t* off,
     LP_GATE(gate);
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const int s = sys_of(off, n_sys, i);
-    const GridInfo& g = grid[s];
-    int cx, cy, cz;
-    cell_of(g, x[i], y[i], z[i], cx, cy, cz);
-    keys[i] = ((unsigned long long)s << shift_sys) | morton3(cx, cy, cz);
+    keys[i] = key_of(n_sys, off, grid, i, x[i], y[i], z[i], shift_sys, err);
     vals[i] = (int32_t)i;
-    // positions along a periodic axis must lie within one period of the box
-    const bool outx = g.Lx > 0.0 && !(x[i] >= dsub(g.xlo, g.Lx) &&
-                                      x[i] < dadd(g.xlo, dmul(2.0, g.Lx)));
-    const bool outy = g.Ly > 0.0 && !(y[i] >= dsub(g.ylo, g.Ly) &&
-                                      y[i] < dadd(g.ylo, dmul(2.0, g.Ly)));
-    if (outx || outy) raise_error(err, ERR_BOX, i);
 }
 
 // ---- stable LSD radix sort, digits of up to RADIX_MAX_BITS bits ---------
@@ -454,14 +470,11 @@ struct Dest7 {
 // for a rebuild (rx not null) the positions again as the reference of the
 // next displacement check; the positions' 32-byte records (p4, optional);
 // and the caller's particle ids (ids, optional) into ids_tmp.
-__global__ void k_gather7(int64_t n, const int32_t* perm, State7 in, Dest7 out,
-                          double* rx, double* ry, double* rz, double* p4,
-                          const int32_t* ids, int32_t* ids_tmp, const int32_t* gate)
+__device__ __forceinline__ void gather_one(int64_t i, int64_t j, const State7& in,
+                                           const Dest7& out, double* rx, double* ry,
+                                           double* rz, double* p4, const int32_t* ids,
+                                           int32_t* ids_tmp)
 {
-    LP_GATE(gate);
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int64_t j = perm ? perm[i] : i;
     double v[7];
 #pragma unroll
     for (int a = 0; a < 7; ++a) v[a] = in.a[a][j];
@@ -480,6 +493,16 @@ __global__ void k_gather7(int64_t n, const int32_t* perm, State7 in, Dest7 out,
         r[1] = make_double2(v[2] + 0.0, 0.0);
     }
     if (ids) ids_tmp[i] = ids[j];
+}
+
+__global__ void k_gather7(int64_t n, const int32_t* perm, State7 in, Dest7 out,
+                          double* rx, double* ry, double* rz, double* p4,
+                          const int32_t* ids, int32_t* ids_tmp, const int32_t* gate)
+{
+    LP_GATE(gate);
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    gather_one(i, perm ? perm[i] : i, in, out, rx, ry, rz, p4, ids, ids_tmp);
 }
 
 __global__ void k_copy_i32(int64_t n, const int32_t* a, int32_t* b, const int32_t* gate)
@@ -521,6 +544,19 @@ __global__ void k_fill2_i32(int64_t n, int32_t* a, int32_t* b, int32_t v,
     }
 }
 
+// Particle i, the first or last of its cell, into the cell's range.
+__device__ __forceinline__ void cell_ends(int n_sys, const int64_t* off, const GridInfo* grid,
+                                          int64_t i, double x, double y, double z, bool first,
+                                          bool last, int32_t* cs, int32_t* ce)
+{
+    const GridInfo& g = grid[sys_of(off, n_sys, i)];
+    int cx, cy, cz;
+    cell_of(g, x, y, z, cx, cy, cz);
+    const int64_t c = g.cell_base + cx + (int64_t)g.nx * (cy + (int64_t)g.ny * cz);
+    if (first) cs[c] = (int32_t)i;
+    if (last) ce[c] = (int32_t)(i + 1);
+}
+
 // Cell start/end from sorted keys; positions give the linear cell index.
 __global__ void k_cell_bounds(int64_t cnt, int n_sys, const int64_t* off,
                               const GridInfo* grid,
@@ -537,14 +573,7 @@ __global__ void k_cell_bounds(int64_t cnt, int n_sys, const int64_t* off,
     const unsigned long long k = keys[i];
     const bool first = (i == 0) || keys[i - 1] != k;
     const bool last = (i == cnt - 1) || keys[i + 1] != k;
-    if (!first && !last) return;
-    const int s = sys_of(off, n_sys, i);
-    const GridInfo& g = grid[s];
-    int cx, cy, cz;
-    cell_of(g, x[i], y[i], z[i], cx, cy, cz);
-    const int64_t c = g.cell_base + cx + (int64_t)g.nx * (cy + (int64_t)g.ny * cz);
-    if (first) cs[c] = (int32_t)i;
-    if (last) ce[c] = (int32_t)(i + 1);
+    if (first || last) cell_ends(n_sys, off, grid, i, x[i], y[i], z[i], first, last, cs, ce);
 }
 
 __global__ void k_iota(int64_t n, int32_t* p, const int32_t* gate)
@@ -724,19 +753,106 @@ void radix_sort(lp_ctx* c, int64_t cnt, int bits, unsigned long long*& kr,
 // Rebuild decision of a captured step: gate[0] = rebuild (re-sort and
 // rebuild the list), when some particle has moved 0.49 skin R since the
 // last build (or always when `force`).
-__global__ void k_decide(Summary* sum, int32_t* gate, Counters* cnt, int force,
-                         unsigned long long* bbox, int n_sys)
+// A captured step's decision, by one thread.
+__device__ __forceinline__ bool decide(Summary* sum, int32_t* gate, Counters* cnt, int force)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
     const double r = ord_dec(sum->disp);
     const bool rebuild = force || !(sqrt(r) < 0.49);
     gate[0] = rebuild ? 1 : 0;
     // the next step's displacement check starts from zero
     sum->disp = DISP_ZERO;
-    if (!rebuild) return;
-    atomicAdd(&cnt->rebuilds, 1ull);
+    if (rebuild) atomicAdd(&cnt->rebuilds, 1ull);
+    return rebuild;
+}
+
+__global__ void k_decide(Summary* sum, int32_t* gate, Counters* cnt, int force,
+                         unsigned long long* bbox, int n_sys)
+{
+    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    if (!decide(sum, gate, cnt, force)) return;
     // empty bounding boxes for the rebuild's k_bbox (as k_bbox_init)
     for (int q = 0; q < 6 * n_sys; ++q) bbox[q] = (q % 6) < 3 ? ~0ull : 0ull;
+}
+
+// A captured step's decision and re-sort in one block, for few particles and
+// systems: boxes, grids, keys, sort (bitonic in LDS, the particle in a key's
+// low bits, which makes the order the stable one), gather and cell tables.
+// The launches of k_decide to k_cell_bounds (twelve) run in every captured
+// step, nearly always to find that nothing is to be done: a step of a periodic
+// layer of some 6,000 particles took 72 us with them and takes 53 with this.
+constexpr int SMALL_NT = 1024, SMALL_N = 8192, SMALL_SYS = 64, SMALL_BITS = 13;
+static_assert(1 << SMALL_BITS == SMALL_N, "a particle in the low bits");
+
+__global__ __launch_bounds__(SMALL_NT) void k_rebuild_small(
+    int64_t n, int n_sys, const int64_t* off, const lp_params* prm, double skin, State7 in,
+    Dest7 out, unsigned long long* bbox, GridInfo* grid, Summary* sum, int max_bits,
+    int64_t max_cells, int shift_sys, double* rx, double* ry, double* rz, double* p4,
+    int32_t* ids, int32_t* ids_tmp, int32_t* cs, int32_t* ce, ErrWord* err, Counters* cnt,
+    int32_t* gate, int force)
+{
+    __shared__ unsigned long long key[SMALL_N];
+    __shared__ unsigned long long box[6 * SMALL_SYS];
+    __shared__ int go;
+    const int t = threadIdx.x;
+    if (t == 0) go = decide(sum, gate, cnt, force) ? 1 : 0;
+    for (int q = t; q < 6 * n_sys; q += SMALL_NT) box[q] = (q % 6) < 3 ? ~0ull : 0ull;
+    __syncthreads();
+    if (!go) return;
+    // ---- boxes (a wavefront inside one system combines its particles first)
+    for (int64_t i0 = 0; i0 < n; i0 += SMALL_NT) {
+        const int64_t i = i0 + t < n ? i0 + t : n - 1;
+        const int s = sys_of(off, n_sys, i);
+        double lo[3] = {in.a[0][i], in.a[1][i], in.a[2][i]}, hi[3] = {lo[0], lo[1], lo[2]};
+        const bool one = __ballot(s == __builtin_amdgcn_readfirstlane(s)) == ~0ull;
+        if (one)
+            for (int d = 32; d > 0; d >>= 1)
+                for (int a = 0; a < 3; ++a) {
+                    lo[a] = fmin(lo[a], __shfl_xor(lo[a], d));
+                    hi[a] = fmax(hi[a], __shfl_xor(hi[a], d));
+                }
+        if (!one || (t & 63) == 0) bbox_flush(box, s, lo, hi);
+    }
+    __syncthreads();
+    for (int q = t; q < 6 * n_sys; q += SMALL_NT) bbox[q] = box[q];
+    if (t == 0)
+        grid_of(n_sys, off, prm, skin, box, grid, sum, max_bits, max_cells, err);
+    __syncthreads();
+    // ---- keys, sorted
+    int len = 2;
+    while (len < n) len *= 2;
+    for (int i = t; i < len; i += SMALL_NT)
+        key[i] = i < n ? key_of(n_sys, off, grid, i, in.a[0][i], in.a[1][i], in.a[2][i],
+                                shift_sys, err) << SMALL_BITS | (unsigned)i
+                       : ~0ull;
+    __syncthreads();
+    for (int k = 2; k <= len; k *= 2)
+        for (int j = k / 2; j > 0; j /= 2) {
+            for (int q = t; q < len / 2; q += SMALL_NT) {
+                const int lo = 2 * q - (q & (j - 1)), hi = lo + j;
+                const unsigned long long a = key[lo], b = key[hi];
+                if ((a > b) == ((lo & k) == 0)) {
+                    key[lo] = b;
+                    key[hi] = a;
+                }
+            }
+            __syncthreads();
+        }
+    // ---- the state in its new order, empty cell tables
+    for (int64_t i = t; i < n; i += SMALL_NT)
+        gather_one(i, (int64_t)(key[i] & (SMALL_N - 1)), in, out, rx, ry, rz, p4, ids, ids_tmp);
+    const int64_t cells = sum->total_cells < max_cells ? sum->total_cells : max_cells;
+    for (int64_t q = t; q < cells; q += SMALL_NT) cs[q] = ce[q] = 0;
+    __syncthreads();
+    // ---- cell tables
+    for (int64_t i = t; i < n; i += SMALL_NT) {
+        if (ids) ids[i] = ids_tmp[i];
+        const unsigned long long k = key[i] >> SMALL_BITS;
+        const bool first = i == 0 || key[i - 1] >> SMALL_BITS != k;
+        const bool last = i == n - 1 || key[i + 1] >> SMALL_BITS != k;
+        if (first || last)
+            cell_ends(n_sys, off, grid, i, out.a[0][i], out.a[1][i], out.a[2][i], first, last,
+                      cs, ce);
+    }
 }
 
 __global__ void k_gather_i32(int64_t n, const int32_t* perm, const int32_t* a,
@@ -745,6 +861,20 @@ __global__ void k_gather_i32(int64_t n, const int32_t* perm, const int32_t* a,
     LP_GATE(gate);
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) b[i] = a[perm[i]];
+}
+
+int system_bits(const lp_ctx* c)
+{
+    int b = 0;
+    while ((1 << b) < c->n_sys) ++b;
+    return b;
+}
+
+// May a captured step re-sort in one block (k_rebuild_small)?
+bool rebuild_is_small(const lp_ctx* c, int dev_bits)
+{
+    return c->n > 0 && c->n <= SMALL_N && c->n_sys <= SMALL_SYS &&
+           3 * dev_bits + system_bits(c) + SMALL_BITS < 64;
 }
 
 // Re-sort + cell tables (+ list): eagerly with one host synchronisation for
@@ -794,10 +924,8 @@ lp_status rebuild(lp_ctx* c, double* const st[7], int32_t* perm_out, int32_t* id
         c->axis_bits = axis_bits = sm.axis_bits;
         c->total_cells = sm.total_cells;
     }
-    int sys_bits = 0;
-    while ((1 << sys_bits) < ns) ++sys_bits;
     const int shift_sys = 3 * axis_bits;
-    const int bits = shift_sys + sys_bits;
+    const int bits = shift_sys + system_bits(c);
 
     unsigned long long* kr = nullptr;
     int32_t* vr = nullptr;
@@ -844,9 +972,23 @@ lp_status cells_build(lp_ctx* c, double* const st[7], int32_t* perm_out)
 }
 
 lp_status cells_build_device(lp_ctx* c, double* const st[7], int32_t* ids,
-                             const int32_t* gate, int bits)
+                             int32_t* gate, int bits, int force)
 {
-    return rebuild(c, st, nullptr, ids, gate, bits);
+    if (!rebuild_is_small(c, bits)) return rebuild(c, st, nullptr, ids, gate, bits);
+    Work& w = c->w;
+    State7 s7;
+    Dest7 d7;
+    for (int a = 0; a < 7; ++a) {
+        s7.a[a] = st[a];
+        d7.a[a] = w.sst[a];
+    }
+    hipLaunchKernelGGL(k_rebuild_small, dim3(1), dim3(SMALL_NT), 0, c->stream, c->n, c->n_sys,
+                       w.off, w.prm, c->cfg.skin, s7, d7, w.bbox, w.grid, w.summary, bits,
+                       w.cells_max, 3 * bits, w.xref[0], w.xref[1], w.xref[2], w.p4, ids,
+                       w.ids_tmp, w.cs, w.ce, w.err, w.cnt, gate, force);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(c, e, "cell build launch");
+    return list_build(c, gate);
 }
 
 lp_status state_copy(lp_ctx* c, double* const st[7], int32_t* perm_out,
@@ -931,7 +1073,8 @@ static void launch_copy_disp(lp_ctx* c, const double* const st[7], Summary* host
                            w.xref[1], w.xref[2], w.p4, w.summary, host);
 }
 
-lp_status rebuild_decision(lp_ctx* c, const double* const st[7], int force, bool first)
+lp_status rebuild_decision(lp_ctx* c, const double* const st[7], int force, bool first,
+                           int bits)
 {
     Work& w = c->w;
     const int64_t n = c->n;
@@ -941,8 +1084,10 @@ lp_status rebuild_decision(lp_ctx* c, const double* const st[7], int force, bool
     // the state copied into the working state (in the current order) with
     // the displacement check; a rebuild then overwrites it
     if (n > 0) launch_copy_disp(c, st, nullptr);
-    hipLaunchKernelGGL(k_decide, dim3(1), dim3(1), 0, c->stream, w.summary, w.gate,
-                       w.cnt, force, w.bbox, c->n_sys);
+    // (k_rebuild_small decides itself)
+    if (!rebuild_is_small(c, bits))
+        hipLaunchKernelGGL(k_decide, dim3(1), dim3(1), 0, c->stream, w.summary, w.gate,
+                           w.cnt, force, w.bbox, c->n_sys);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? LP_OK : hip_fail(c, e, "rebuild decision");
 }

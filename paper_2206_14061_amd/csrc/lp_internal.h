@@ -507,14 +507,15 @@ lp_status state_copy(lp_ctx* c, double* const st[7], int32_t* perm_out,
 // Re-sort + list rebuild entirely on the device, skipped unless *gate;
 // ids (optional) are permuted with the state; `bits` per grid axis.
 lp_status cells_build_device(lp_ctx* c, double* const st[7], int32_t* ids,
-                             const int32_t* gate, int bits);
+                             int32_t* gate, int bits, int force);
 // ids[i] = ids[perm[i]]
 lp_status permute_ids(lp_ctx* c, const int32_t* perm, int32_t* ids);
 // working copy of st in the order perm (sst[new] = st[perm[new]]; perm
 // null: the same order) with its positions' 32-byte records
 lp_status state_gather(lp_ctx* c, const double* const st[7], const int32_t* perm);
 // Device-side rebuild decision into w.gate (no synchronisation).
-lp_status rebuild_decision(lp_ctx* c, const double* const st[7], int force, bool first);
+lp_status rebuild_decision(lp_ctx* c, const double* const st[7], int force, bool first,
+                           int bits);
 // Copies the working copy back into the caller's arrays.
 lp_status state_write_back(lp_ctx* c, double* const out[7]);
 // Largest displacement since the list build in units of the skin: the
