@@ -1524,7 +1524,8 @@ lp_status step_rhs(lp_ctx* c, const double* const st[7])
             run_pass1(c, v, so, fq);
         prof_mark(c, 3, true);
         prof_mark(c, 4, false);
-        if (!own_refits(c, fq))
+        // (the cubic fits queue no refits)
+        if (!own_refits(c, fq) && c->cfg.fit_order != 3)
             hipLaunchKernelGGL(k_pass1_qr, dim3(QR_BLOCKS), dim3(QR_TPB), 0,
                                c->stream, v, so, (const int32_t*)w.redo,
                                (const unsigned int*)w.redo_n, w.cnt);
@@ -1589,7 +1590,7 @@ lp_status step_pass2(lp_ctx* c, const double* const st[7], double dt,
             run_pass2(c, v, o, own);
         prof_mark(c, 5, true);
         prof_mark(c, 6, false);
-        if (!own)
+        if (!own && c->cfg.fit_order != 3)
             hipLaunchKernelGGL(k_pass2_qr, dim3(QR_BLOCKS), dim3(QR_TPB), 0,
                                c->stream, v, (const double*)w.P, (const double*)w.eta,
                                (const double*)w.hand, (const int32_t*)w.redo,
