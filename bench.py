@@ -62,7 +62,8 @@ LIST_ENTRIES = 77.5
 # Algorithmic HBM bytes per particle of the selection kernel: own position
 # (24) and list count (4), the list (4 per entry), every neighbour position
 # once (24), a bucket code per entry (1 per entry), the stencil record (12)
-# and keep mask (32).
+# and keep mask (32): the selection as first built, kept as a fixed
+# yardstick.
 SELECT_BYTES_PER_PARTICLE = 24 + 4 + 4 * LIST_ENTRIES + 24 + LIST_ENTRIES + 12 + 32
 # ... of the pass-2 kernel on a 60-row stencil: own state (56), P, eta and
 # flags (17), record and mask (44), the slot words of the kept rows

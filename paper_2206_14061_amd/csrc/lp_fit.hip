@@ -479,9 +479,12 @@ constexpr int st_threads(int lpp) { return lpp == 1 ? BLOCK : 2 * BLOCK; }
 // (rows_ok = 0).  UNIT: the weights are unit, PERIODIC: some axis is
 // periodic (both known at compile time).
 // skip_rows > 0: particles whose stencils have at most skip_rows rows
-// (ghosts included) are left to the size-class launches.  redo null: the
-// block refits its ill-conditioned particles itself, a wavefront each (else
-// a launch after this one does; idle, it costs a step some 5 us).
+// (ghosts included) are left to the size-class launches.  redo null (on
+// eight lanes only): the block refits its ill-conditioned particles itself, a
+// wavefront each; else a launch after this one does, which costs a step some
+// 5 us when idle, but spreads refits that lie together over the chip (900 of
+// 1,048,576 particles, in the thin top of a graded cloud, took the two fits
+// 130 us longer inside them).
 template <int LPP, bool UNIT, bool PERIODIC>
 __global__ __launch_bounds__(st_threads(LPP), 2) void k_pass1_st(View v, StepOut o,
                                                                 int32_t* redo,
@@ -490,8 +493,9 @@ __global__ __launch_bounds__(st_threads(LPP), 2) void k_pass1_st(View v, StepOut
                                                                 int skip_rows, Counters* cnt)
 {
     constexpr int NT = st_threads(LPP), P = NT / LPP;
+    constexpr bool OWN = LPP > 1;
     __shared__ unsigned int own_n;
-    __shared__ int32_t own_redo[P];
+    __shared__ int32_t own_redo[OWN ? P : 1];
     __shared__ double sx[STAGE_CAP], sy[STAGE_CAP], sz[STAGE_CAP];
     __shared__ double su[STAGE_CAP], sv[STAGE_CAP], sw[STAGE_CAP];
     const BlockPart<P> part(v, rows_ok);
@@ -499,7 +503,7 @@ __global__ __launch_bounds__(st_threads(LPP), 2) void k_pass1_st(View v, StepOut
     const StageUnit& unit = part.unit;
     const int64_t i = part.i0 + threadIdx.x / LPP;
     const int sub = threadIdx.x % LPP;
-    if (threadIdx.x == 0) own_n = 0u;
+    if (OWN && threadIdx.x == 0) own_n = 0u;
     if (unit.S >= 0) stage_pass1<NT>(v, unit, sx, sy, sz, su, sv, sw);
     __syncthreads();
     [&]() {
@@ -553,10 +557,10 @@ __global__ __launch_bounds__(st_threads(LPP), 2) void k_pass1_st(View v, StepOut
     }
 #pragma unroll
     for (int f = 0; f < 3; ++f) halve_squares(B[f]);
-    pass1_solve<LPP>(v, o, g, s, i, M, B, order_rows(v, r, mt), sub, redo ? redo : own_redo,
-                     redo ? redo_n : &own_n, force_qr);
+    pass1_solve<LPP>(v, o, g, s, i, M, B, order_rows(v, r, mt), sub, !OWN || redo ? redo : own_redo,
+                     !OWN || redo ? redo_n : &own_n, force_qr);
     }();
-    if (redo) return;
+    if (!OWN || redo) return;
     __syncthreads();
     const int refits = (int)own_n;
     if (refits == 0) return;
@@ -740,8 +744,9 @@ __global__ __launch_bounds__(st_threads(LPP), 2) void k_pass2_st(
     View v, const double* P, const double* eta, const double* hand, const uint8_t* flags,
     RhsOut o, int rows_ok, int skip_rows, int own_qr)
 {
+    constexpr bool OWN = LPP > 1;
     __shared__ unsigned int own_n;
-    __shared__ int32_t own_redo[st_threads(LPP) / LPP];
+    __shared__ int32_t own_redo[OWN ? st_threads(LPP) / LPP : 1];
     constexpr int NT = st_threads(LPP), PB = NT / LPP;
     __shared__ double sx[STAGE_CAP], sy[STAGE_CAP], sz[STAGE_CAP];
     __shared__ double sP[STAGE_CAP], sE[STAGE_CAP];
@@ -750,14 +755,14 @@ __global__ __launch_bounds__(st_threads(LPP), 2) void k_pass2_st(
     const StageUnit& unit = part.unit;
     const int64_t i = part.i0 + threadIdx.x / LPP;
     const int sub = threadIdx.x % LPP;
-    if (threadIdx.x == 0) own_n = 0u;
+    if (OWN && threadIdx.x == 0) own_n = 0u;
     if (unit.S >= 0) stage_pass2<NT>(v, P, eta, unit, sx, sy, sz, sP, sE);
     __syncthreads();
     [&]() {
     const int64_t n = v.n;
     if (i >= n || !part.mine(threadIdx.x / LPP)) return;
     if (flags[i] & FLAG_QR) {
-        if (own_qr && sub == 0) own_redo[atomicAdd(&own_n, 1u)] = (int32_t)i;
+        if (OWN && own_qr && sub == 0) own_redo[atomicAdd(&own_n, 1u)] = (int32_t)i;
         return;
     }
     const int s = sys_of(v.off, v.n_sys, i);
@@ -824,7 +829,7 @@ __global__ __launch_bounds__(st_threads(LPP), 2) void k_pass2_st(
     load_hand_tail(hand, n, i, Ei, hv);
     finish_rhs(v, prm, i, hv, gP, gE, o);
     }();
-    if (!own_qr) return;
+    if (!OWN || !own_qr) return;
     __syncthreads();
     const int refits = (int)own_n;
     for (int t = threadIdx.x >> 6; t < refits; t += NT / 64)
@@ -1227,10 +1232,11 @@ bool classes_on(const lp_ctx* c)
 }
 
 // The staged fits refit their own ill-conditioned particles: both fits run
-// as one staged launch each (the refits of one fit are those of the other).
+// as one staged launch each on eight lanes (the refits of one fit are those of
+// the other).
 bool own_refits(const lp_ctx* c, int fq)
 {
-    return c->lpp1 == 1 && c->lpp2 == 1 && !classes_on(c) && !fq &&
+    return c->n <= ST_L8_MAX && c->lpp1 == 1 && c->lpp2 == 1 && !classes_on(c) && !fq &&
            c->cfg.precision == LP_FP64 && c->cfg.fit_order == 2;
 }
 

@@ -709,7 +709,8 @@ __global__ void k_mirror_write(int64_t n, int n_sys, const int64_t* off,
 // lists are read coalesced: 11 us (L = 16), 20 (L = 8), 47 (L = 8).  Above
 // that the vector ALU bounds it (L = 4: 1,840 instructions per 16 particles,
 // 98 us of issue at 524,288) once the gathers go to the tile's sources in
-// LDS: 66, 119 and 394 us (76, 136 and 427 from the records).  There the rare
+// LDS: 66, 119 and 394 us (76, 136 and 427 from the records; 71, 131 and 410
+// with the kept rows written for the fits).  There the rare
 // cases take a kernel of their own (k_select_rest, 13 us): with them the
 // four-lane form needs 150 registers and 87 us at 262,144.
 typedef short s16x2 __attribute__((ext_vector_type(2)));

@@ -229,28 +229,6 @@ __device__ __forceinline__ void visit_stencil(const View& v, const GridInfo& g,
     }
 }
 
-// Calls f(src, mirror) for every stencil row of real particle i, in the
-// order of visit_stencil: the real particle the row's point stands for
-// (a mirror's source) and whether it is a mirror.  Reads no positions.
-template <int B = 8, class F>
-__device__ __forceinline__ void visit_sources(const View& v, int64_t i, const Rec& r, F&& f)
-{
-    const int64_t n = v.n;
-    MaskWalk mw(r);
-    int t = 0;
-    for (; t + B <= r.m; t += B) {
-        int32_t e[B];
-#pragma unroll
-        for (int u = 0; u < B; ++u) e[u] = v.vl[vl_at(n, i, mw.pop())];
-#pragma unroll
-        for (int u = 0; u < B; ++u) f(e[u] & ~MBIT, (e[u] & MBIT) != 0);
-    }
-    for (; t < r.m; ++t) {
-        const int32_t e = v.vl[vl_at(n, i, mw.pop())];
-        f(e & ~MBIT, (e & MBIT) != 0);
-    }
-}
-
 // The sources staged for half h of a tile: those of the half, or of the
 // whole tile.  S < 0: not staged; reals: those that are no mirrors.
 struct StageUnit {
