@@ -710,6 +710,7 @@ lp_status lp_step_graph(lp_ctx* c, lp_state* s, int32_t* ids, double dt,
     key.bits = bits;
     key.n = c->n;
     key.n_sys = c->n_sys;
+    key.periodic = c->periodic;
     if (!c->gexec || !(key == c->gkey)) {
         drop_graph(c);
         hipError_t e = hipSuccess;

@@ -382,12 +382,13 @@ struct lp_ctx {
         int32_t nsteps, bits;
         int64_t n;
         int32_t n_sys;
+        bool periodic;          // (kernels are chosen by it)
         bool operator==(const GraphKey& o) const
         {
             for (int a = 0; a < 7; ++a)
                 if (st[a] != o.st[a]) return false;
             return ids == o.ids && dt == o.dt && nsteps == o.nsteps && bits == o.bits &&
-                   n == o.n && n_sys == o.n_sys;
+                   n == o.n && n_sys == o.n_sys && periodic == o.periodic;
         }
     } gkey{};
     std::string err;
