@@ -37,10 +37,13 @@ __global__ void k_bbox_init(unsigned long long* bbox, int n_sys, const int32_t* 
 
 constexpr int BBOX_CHUNK = 8;
 
+// (a NaN bounds nothing: with it in the box of one system, no grid
+// would fit, of any system)
 __device__ void bbox_flush(unsigned long long* bbox, int s, const double* lo,
                            const double* hi)
 {
     for (int a = 0; a < 3; ++a) {
+        if (!(lo[a] == lo[a])) continue;
         atomicMin(&bbox[6 * s + a], ord_enc(lo[a]));
         atomicMax(&bbox[6 * s + 3 + a], ord_enc(hi[a]));
     }
