@@ -275,7 +275,7 @@ __global__ __launch_bounds__(BLOCK) void k_list_cells(
     int64_t n, int n_sys, const GridInfo* __restrict__ grid,
     const double* __restrict__ p4, const int32_t* __restrict__ cs,
     const int32_t* __restrict__ ce, int64_t n_cells, const int64_t* __restrict__ n_cells_dev,
-    int split, int32_t* __restrict__ vl, int32_t* __restrict__ vcnt, ErrWord* err,
+    int split_bits, int32_t* __restrict__ vl, int32_t* __restrict__ vcnt, ErrWord* err,
     const int32_t* gate)
 {
     if (gate && *gate == 0) return;
@@ -286,8 +286,8 @@ __global__ __launch_bounds__(BLOCK) void k_list_cells(
     int32_t* sb = seqb[wv];
     int32_t* so = seqo[wv];
     const int64_t tc = n_cells_dev ? *n_cells_dev : n_cells;
-    const int64_t units = tc * split;
-    const int64_t groups = (units + LC_WAVES - 1) / LC_WAVES;
+    const int64_t units = tc << split_bits;
+    const int64_t step = (int64_t)gridDim.x * LC_WAVES;
     const char* p4b = reinterpret_cast<const char*>(p4);
     const uint32_t cst = (uint32_t)(n * VCHUNK);
     auto load_pos = [&](int32_t j, double& qx, double& qy, double& qz) {
@@ -297,17 +297,26 @@ __global__ __launch_bounds__(BLOCK) void k_list_cells(
         qy = xy.y;
         qz = r[2];
     };
-    for (int64_t grp = xcd_block(blockIdx.x, gridDim.x); grp < groups; grp += gridDim.x) {
-        const int64_t unit = grp * LC_WAVES + wv;
-        if (unit >= units) break;
-        // this wavefront's share of a cell's particles
-        const int64_t cell = unit / split;
-        const int part = (int)(unit - cell * split);
-        const int32_t first = cs[cell], all = ce[cell] - first;
-        const int share = (all + split - 1) / split;
-        const int32_t cb = first + part * share;
-        const int32_t cend = first + ((part + 1) * share < all ? (part + 1) * share : all);
-        if (cend <= cb) continue;
+    // a unit is one share of a cell's particles; the wavefront looks at its
+    // next 64 units at once, one per lane, and takes those that hold particles
+    // (in a sparse state nearly none does: one unit after another took 436 us
+    // at 131,072 particles in 1.1 M cells and 394 at 33,000 in 2.2 M)
+    for (int64_t u0 = xcd_block(blockIdx.x, gridDim.x) * LC_WAVES + wv; u0 < units;
+         u0 += 64 * step) {
+        int32_t mine = 0, mine_end = 0;
+        if (u0 + lane * step < units) {
+            const int64_t unit = u0 + lane * step, cell = unit >> split_bits;
+            const int part = (int)(unit & ((1 << split_bits) - 1));
+            const int32_t first = cs[cell], all = ce[cell] - first;
+            const int share = (all + (1 << split_bits) - 1) >> split_bits;
+            mine = first + part * share;
+            mine_end = first + ((part + 1) * share < all ? (part + 1) * share : all);
+        }
+        for (uint64_t left = __ballot(mine_end > mine); left; left &= left - 1) {
+        const int at = __builtin_ctzll(left);
+        const int64_t cell = (u0 + at * step) >> split_bits;
+        const int32_t cb = __builtin_amdgcn_readlane(mine, at);
+        const int32_t cend = __builtin_amdgcn_readlane(mine_end, at);
         const GridInfo& g = grid[sys_of_cell(grid, n_sys, cell)];
         const int loc = (int)(cell - g.cell_base);
         const int cx = loc % g.nx, cy = (loc / g.nx) % g.ny, cz = loc / (g.nx * g.ny);
@@ -413,6 +422,7 @@ __global__ __launch_bounds__(BLOCK) void k_list_cells(
             if (reseq && q0 + 64 < cend) tot = cell_seq(g, cs, ce, cx, cy, cz, sb, so);
         }
         wave_sync();
+        }
     }
 }
 
@@ -1824,17 +1834,18 @@ lp_status list_build(lp_ctx* c, const int32_t* gate)
         // with 1, 2, 4 and 8, us: 4,096 particles 52, 32, 22, 17; 12,075 53,
         // 33, 23, 22; 32,768 54, 41, 39, 43; 65,536 63, 58, 59, 66; 131,072
         // 95, 87, 97, 112; 262,144 150, 149, 167, 279.
-        const int split = n <= 16384 ? 8 : n <= 65536 ? 4 : n <= 262144 ? 2 : 1;
-        const int64_t groups = (tc * split + LC_WAVES - 1) / LC_WAVES;
-        const int64_t cap = gate ? 2 * split * (int64_t)blocks_for(n) : (int64_t)LC_MAX_BLOCKS;
+        const int split_bits = n <= 16384 ? 3 : n <= 65536 ? 2 : n <= 262144 ? 1 : 0;
+        const int64_t groups = ((tc << split_bits) + LC_WAVES - 1) / LC_WAVES;
+        const int64_t cap =
+            gate ? (2 * (int64_t)blocks_for(n)) << split_bits : (int64_t)LC_MAX_BLOCKS;
         const unsigned nb = (unsigned)std::max<int64_t>(1, std::min(groups, cap));
         if (c->periodic)
             hipLaunchKernelGGL(k_list_cells<true>, dim3(nb), dim3(BLOCK), 0, c->stream, n,
-                               c->n_sys, w.grid, w.p4, w.cs, w.ce, tc, tdev, split, w.vl,
+                               c->n_sys, w.grid, w.p4, w.cs, w.ce, tc, tdev, split_bits, w.vl,
                                w.vcnt, w.err, gate);
         else
             hipLaunchKernelGGL(k_list_cells<false>, dim3(nb), dim3(BLOCK), 0, c->stream, n,
-                               c->n_sys, w.grid, w.p4, w.cs, w.ce, tc, tdev, split, w.vl,
+                               c->n_sys, w.grid, w.p4, w.cs, w.ce, tc, tdev, split_bits, w.vl,
                                w.vcnt, w.err, gate);
     }
     hipError_t e = hipGetLastError();
