@@ -97,6 +97,7 @@ void free_work(Work& w)
     f(w.cls_idx); f(w.cls_cnt);
     if (w.h_summary) hipHostFree(w.h_summary);
     w.h_summary = w.pinned = nullptr;
+    w.refitted = nullptr;
     w.n_max = w.cells_max = 0;
 }
 
@@ -304,8 +305,13 @@ lp_status lp_reserve(lp_ctx* c, int64_t n_max, int64_t cells_max)
     work_layout(w, n_max, cells_max, mm, SYS_CAP, false, [&](auto*& p, int64_t cnt) {
         if (e == hipSuccess) e = alloc(p, cnt);
     });
-    if (e == hipSuccess) e = hipHostMalloc((void**)&w.h_summary, sizeof(Summary));
-    w.pinned = w.h_summary;
+    HostWords* words = nullptr;
+    if (e == hipSuccess) e = hipHostMalloc((void**)&words, sizeof(HostWords));
+    if (words) {
+        words->refitted = 0u;
+        w.h_summary = w.pinned = &words->summary;
+        w.refitted = &words->refitted;
+    }
     if (e == hipSuccess) e = hipMemset(w.err, 0, sizeof(ErrWord));
     if (e == hipSuccess) e = hipMemset(w.cnt, 0, sizeof(Counters));
     if (e == hipSuccess) e = hipMemset(w.summary, 0, sizeof(Summary));
@@ -399,6 +405,7 @@ lp_status lp_set_systems(lp_ctx* c, int32_t n_sys, const int64_t* offsets,
                            hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "lp_set_systems upload");
+    if (c->w.refitted) *c->w.refitted = 0u;
     return LP_OK;
 }
 
@@ -711,6 +718,7 @@ lp_status lp_step_graph(lp_ctx* c, lp_state* s, int32_t* ids, double dt,
     key.n = c->n;
     key.n_sys = c->n_sys;
     key.periodic = c->periodic;
+    key.own = step_own_refits(c);
     if (!c->gexec || !(key == c->gkey)) {
         drop_graph(c);
         hipError_t e = hipSuccess;

@@ -481,16 +481,18 @@ constexpr int st_threads(int lpp) { return lpp == 1 ? BLOCK : 2 * BLOCK; }
 // skip_rows > 0: particles whose stencils have at most skip_rows rows
 // (ghosts included) are left to the size-class launches.  redo null (on
 // eight lanes only): the block refits its ill-conditioned particles itself, a
-// wavefront each; else a launch after this one does, which costs a step some
-// 5 us when idle, but spreads refits that lie together over the chip (900 of
+// wavefront each; else a launch after this one does, which costs a step
+// 3.5 us when idle, but spreads refits that lie together over the chip (900 of
 // 1,048,576 particles, in the thin top of a graded cloud, took the two fits
-// 130 us longer inside them).
+// 130 us longer inside them).  A block that refits says so in *refitted, and
+// the launches take over (own_refits).
 template <int LPP, bool UNIT, bool PERIODIC>
 __global__ __launch_bounds__(st_threads(LPP), 2) void k_pass1_st(View v, StepOut o,
                                                                 int32_t* redo,
                                                                 unsigned int* redo_n,
                                                                 int force_qr, int rows_ok,
-                                                                int skip_rows, Counters* cnt)
+                                                                int skip_rows, Counters* cnt,
+                                                                uint32_t* refitted)
 {
     constexpr int NT = st_threads(LPP), P = NT / LPP;
     constexpr bool OWN = LPP > 1;
@@ -564,7 +566,10 @@ __global__ __launch_bounds__(st_threads(LPP), 2) void k_pass1_st(View v, StepOut
     __syncthreads();
     const int refits = (int)own_n;
     if (refits == 0) return;
-    if (threadIdx.x == 0) atomicAdd(&cnt->qr_refits, (unsigned long long)refits);
+    if (threadIdx.x == 0) {
+        atomicAdd(&cnt->qr_refits, (unsigned long long)refits);
+        __hip_atomic_store(refitted, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
     for (int t = threadIdx.x >> 6; t < refits; t += NT / 64) pass1_refit(v, o, own_redo[t]);
 }
 
@@ -1233,11 +1238,17 @@ bool classes_on(const lp_ctx* c)
 
 // The staged fits refit their own ill-conditioned particles: both fits run
 // as one staged launch each on eight lanes (the refits of one fit are those of
-// the other).
+// the other), and no fit since lp_set_systems has met any: refits take the
+// wavefronts of one block, up to eight at a time, longer than the launch takes
+// spread over the chip.  Measured, us per step in the fits and by the
+// launches: no refits, 9,600 particles, 52.6 and 56.4; 19 of 9,664 115 and 103;
+// 316 of 10,000 in a spray, up to 16 in a block, 163 and 97.  The refits are the same either way,
+// bit for bit.
 bool own_refits(const lp_ctx* c, int fq)
 {
     return c->n <= ST_L8_MAX && c->lpp1 == 1 && c->lpp2 == 1 && !classes_on(c) && !fq &&
-           c->cfg.precision == LP_FP64 && c->cfg.fit_order == 2;
+           c->cfg.precision == LP_FP64 && c->cfg.fit_order == 2 && c->w.refitted &&
+           __atomic_load_n(c->w.refitted, __ATOMIC_RELAXED) == 0u;
 }
 
 template <int LPP>
@@ -1250,7 +1261,7 @@ void launch_pass1_st(lp_ctx* c, const View& v, const StepOut& so, int fq, int sk
         hipLaunchKernelGGL((k_pass1_st<LPP, unit.value, per.value>),
                            dim3(BlockPart<NT / LPP>::blocks(c->n)), dim3(NT), 0, c->stream, v, so,
                            own ? nullptr : w.redo, own ? nullptr : w.redo_n, fq,
-                           staged_rows(c), skip_rows, w.cnt);
+                           staged_rows(c), skip_rows, w.cnt, w.refitted);
     });
 }
 
@@ -1399,7 +1410,7 @@ void run_pass1(lp_ctx* c, const View& v, const StepOut& so, int fq)
         classify(c, v);
         for (int k = 0; k < NCLASS; ++k) launch_pass1_class(c, k, c->cls_lpp1[k], v, so, fq);
     } else {
-        launch_pass1(c, c->lpp1, v, so, fq, own_refits(c, fq));
+        launch_pass1(c, c->lpp1, v, so, fq, c->own);
     }
 }
 
@@ -1506,6 +1517,11 @@ lp_status rhs_from_coef(lp_ctx* c, const double* const st[7],
     return LP_OK;
 }
 
+bool step_own_refits(const lp_ctx* c)
+{
+    return own_refits(c, (c->cfg.debug_flags & LP_DEBUG_QR_FIT) ? 1 : 0);
+}
+
 lp_status step_rhs(lp_ctx* c, const double* const st[7])
 {
     Work& w = c->w;
@@ -1513,6 +1529,8 @@ lp_status step_rhs(lp_ctx* c, const double* const st[7])
     View v = make_view(c, st);
     StepOut so{w.P, w.eta, w.hand, w.flags, nullptr, nullptr};
     const int fq = (c->cfg.debug_flags & LP_DEBUG_QR_FIT) ? 1 : 0;
+    // (once for both fits of these stencils)
+    c->own = own_refits(c, fq);
     redo_reset(c);
     if (n > 0) {
         prof_mark(c, 3, false);
@@ -1531,7 +1549,7 @@ lp_status step_rhs(lp_ctx* c, const double* const st[7])
         prof_mark(c, 3, true);
         prof_mark(c, 4, false);
         // (the cubic fits queue no refits)
-        if (!own_refits(c, fq) && c->cfg.fit_order != 3)
+        if (!c->own && c->cfg.fit_order != 3)
             hipLaunchKernelGGL(k_pass1_qr, dim3(QR_BLOCKS), dim3(QR_TPB), 0,
                                c->stream, v, so, (const int32_t*)w.redo,
                                (const unsigned int*)w.redo_n, w.cnt);
@@ -1550,7 +1568,7 @@ lp_status step_pass1_coef(lp_ctx* c, const double* const st[7])
     StepOut so{w.P, w.eta, w.hand, w.flags, nullptr, w.coefu};
     // float64 whatever the steps' precision: refits of its own only where the
     // step's would be
-    const bool own = own_refits(c, 0);
+    const bool own = c->own = own_refits(c, 0);
     redo_reset(c);
     if (n > 0) {
         // the pass-2 fit of these stencils may run by size class
@@ -1575,9 +1593,8 @@ lp_status step_pass2(lp_ctx* c, const double* const st[7], double dt,
     RhsOut o = rhs_out(c, acc, dVdt, nullptr);
     for (int a = 0; a < 7; ++a) o.out[a] = out ? out[a] : nullptr;
     o.dt = dt;
-    // as pass 1 of these stencils did (fp64: step_pass1_coef)
-    const bool own =
-        own_refits(c, !fp64 && (c->cfg.debug_flags & LP_DEBUG_QR_FIT) ? 1 : 0);
+    // as pass 1 of these stencils did
+    const bool own = c->own;
     if (n > 0) {
         prof_mark(c, 5, false);
         if (c->cfg.fit_order == 3)

@@ -145,6 +145,12 @@ struct Summary {
     uint32_t done, pad;         // blocks of a displacement check that have ended
 };
 
+// What the device writes into pinned memory.
+struct HostWords {
+    Summary summary;
+    uint32_t refitted, pad;
+};
+
 // Device error word.
 struct ErrWord {
     int32_t code;
@@ -217,6 +223,9 @@ struct Work {
     Summary* summary = nullptr;
     Summary* h_summary = nullptr;         // host copy
     Summary* pinned = nullptr;            // the same where the device can write it
+    // pinned word: set by a fit that refitted particles itself (null: no pinned
+    // memory)
+    uint32_t* refitted = nullptr;
     ErrWord* err = nullptr;
     Counters* cnt = nullptr;
     // sort
@@ -349,6 +358,7 @@ struct lp_ctx {
     // lanes per particle of each class in each fit, and what the last
     // autotune measured (class counts, best milliseconds)
     bool classes = false;
+    bool own = false;           // the last pass-1 fit refitted its own particles
     // (lanes 0 on the largest class: the LDS-staged one-lane tile kernel)
     int cls_lpp1[lp::NCLASS] = {1, 2, 4}, cls_lpp2[lp::NCLASS] = {1, 2, 4};
     int64_t cls_count[lp::NCLASS] = {0, 0, 0};
@@ -382,13 +392,13 @@ struct lp_ctx {
         int32_t nsteps, bits;
         int64_t n;
         int32_t n_sys;
-        bool periodic;          // (kernels are chosen by it)
+        bool periodic, own;     // (kernels are chosen by them)
         bool operator==(const GraphKey& o) const
         {
             for (int a = 0; a < 7; ++a)
                 if (st[a] != o.st[a]) return false;
             return ids == o.ids && dt == o.dt && nsteps == o.nsteps && bits == o.bits &&
-                   n == o.n && n_sys == o.n_sys && periodic == o.periodic;
+                   n == o.n && n_sys == o.n_sys && periodic == o.periodic && own == o.own;
         }
     } gkey{};
     std::string err;
@@ -552,6 +562,8 @@ lp_status rhs_from_coef(lp_ctx* c, const double* const st[7],
                         const double* coef_u, double* dVdt, double* acc,
                         double* diag, double* grad, uint8_t* flags);
 lp_status step_rhs(lp_ctx* c, const double* const st[7]);
+// Do the fits of a step refit their ill-conditioned particles themselves?
+bool step_own_refits(const lp_ctx* c);
 // times each lanes-per-particle variant of the two fit kernels on the
 // stencils of st and keeps the fastest (choice: host int32[2], optional)
 lp_status autotune_fits(lp_ctx* c, const double* const st[7], int32_t* choice);
