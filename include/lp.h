@@ -344,8 +344,10 @@ lp_status lp_fit_plan(lp_ctx* ctx, int32_t* plan, double* ms);
  * list (same rule as lp_step) and synchronises nothing.  The sequence is
  * captured on the first call (on a stream the library creates) and
  * replayed on the context's stream by later calls with the same state
- * arrays, ids, dt and nsteps (any change recaptures; lp_reserve drops the
- * capture).  ids (device int32[n], optional) are permuted along with the
+ * arrays, ids, dt and nsteps.  Any change of these recaptures, and so does
+ * once the first replay that met stencils to refit (up to 16,384 particles);
+ * the call then waits for the replays before it.  lp_reserve drops the
+ * capture.  ids (device int32[n], optional) are permuted along with the
  * state at every re-sort, so they track particle identity.  If the
  * context has no neighbour list, the state (and ids) are first re-sorted
  * in place as by lp_build_cells.  Between re-sorts the grid keeps the bit

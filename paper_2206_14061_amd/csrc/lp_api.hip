@@ -134,9 +134,13 @@ void state_arrays(const lp_state* s, double* st[7])
     st[3] = s->u; st[4] = s->v; st[5] = s->w; st[6] = s->V;
 }
 
+// (a replay may still be running)
 void drop_graph(lp_ctx* c)
 {
-    if (c->gexec) hipGraphExecDestroy(c->gexec);
+    if (c->gexec) {
+        hipStreamSynchronize(c->stream);
+        hipGraphExecDestroy(c->gexec);
+    }
     if (c->graph) hipGraphDestroy(c->graph);
     c->gexec = nullptr;
     c->graph = nullptr;
