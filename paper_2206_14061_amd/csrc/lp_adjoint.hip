@@ -217,7 +217,7 @@ __device__ __forceinline__ void adj_rows2(const View& v, const GridInfo& g,
                 body(a, w, RowPt{true, false, -1}, 0.0, 0.0);
             });
     } else {
-        for_rows_sub<LPP>(v, g, i, load_rec(v, i), sub,
+        for_rows_sub<LPP, FIT_BATCH, 1>(v, g, i, load_rec(v, i), sub,
                           [&](const double* a, double w, const Pt* p) {
             double Pj, Ej;
             pass2_values(v, B.P, B.eta, p, prm, Pj, Ej);
@@ -512,7 +512,7 @@ __global__ __launch_bounds__(BLOCK * LPP, 1) void k_adj_pass1(View v, AdjBufs B,
                         body(a, w, RowPt{true, false, -1}, 0.0, 0.0, 0.0);
                     });
             } else {
-                for_rows_sub<LPP>(v, g, i, load_rec(v, i), sub,
+                for_rows_sub<LPP, FIT_BATCH, 1>(v, g, i, load_rec(v, i), sub,
                                   [&](const double* a, double w, const Pt* p) {
                     if (!p) {
                         body(a, w, RowPt{true, false, -1}, 0.0, 0.0, 0.0);

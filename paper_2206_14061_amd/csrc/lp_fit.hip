@@ -408,7 +408,7 @@ __global__ __launch_bounds__(BLOCK, 2) void k_pass1(View v, StepOut o,
     for (int q = 0; q < 31; ++q) M[q] = 0.0;
 #pragma unroll
     for (int q = 0; q < 9; ++q) B[0][q] = B[1][q] = B[2][q] = 0.0;
-    int mt = for_rows_sub<LPP>(v, g, i, r, sub, [&](const double* a, double w,
+    int mt = for_rows_sub<LPP, FIT_BATCH, 1>(v, g, i, r, sub, [&](const double* a, double w,
                                                     const Pt* p) {
         moments_add(M, a, w);
         if (!p) return;   // ghosts carry u_i (b = 0)
@@ -682,7 +682,7 @@ __global__ __launch_bounds__(BLOCK) void k_pass2(View v, const double* P,
     double yP[9], yE[9];
 #pragma unroll
     for (int q = 0; q < 9; ++q) yP[q] = yE[q] = 0.0;
-    for_rows_sub<LPP, PASS2_BATCH>(v, g, i, r, sub, [&](const double* a, double w,
+    for_rows_sub<LPP, PASS2_BATCH, 1>(v, g, i, r, sub, [&](const double* a, double w,
                                                          const Pt* p) {
         double Pj, Ej;
         pass2_values(v, P, eta, p, prm, Pj, Ej);

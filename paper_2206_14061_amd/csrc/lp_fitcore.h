@@ -299,13 +299,13 @@ __device__ __forceinline__ void for_rows_staged(const View& v, const GridInfo& g
 // for_rows with the rows spread over LPP lanes (stencil rows as in
 // visit_stencil_sub, ghost o to lane o mod LPP; B: rows loaded together
 // with one lane per particle); returns this lane's rows.
-template <int LPP, int B = FIT_BATCH, class F>
+template <int LPP, int B = FIT_BATCH, int CH = 4, class F>
 __device__ __forceinline__ int for_rows_sub(const View& v, const GridInfo& g, int64_t i,
                                             const Rec& r, int sub, F&& f)
 {
     if (LPP == 1) return for_rows<B>(v, g, i, r, f);
     int m = 0;
-    visit_stencil_sub<LPP>(v, g, i, r, sub, [&](const Pt& p, double dx, double dy,
+    visit_stencil_sub<LPP, CH>(v, g, i, r, sub, [&](const Pt& p, double dx, double dy,
                                                 double dz) {
         double a[9];
         const double w = point_row(v, g, dx, dy, dz, a);

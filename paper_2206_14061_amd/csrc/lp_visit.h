@@ -336,10 +336,14 @@ __device__ __forceinline__ void visit_staged(const View& v, const Seen& s, int64
             row(((u & 2 ? w.y : w.x) >> (16 * (u & 1))) & 0xFFFFu);
 }
 
-// visit_stencil with the rows of particle i spread over LPP adjacent
-// lanes as in visit_staged: lane `sub` takes the chunks of four kept rows
-// sub, sub + LPP, ...
-template <int LPP, class F>
+// visit_stencil with the rows of particle i spread over LPP adjacent lanes:
+// lane `sub` takes the chunks of CH kept rows sub, sub + LPP, ...  CH = 4 are
+// the rows of visit_staged.  CH = 1 is faster where every particle gathers:
+// adjacent lanes read and add to adjacent sources, and a row at a time needs
+// fewer registers (us at 400,000 particles, chunks of four and of one: the
+// reverse kernels 2,260 and 2,190, 2,010 and 1,930; a step with two lanes in the
+// fits 554, 522, with four 639, 579).
+template <int LPP, int CH, class F>
 __device__ __forceinline__ void visit_stencil_sub(const View& v, const GridInfo& g,
                                                   int64_t i, const Rec& r, int sub, F&& f)
 {
@@ -348,18 +352,27 @@ __device__ __forceinline__ void visit_stencil_sub(const View& v, const GridInfo&
         return;
     }
     const int64_t n = v.n;
+    MaskWalk mw(r);
+    for (int t = 0; t < CH * sub && t < r.m; ++t) mw.pop();
+    if constexpr (CH == 1) {
+        const double xi = v.x[i], yi = v.y[i], zi = v.z[i];
+        for (int t = sub; t < r.m; t += LPP) {
+            const Pt p = list_point(v, g, v.vl[vl_at(n, i, mw.pop())], xi, yi);
+            f(p, dsub(p.x, xi), dsub(p.y, yi), dsub(p.z, zi));
+            for (int u = 1; u < LPP && t + u < r.m; ++u) mw.pop();
+        }
+        return;
+    }
     const Seen s = seen_from(v, g, i);
     const double xi = s.xi, yi = s.yi, zi = s.zi;
-    MaskWalk mw(r);
-    for (int t = 0; t < 4 * sub && t < r.m; ++t) mw.pop();
-    for (int t = 4 * sub; t < r.m; t += 4 * LPP) {
-        for (int u = t; u < t + 4 && u < r.m; ++u) {
+    for (int t = CH * sub; t < r.m; t += CH * LPP) {
+        for (int u = t; u < t + CH && u < r.m; ++u) {
             const int32_t e[1] = {v.vl[vl_at(n, i, mw.pop())]};
             Pt p[1];
             gather_list(v, s, e, p);
             f(p[0], dsub(p[0].x, xi), dsub(p[0].y, yi), dsub(p[0].z, zi));
         }
-        for (int u = t + 4; u < t + 4 * LPP && u < r.m; ++u) mw.pop();
+        for (int u = t + CH; u < t + CH * LPP && u < r.m; ++u) mw.pop();
     }
 }
 
