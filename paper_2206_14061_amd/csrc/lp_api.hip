@@ -958,7 +958,8 @@ lp_status lp_stats(lp_ctx* c, int64_t* out8)
         if (e != hipSuccess) return hip_fail(c, e, "lp_stats");
         int64_t off = 0;
         // (staged in halves, or not at all)
-        for (int64_t t = 0; t < tiles; ++t) off += tc[2 * t + 1] != TILE_WHOLE ? 1 : 0;
+        for (int64_t t = 0; t < tiles; ++t)
+            off += tc[2 * t] < 0 || tc[2 * t + 1] != TILE_WHOLE ? 1 : 0;
         out8[6] = off;
         out8[7] = tiles;
     }

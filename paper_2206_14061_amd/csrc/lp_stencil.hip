@@ -1693,7 +1693,7 @@ __global__ __launch_bounds__(MAP_NT, 8) void k_tile_map(
     __syncthreads();
     const int G = ng;
     if (full) {
-        if (t < 2) tile_cnt[2 * tile + t] = -1;
+        if (t < 2) tile_cnt[2 * tile + t] = t ? TILE_WHOLE : -1;
         return;
     }
     // thread t takes the granules t, t + MAP_NT, ... of the list: their marks
@@ -1751,7 +1751,9 @@ __global__ __launch_bounds__(MAP_NT, 8) void k_tile_map(
     const int S = (int)total;
     if (t == 0) reals = S;
     if (S > STAGE_CAP) {
-        if (t == 0 && unit >= 0) tile_cnt[2 * tile + unit] = -1;
+        // (neither half staged: one unit, which gathers from memory)
+        if (t == 0 && unit >= 0)
+            tile_cnt[2 * tile + unit] = unit && tile_cnt[2 * tile] < 0 ? TILE_WHOLE : -1;
         continue;                          // (the same in every thread)
     }
     __syncthreads();
