@@ -692,13 +692,13 @@ __global__ __launch_bounds__(BLOCK * LPP, 1) void k_adj_pass1(View v, AdjBufs B,
         __syncthreads();
         acc_flush<NT>(B, v.n, acc, unit.src, unit.S);
     }
-    // parameter cotangents: one atomic per block when the block lies in
+    // parameter cotangents: one atomic per block when its particles lie in
     // one system, else one per thread (the staged rows are dead once every
     // thread has passed the first barrier)
     double (*red)[NT] = reinterpret_cast<double (*)[NT]>(lds);
     sys_t[t] = s;
     __syncthreads();
-    const int s0 = sys_t[0];
+    const int s0 = sys_t[part.h * HALF * LPP];   // (its first particle's)
     const bool uniform = __syncthreads_and((s == s0 || s < 0) ? 1 : 0) != 0 && s0 >= 0;
     if (uniform) {
         red[0][t] = th[0];
