@@ -783,6 +783,12 @@ __global__ void k_decide(Summary* sum, int32_t* gate, Counters* cnt, int force,
 // The launches of k_decide to k_cell_bounds (twelve) run in every captured
 // step, nearly always to find that nothing is to be done: a step of a periodic
 // layer of some 6,000 particles took 72 us with them and takes 53 with this.
+// Where a re-sort is due it costs one block more the larger the state: us per
+// step with one due in every step (skin 0) and by the launches, 1,000
+// particles 99 and 124, 4,096 150 and 147, 6,156 198 and 150, 8,000 211 and
+// 155; 6,633 in 16 systems 231 and 294 (one thread lays out the grids either
+// way); without one due 46 and 65, 47 and 65, 49 and 68, 51 and 69, 58 and 82.
+// Empty cells cost little: 1,000 particles in 729,000 cells 399 and 390.
 constexpr int SMALL_NT = 1024, SMALL_N = 8192, SMALL_SYS = 64, SMALL_BITS = 13;
 static_assert(1 << SMALL_BITS == SMALL_N, "a particle in the low bits");
 
