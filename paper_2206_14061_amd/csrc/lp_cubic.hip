@@ -18,6 +18,7 @@
 #include <type_traits>
 
 #include "lp_finish.h"
+#include "lp_rowsum.h"
 
 namespace lp {
 
@@ -55,26 +56,23 @@ __device__ __forceinline__ double group_sum(double x)
     return x;
 }
 
-// Four sums over the group at once, times s: in the quads each lane keeps one
-// of the four (halving what is exchanged), which rotations by 4 and 8 lanes
-// then add up over the quads, and every lane reads all four from its quad.
+// Four sums over the group at once, times s, the same values in every lane.
 // (36 instructions with the products; four group sums and theirs take 52.  The
 // two fits of 65,536 particles took 334 and 309 us by single sums, 302 and 281
 // under the same profiler with these.)
+struct RowLane {
+    int sl;
+    __device__ __forceinline__ double pick(int bit, double a, double b) const
+    {
+        return sl & bit ? a : b;
+    }
+    template <int CTRL>
+    __device__ __forceinline__ double move(double x) const { return dpp_f64<CTRL>(x); }
+};
 __device__ __forceinline__ void group_sum4(int sl, const double (&d)[4], double s,
                                            double (&f)[4])
 {
-    const bool o1 = sl & 1, o2 = sl & 2;
-    const double e0 = (o1 ? d[1] : d[0]) + dpp_f64<0xB1>(o1 ? d[0] : d[1]);
-    const double e1 = (o1 ? d[3] : d[2]) + dpp_f64<0xB1>(o1 ? d[2] : d[3]);
-    double e = (o2 ? e1 : e0) + dpp_f64<0x4E>(o2 ? e0 : e1);
-    e += dpp_f64<0x124>(e);   // row_ror:4
-    e += dpp_f64<0x128>(e);   // row_ror:8
-    e *= s;
-    f[0] = dpp_f64<0x00>(e);
-    f[1] = dpp_f64<0x55>(e);
-    f[2] = dpp_f64<0xAA>(e);
-    f[3] = dpp_f64<0xFF>(e);
+    row_sum4(RowLane{sl}, d, s, f);
 }
 
 // f(integral_constant<int, K>) for K = B .. E-1, in order
