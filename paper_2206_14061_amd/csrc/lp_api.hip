@@ -487,7 +487,7 @@ lp_status lp_rheology_rhs(lp_ctx* c, const lp_state* s, const double* coef_u,
 
 // The displacement check of a step on the current list, with the state
 // copied into the working state: its result comes back to the host while
-// the stream already runs the mirrors and the histogram selection on the
+// the stream already runs the mirrors and the selection on the
 // current list (when its tile map is current), which a rebuild then
 // repeats.  rebuild: some particle moved `limit` skins or more; ahead: the
 // selection was enqueued (the step then adds only its tail).
@@ -916,8 +916,9 @@ lp_status lp_sync_status(lp_ctx* c, int64_t* index)
         return LP_E_STATE;
     }
     if (ew.code & ERR_CAPACITY) {
-        c->err = "device capacity exceeded (too many candidates for the sorted "
-                 "stencil path) at particle " + std::to_string(ew.index);
+        c->err = "device capacity exceeded (more neighbour-list entries than a "
+                 "particle holds, or more cells than reserved) at particle " +
+                 std::to_string(ew.index);
         return LP_E_CAPACITY;
     }
     c->err = "non-finite state at particle " + std::to_string(ew.index);

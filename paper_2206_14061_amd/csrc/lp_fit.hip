@@ -1241,9 +1241,9 @@ bool classes_on(const lp_ctx* c)
 // the other), and no fit since lp_set_systems has met any: refits take the
 // wavefronts of one block, up to eight at a time, longer than the launch takes
 // spread over the chip.  Measured, us per step in the fits and by the
-// launches: no refits, 9,600 particles, 52.6 and 56.4; 19 of 9,664 115 and 103;
-// 316 of 10,000 in a spray, up to 16 in a block, 163 and 97.  The refits are the same either way,
-// bit for bit.
+// launches: no refits, 9,600 particles, 52.6 and 56.4; 19 of 9,664 115 and
+// 103; 316 of 10,000 in a spray, up to 16 in a block, 163 and 97.  The refits
+// are the same either way, bit for bit.
 bool own_refits(const lp_ctx* c, int fq)
 {
     return c->n <= ST_L8_MAX && c->lpp1 == 1 && c->lpp2 == 1 && !classes_on(c) && !fq &&

@@ -243,7 +243,8 @@ struct Work {
     int32_t* bsum = nullptr;              // scan block sums
     // cell tables
     int32_t *cs = nullptr, *ce = nullptr;
-    // neighbour list, records, sorted-path stencils
+    // neighbour list, its tile map, stencil records and keep masks, particles
+    // left to the selection's second kernel
     int32_t* vl = nullptr;
     int32_t* vcnt = nullptr;
     int32_t* tile_src = nullptr;          // 2 x tiles x STAGE_CAP
@@ -314,7 +315,7 @@ constexpr void work_layout(Work& w, int64_t n_max, int64_t cells_max, int mm,
     A(w.vs, (int64_t)VCAP * n_max);
     A(w.ks, (int64_t)row_cap(mm) * n_max);
     A(w.kmask, (int64_t)MASK_WORDS * n_max);
-    A(w.rec, (int64_t)REC_FIELDS * n_max); 
+    A(w.rec, (int64_t)REC_FIELDS * n_max);
     A(w.hard, n_max); A(w.hard_n, 1);
     A(w.redo, n_max); A(w.redo_n, 1);
     A(w.P, n_max); A(w.eta, n_max); A(w.hand, (int64_t)HAND * n_max);
@@ -359,7 +360,7 @@ struct lp_ctx {
     // autotune measured (class counts, best milliseconds)
     bool classes = false;
     bool own = false;           // the last pass-1 fit refitted its own particles
-    // (lanes 0 on the largest class: the LDS-staged one-lane tile kernel)
+    // (lanes 0 on the largest class: the LDS-staged tile kernel)
     int cls_lpp1[lp::NCLASS] = {1, 2, 4}, cls_lpp2[lp::NCLASS] = {1, 2, 4};
     int64_t cls_count[lp::NCLASS] = {0, 0, 0};
     double tune_ms[8] = {0};
@@ -539,7 +540,7 @@ lp_status list_check_wait(lp_ctx* c, double* ratio);
 // Mirror ids of the current state, stencil records.
 // packed: the positions' 32-byte records (p4) already hold st's positions
 // (written by the step's state copy or re-sort).  part: STENCIL_ALL, or
-// STENCIL_HEAD (mirrors and the histogram selection, which a step enqueues
+// STENCIL_HEAD (mirrors and the selection, which a step enqueues
 // before it knows whether the list must be rebuilt) and then STENCIL_TAIL
 // (the particles the selection handed over to its second kernel).
 enum { STENCIL_ALL = 0, STENCIL_HEAD = 1, STENCIL_TAIL = 2 };

@@ -15,11 +15,12 @@
 // Stencil selection (nearest candidate of each octant, then the nearest
 // others by key (r^2, id), m_max in all), a few adjacent lanes per particle,
 // without storing or sorting the candidates: every list entry's exact test
-// leaves a 16-bit key (r^2 in units of R^2/65534; monotone) and its octant
+// leaves a 15-bit key (r^2 in units of R^2/32766; monotone) and its octant
 // in the lanes' registers, and the cut is the key value below which exactly
 // m_max candidates lie, found by counting (k_select).  The result is a keep
-// bitmask over the list entries (plus row count and ghost mask); the fits
-// walk its set bits.
+// bitmask over the list entries (plus row count and ghost mask), which the
+// exports, the refits and the fits that gather walk, and, where the tile is
+// staged, the kept rows' slot words in list order, which the other fits read.
 #include <algorithm>
 #include <type_traits>
 
@@ -716,7 +717,7 @@ __global__ void k_mirror_write(int64_t n, int n_sys, const int64_t* off,
 // 73 at 131,072), and above for its uncoalesced gathers and 7,300 VALU
 // instructions per wavefront (106 us at 262,144, 188 at 524,288, 781 on the
 // sheared 1,048,576).  With L lanes the chains are L times shorter and the
-// lists are read coalesced: 11 us (L = 16), 20 (L = 8), 47 (L = 8).  Above
+// lists are read coalesced: 9 us (L = 16), 20 (L = 8), 47 (L = 8).  Above
 // that the vector ALU bounds it (L = 4: 1,840 instructions per 16 particles,
 // 98 us of issue at 524,288) once the gathers go to the tile's sources in
 // LDS: 66, 119 and 394 us (76, 136 and 427 from the records; 71, 131 and 410
@@ -1408,7 +1409,7 @@ void launch_select_as(lp_ctx* c, const View& v, int force)
 // particles, above by k_select and k_select_rest (LP_DEBUG_SORTED_STENCIL:
 // always, every particle through the rest).  Measured, us: 131,072
 // particles 47 in one, 38 + 13 in two; 262,144 88 and 66 + 13.  16 lanes
-// against 8: 4,096 particles 11.0 and 12.1, 12,075 14.3 and 14.0.
+// against 8: 4,096 particles 9.5 and 11.1, 12,075 13.6 and 13.5.
 constexpr int64_t SELECT_L16_MAX = 8192, SELECT_FULL_MAX = 163840;
 
 bool select_in_one(const lp_ctx* c)
