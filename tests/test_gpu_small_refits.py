@@ -3,6 +3,8 @@ particles until they have met some, then a launch after each fit does.  Both
 give the same bits: steps, second-order steps and reversed steps on a context
 that has changed against one that has not, and captured sequences, captured
 anew at the change, against eager steps."""
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -24,9 +26,9 @@ def _spray(n, dens):
     return lpgen.Workload("spray", st, np.array([0, n]), [p], 1e-5, 1)
 
 
-def _changed(lp, wl):
+def _changed(lp, wl, **cfg):
     """A context that has met refits, and the state again."""
-    ctx = lp.make_context(wl)
+    ctx = lp.make_context(wl, **cfg)
     st = lp.DeviceState.from_host(wl.state)
     ctx.lp_step(st, wl.dt)
     ctx.sync_status()
@@ -37,13 +39,18 @@ def _changed(lp, wl):
 
 
 # (16,384 particles: the most that the fits refit themselves)
-@pytest.mark.parametrize("n", [1000, 10000, 16384])
-def test_steps_on_both_sides_of_the_change(lp, n):
+@pytest.mark.parametrize("n,weight,periodic", [(1000, 0, False), (10000, 0, False),
+                                               (16384, 0, False), (10000, 1, False),
+                                               (10000, 0, True), (10000, 1, True)])
+def test_steps_on_both_sides_of_the_change(lp, n, weight, periodic):
     import torch
     wl = _spray(n, 0.1)
-    print("n", n, flush=True)
-    a, sa = lp.make_context(wl), lp.DeviceState.from_host(wl.state)
-    b, sb = _changed(lp, wl)
+    if periodic:
+        side = (n / 0.1) ** (1.0 / 3.0) * wl.params[0].h
+        wl.params = [dataclasses.replace(p, box_len=(side, side)) for p in wl.params]
+    print("n", n, weight, periodic, flush=True)
+    a, sa = lp.make_context(wl, weight=weight), lp.DeviceState.from_host(wl.state)
+    b, sb = _changed(lp, wl, weight=weight)
     refits = []
     for k in range(3):
         for ctx, st in ((a, sa), (b, sb)):
